@@ -4,7 +4,7 @@
 //   F = H0 + 1/2 S (sigma_mu + sigma_nu)                        (k_fock)
 //   A = C^T F C in the current S-orthonormal basis C            (k_gemm x2)
 //   Jacobi rotations diagonalise A and rotate C                 (k_jacobi)
-//   Fermi-Dirac occupations, eps_F by bisection                 (k_fermi)
+//   Fermi-Dirac occupations                                     (k_fermi)
 //   P = C diag(n) C^T                                           (k_gemm TN)
 //   Mulliken shell charges, energy, Anderson mixing, test       (k_charges_mix)
 // Because C stays S-orthonormal, the generalized problem F C = S C eps is
@@ -1108,8 +1108,17 @@ __global__ void k_eigh_batched(const int* nvec, const long long* off, double* Ab
 }
 
 // ---------------------------------------------------------------------------
-// Fermi-Dirac occupations n_i = 2 / (1 + exp((eps_i - eF)/kT)), eF by bisection
-// so that sum n_i = N_el; also -T S_el.
+// Fermi-Dirac occupations n_i = 2 / (1 + exp((eps_i - eF)/kT)), eF such that
+// sum n_i = N_el; also -T S_el.
+//
+// The kernel is a chain of dependent reductions, bound by their latency.  A
+// bisection to 1e-15 takes some 55 of them (36 us a launch, 15% of a run of a
+// few waters); with an even number of electrons and a gap eF is the root of
+//   ln sum_virtual f - ln sum_occupied (1 - f) = 0,
+// nearly linear in eF (slope 2 / kT) and free of the cancellation that
+// sum n_i - N_el suffers inside a gap, so that Newton's method from the
+// middle of the gap takes two or three: 5 us.  Levels without a gap of 8 kT
+// (or an odd electron) keep the bisection.
 __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list) {
   int si = list[blockIdx.x];
   if (bt.status[si] != 0) return;  // converged or failed: nothing to do
@@ -1117,6 +1126,7 @@ __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list) {
   const int n = d.nao;
   const double kT = sys.g.kT;
   __shared__ double red[256];
+  __shared__ double es[MAXN];
   // (256 threads, n <= 512: each thread keeps its two eigenvalues in registers)
   const double* e = bt.eps + d.ao_off;
   constexpr int PER = MAXN / 256;
@@ -1127,24 +1137,80 @@ __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list) {
     const int i = threadIdx.x + 256 * k;
     ev[k] = i < n ? e[i] : 0.0;
     if (i < n) {
+      es[i] = ev[k];
       lo = fmin(lo, ev[k]);
       hi = fmax(hi, ev[k]);
     }
   }
-  lo = -block_max(-lo, red) - 1.0;
-  hi = block_max(hi, red) + 1.0;
-  for (int it = 0; it < 300; ++it) {
-    double mid = 0.5 * (lo + hi);
-    double loc = 0.0;
+  const int no = (int)(0.5 * d.nel + 0.5);
+  const bool even = fabs(d.nel - 2.0 * no) < 1e-9 && no >= 1 && no < n;
+  double ef = 0.0;
+  bool found = false;
+  if (even) {
+    // the no lowest levels are occupied (equal ones by index)
+    __syncthreads();
+    bool oc[PER];
+    double homo = -1e300, lumo = 1e300;
 #pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if (threadIdx.x + 256 * k < n) loc += 2.0 / (1.0 + exp((ev[k] - mid) / kT));
-    double tot = block_sum_waves(loc, red);
-    if (tot > d.nel) hi = mid;
-    else lo = mid;
-    if (hi - lo < 1e-15) break;
+    for (int k = 0; k < PER; ++k) {
+      const int i = threadIdx.x + 256 * k;
+      int rank = 0;
+      if (256 * k < n)
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) rank += es[j] < ev[k] || (es[j] == ev[k] && j < i) ? 1 : 0;
+      oc[k] = rank < no;
+      if (i < n && oc[k]) homo = fmax(homo, ev[k]);
+      if (i < n && !oc[k]) lumo = fmin(lumo, ev[k]);
+    }
+    homo = block_max_waves(homo, red);
+    lumo = -block_max_waves(-lumo, red);
+    const double gap = lumo - homo;
+    if (gap > 8.0 * kT) {
+      ef = 0.5 * (homo + lumo);
+      found = gap > 1200.0 * kT;  // (tails below 1e-260: the middle serves)
+      for (int it = 0; it < 20 && !found; ++it) {
+        // electrons above and holes below the gap, and their slopes times kT
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+          if (threadIdx.x + 256 * k < n) {
+            const double f = 1.0 / (1.0 + exp((oc[k] ? ef - ev[k] : ev[k] - ef) / kT));
+            s[0] += oc[k] ? 0.0 : f;
+            s[1] += oc[k] ? 0.0 : f * (1.0 - f);
+            s[2] += oc[k] ? f : 0.0;
+            s[3] += oc[k] ? f * (1.0 - f) : 0.0;
+          }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] = wave_sum_f64(s[c]);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0)
+          for (int c = 0; c < 4; ++c) red[4 * (threadIdx.x >> 6) + c] = s[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] = (red[c] + red[4 + c]) + (red[8 + c] + red[12 + c]);
+        const double step = -kT * log(s[0] / s[2]) / (s[1] / s[0] + s[3] / s[2]);
+        if (!(fabs(step) < gap)) break;  // (also a NaN)
+        ef += step;
+        found = fabs(step) < 1e-9 * kT;
+      }
+    }
   }
-  double ef = 0.5 * (lo + hi);
+  if (!found) {
+    lo = -block_max_waves(-lo, red) - 1.0;
+    hi = block_max_waves(hi, red) + 1.0;
+    for (int it = 0; it < 300; ++it) {
+      double mid = 0.5 * (lo + hi);
+      double loc = 0.0;
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+        if (threadIdx.x + 256 * k < n) loc += 2.0 / (1.0 + exp((ev[k] - mid) / kT));
+      double tot = block_sum_waves(loc, red);
+      if (tot > d.nel) hi = mid;
+      else lo = mid;
+      if (hi - lo < 1e-15) break;
+    }
+    ef = 0.5 * (lo + hi);
+  }
   double ts = 0.0;
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
