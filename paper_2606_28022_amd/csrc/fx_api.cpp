@@ -674,7 +674,7 @@ void Ctx::mlp_set_master(const float* w) {
 
 void Ctx::mlp_features(float* d_out) {
   if (!has_system) throw FxError(FX_E_STATE, "no system set");
-  hipLaunchKernelGGL(k_mlp_features, dim3((N + 255) / 256), dim3(256), 0, stream, dev_system(), d_out);
+  hipLaunchKernelGGL(k_mlp_features, dim3((N + 3) / 4), dim3(256), 0, stream, dev_system(), d_out);
   check(hipGetLastError(), "k_mlp_features");
 }
 
