@@ -1606,8 +1606,26 @@ void Ctx::hist_coef(const double* R, long long n, const Slots& sl, double* coef)
   hipLaunchKernelGGL(k_hist_solve, dim3(1), dim3(64), 0, stream, red_part.p, np, sl, coef);
 }
 
+void Ctx::sum_arrays(const SumArrays& a, double* out) {
+  long long total = 0;
+  for (int k = 0; k < a.n; ++k) total += a.len[k];
+  // eight terms per thread: the first stage's chains stay short
+  const int nb = (int)std::max(1LL, std::min(512LL, (total + 2047) / 2048));
+  if (red_part.n < 64LL * 36) red_part.alloc(64LL * 36);
+  hipLaunchKernelGGL(k_sum_neumaier, dim3(nb), dim3(256), 0, stream, a, red_part.p);
+  hipLaunchKernelGGL(k_sum_neumaier_final, dim3(1), dim3(256), 0, stream, (const double*)red_part.p, nb, out);
+  check(hipGetLastError(), "k_sum_neumaier");
+}
+
 void Ctx::field(const double* d_q, double* d_phi, bool fp32) {
   const DevSystem ds = dev_system();
+  if (!fp32 && ds.g.kg == 2.0 && Ne <= field_wave_max) {
+    const int ev = timers.begin(stream);
+    hipLaunchKernelGGL(k_field_wave, dim3((Ne + 3) / 4), dim3(256), 0, stream, ds, d_q, d_phi);
+    timers.end(stream, ev, kt("fx::k_field_wave"), 8e-9 * field_pairs);
+    check(hipGetLastError(), "field");
+    return;
+  }
   const int nbk = (Ne + 63) / 64;
   const long long ncol = (long long)nbk * (nbk - 1) / 2 * 128;
   if (!fp32 && ds.g.kg == 2.0 && ncol <= (1LL << 29)) {
@@ -2227,13 +2245,7 @@ void Ctx::run(fx_result* out) {
     sync();
   }
   {
-    std::vector<const double*> arr = {e_mono.p, dE_scc.p, dE_esd.p};
-    std::vector<long long> len = {F, nscc, nesd};
-    DevBuf<const double*> da;
-    da.upload(arr);
-    DevBuf<long long> dl;
-    dl.upload(len);
-    hipLaunchKernelGGL(k_sum_neumaier, dim3(1), dim3(256), 0, stream, da.p, dl.p, 3, d_scalar.p);
+    sum_arrays({3, {e_mono.p, dE_scc.p, dE_esd.p}, {F, nscc, nesd}}, d_scalar.p);
     std::vector<double> hs(1);
     d_scalar.download(hs, stream, 1);
     sync();
@@ -2261,15 +2273,9 @@ void Ctx::run(fx_result* out) {
                        (const double*)d_dEIJK.p, (const double*)dE_scc.p, nscc, (const double*)dE_esd.p,
                        (const long long*)d_sub.p, dE_tri.p);
     check(hipGetLastError(), "k_trimer_corr");
-    std::vector<const double*> arr = {d_scalar.p, dE_tri.p};
-    std::vector<long long> len = {1, ntri};
-    DevBuf<const double*> da;
-    da.upload(arr);
-    DevBuf<long long> dl;
-    dl.upload(len);
     DevBuf<double> outv;
     outv.alloc(1);
-    hipLaunchKernelGGL(k_sum_neumaier, dim3(1), dim3(256), 0, stream, da.p, dl.p, 2, outv.p);
+    sum_arrays({2, {d_scalar.p, dE_tri.p, nullptr}, {1, ntri, 0}}, outv.p);
     std::vector<double> hs(1);
     outv.download(hs, stream, 1);
     sync();

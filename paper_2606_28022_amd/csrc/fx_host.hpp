@@ -19,6 +19,7 @@
 
 #include "../../include/fmoxtb.h"
 #include "fx_device.hpp"
+#include "fx_kernels.hpp"
 
 namespace fx {
 
@@ -511,7 +512,14 @@ struct Ctx {
   DevBuf<double> red_part;
   void max_absdiff(const double* a, const double* b, int n, double* out);
   void hist_coef(const double* R, long long n, const Slots& sl, double* coef);
+  // compensated sum of the arrays into *out (device)
+  void sum_arrays(const SumArrays& a, double* out);
   void field(const double* d_q, double* d_phi, bool fp32 = false);
+  // FP64 field passes (kg = 2) of up to this many atoms by the one-launch form
+  // (a wave per target atom): a host call on 288 atoms takes 53 us by it and 96
+  // by the symmetric form, 3,456 atoms 85 and 101, 4,608 atoms 113 and 132,
+  // 5,760 atoms 144 and 136
+  int field_wave_max = std::getenv("FX_FIELD_WAVE_MAX") ? std::atoi(std::getenv("FX_FIELD_WAVE_MAX")) : 5000;
   void build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters, int nfrag_each);
   void build_matrices(Batch& b, bool from_mono = false);
   void eigh_hot(const std::vector<int>& nv, const double* A, double* w, double* V, bool global_kernel = false);

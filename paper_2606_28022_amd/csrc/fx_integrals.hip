@@ -519,6 +519,66 @@ __global__ void __launch_bounds__(256) k_field_partial_f32(DevSystem sys, const 
   }
 }
 
+// The FP64 field pass for kg = 2 of a small system: one wave per target atom,
+// lanes over the source atoms, a wave sum at the end.  Every pair is
+// evaluated from both sides, but nothing is serial: the symmetric pass below
+// walks 64 (times its source blocks) dependent steps in one wave, 47 us for
+// 384 atoms on six of the chip's CUs, and needs a second launch to add its
+// partial sums; this one takes 5 us.  The waves of a work-group share the
+// staged source atoms.
+__global__ void __launch_bounds__(256) k_field_wave(DevSystem sys, const double* q, double* phi) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = sys.natoms;
+  const int A = blockIdx.x * 4 + wave;
+  const int At = min(A, N - 1);
+  // source: position and ieta0 | ieta1, q0, q1, fragment
+  __shared__ double4 sa[256], sb[256];
+  const double xa = sys.xyz[3 * At], ya = sys.xyz[3 * At + 1], za = sys.xyz[3 * At + 2];
+  const double fa = (double)sys.frag[At];
+  const int sh0 = sys.atom_sh0[At], na = sys.atom_sh0[At + 1] - sh0;
+  const double ia0 = sys.sh_ieta[sh0], ia1 = na > 1 ? sys.sh_ieta[sh0 + 1] : 0.5;
+  double r0 = 0.0, r1 = 0.0;
+  for (int b0 = 0; b0 < N; b0 += 256) {
+    const int B = b0 + threadIdx.x;
+    if (b0 > 0) __syncthreads();
+    double4 a = make_double4(0.0, 0.0, 0.0, 0.5), b = make_double4(0.5, 0.0, 0.0, -2.0);
+    if (B < N) {
+      a.x = sys.xyz[3 * B];
+      a.y = sys.xyz[3 * B + 1];
+      a.z = sys.xyz[3 * B + 2];
+      const int s0 = sys.atom_sh0[B], ns = sys.atom_sh0[B + 1] - s0;
+      a.w = sys.sh_ieta[s0];
+      b.y = q[s0];
+      if (ns > 1) {
+        b.x = sys.sh_ieta[s0 + 1];
+        b.z = q[s0 + 1];
+      }
+      b.w = (double)sys.frag[B];
+    }
+    sa[threadIdx.x] = a;
+    sb[threadIdx.x] = b;
+    __syncthreads();
+    const int nb = min(256, N - b0);
+    for (int k = lane; k < nb; k += 64) {
+      const double4 c = sa[k], e = sb[k];
+      const double dx = xa - c.x, dy = ya - c.y, dz = za - c.z;
+      const double R2 = dx * dx + dy * dy + dz * dz;
+      const double t00 = ia0 + c.w, t01 = ia0 + e.x, t10 = ia1 + c.w, t11 = ia1 + e.x;
+      const double g0 = rsqrt_pos(R2 + t00 * t00) * e.y + rsqrt_pos(R2 + t01 * t01) * e.z;
+      const double g1 = rsqrt_pos(R2 + t10 * t10) * e.y + rsqrt_pos(R2 + t11 * t11) * e.z;
+      const bool own = e.w == fa;  // own fragment: adds exactly +0
+      r0 += own ? 0.0 : g0;
+      r1 += own ? 0.0 : g1;
+    }
+  }
+  r0 = wave_sum_f64(r0);
+  r1 = wave_sum_f64(r1);
+  if (A < N && lane == 0) {
+    phi[sh0] = r0;
+    if (na > 1) phi[sh0 + 1] = r1;
+  }
+}
+
 // Symmetric form of the FP64 field pass for kg = 2 (gamma_st = gamma_ts):
 // every inter-fragment atom pair is evaluated once and used in both
 // directions.  Atoms form blocks of 64; one wave (the whole work-group) takes

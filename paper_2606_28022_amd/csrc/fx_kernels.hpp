@@ -14,6 +14,7 @@ __global__ void k_pair_contacts(DevSystem sys, const int* frag_atoms, const int*
 __global__ void k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono);
 __global__ void k_field_partial(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_partial_f32(DevSystem sys, const double* q, int nchunk, double* part);
+__global__ void k_field_wave(DevSystem sys, const double* q, double* phi);
 __global__ void k_field_reduce(int nshells, int nchunk, const double* part, double* phi);
 __global__ void k_field_sym(DevSystem sys, const double* q, int group, int ngmax, double* rowpart, double* colpart);
 __global__ void k_field_sym_reduce(DevSystem sys, int group, int ngmax, const double* rowpart,
@@ -156,7 +157,14 @@ __global__ void k_absdiff_part(const double* a, const double* b, int n, double* 
 __global__ void k_max_reduce(const double* part, int np, double* out);
 __global__ void k_cluster_terms(DevBatch bt, const double* qmono, const double* e_mono, double* ddq, double* dEV,
                                 double* dE);
-__global__ void k_sum_neumaier(const double* const* arrays, const long long* lens, int narrays, double* out);
+// the arrays of one compensated sum
+struct SumArrays {
+  int n;
+  const double* p[3];
+  long long len[3];
+};
+__global__ void k_sum_neumaier(SumArrays a, double* part);
+__global__ void k_sum_neumaier_final(const double* part, int nparts, double* out);
 __global__ void k_hist_gram_part(const double* R, long long n, Slots sl, double* part);
 __global__ void k_hist_solve(const double* part, int np, Slots sl, double* coef);
 __global__ void k_hist_mix(const double* X, const double* R, long long n, Slots sl, const double* coef, double beta,

@@ -50,6 +50,12 @@ void Ctx::field_noalloc(const double* d_q, double* d_phi) {
   if (Nsh > FX_NOALLOC_SCRATCH_DOUBLES)
     throw FxError(FX_E_INVALID, "system has " + std::to_string(Nsh) + " shells; the allocation-free field pass "
                                 "handles at most " + std::to_string((long long)FX_NOALLOC_SCRATCH_DOUBLES));
+  if (Ne <= field_wave_max && P.g.kg == 2.0) {
+    // small systems: the one-launch form, which has no partial sums
+    hipLaunchKernelGGL(k_field_wave, dim3((Ne + 3) / 4), dim3(256), 0, stream, dev_system(), d_q, d_phi);
+    check(hipGetLastError(), "field (no allocation)");
+    return;
+  }
   double* part = noalloc_scratch(device);
   // as many source chunks as the scratch holds, at most those of the
   // allocating pass
