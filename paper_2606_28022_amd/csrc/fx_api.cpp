@@ -387,6 +387,18 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
   b.occ.alloc(ao_off);
   b.occ_idx.alloc(ao_off);
   b.occ_cnt.alloc(ns);
+  b.mode.alloc(ns);
+  b.ov_no.alloc(ns);
+  b.ov_idx.alloc(ao_off);
+  b.xn.alloc(ns);
+  b.xpart.alloc(16LL * ns);
+  b.max_occ = 0;
+  b.max_ovb = 0;
+  for (const SysDesc& d : b.h_desc) {
+    const int no = (int)std::ceil(0.5 * d.nel);
+    b.max_occ = std::max(b.max_occ, no);
+    b.max_ovb = std::max(b.max_ovb, (no + 15) / 16 + (std::max(0, d.nao - no) + 15) / 16);
+  }
   b.erep.alloc(ns);
   b.e_int.alloc(ns);
   b.e_prev.alloc(ns);
@@ -443,6 +455,10 @@ DevBatch Batch::dev() {
   d.occ = occ.p;
   d.occ_idx = occ_idx.p;
   d.occ_cnt = occ_cnt.p;
+  d.mode = mode.p;
+  d.ov_no = ov_no.p;
+  d.ov_idx = ov_idx.p;
+  d.xn = xn.p;
   d.erep = erep.p;
   d.e_int = e_int.p;
   d.e_prev = e_prev.p;
@@ -491,6 +507,10 @@ void Ctx::init_device() {
                         reinterpret_cast<const void*>(k_cholinv_lds<float>),
                         reinterpret_cast<const void*>(k_cholinv_block2)})
     (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+  for (const void* k : {reinterpret_cast<const void*>(k_ov_grad), reinterpret_cast<const void*>(k_ov_apply<1, 2>),
+                        reinterpret_cast<const void*>(k_ov_apply<1, 3>),
+                        reinterpret_cast<const void*>(k_ov_apply<2, 2>)})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ov_apply_lds_bytes(OV_MAXN, 2));
   (void)hipGetLastError();
   check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device), "CU count query");
   noalloc_init(device);
@@ -849,6 +869,7 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
   b.Tm.alloc(mat);
   b.eps.alloc(ao);
   b.status.upload(std::vector<int>(nmat, 0));
+  b.mode.upload(std::vector<int>(nmat, 0));  // (the eigensolver's kernels skip systems in rotation mode)
   b.err.upload(std::vector<double>(nmat, 0.0));
   b.sweeps.alloc(nmat);
   std::vector<int> all(nmat);
@@ -932,8 +953,10 @@ void Ctx::build_matrices(Batch& b, bool from_mono) {
 // otherwise the eigenvectors of the previous solve are reused.
 // Returns the number of systems that failed to converge.
 // single: exactly one iteration (no mixing, no convergence test), used by
-// the fused monomer loop; the previous residual is kept for the eigensolver.
-int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single) {
+// the fused monomer loop; the previous residual is kept for the eigensolver,
+// and each system goes on by the route of its last iteration (refresh: all by
+// the eigensolver).
+int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single, bool refresh) {
   if (list.empty()) return 0;
   const double t_start = now_ms();
   DevBatch db = b.dev();
@@ -942,7 +965,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   // reset per-system iteration state on the device
   b.d_list.upload(list);
   hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl,
-                     single ? 1 : 0);
+                     single ? 1 : 0, cold || refresh ? 1 : single ? 2 : 0);
   check(hipGetLastError(), "k_reset_state");
   if (cold) {
     const int nt = (b.max_nao + 31) / 32;
@@ -1059,9 +1082,10 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
                         8 * m4 <= 2 * 64 * apply_rot_waves(b.max_nao);
   // cold solve by the split form (not in the mixed-precision form, whose
   // cold iteration builds only the FP32 Fock matrix)
+  // warm iterations of gapped systems by occupied-virtual rotations
+  const bool ov = ov_batch(b) && split_ok;
   const bool cold_split = split_ok && jacobi_cold_log > 0 && cold && !b.init_from_mono && !(b.has_f32 && prod_mode != 0);
   const long long cold_stride = (long long)jacobi_cold_log * jacobi_rot_log_entries(b.max_nao);
-  DevBuf<int> cold_list;
   if (split_ok) {
     b.rotlog.alloc((long long)b.nsys * (cold_split ? std::max(log_stride, cold_stride) : log_stride));
     b.nlog.alloc(b.nsys);
@@ -1083,8 +1107,9 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   DevBuf<int> d_switched;
   // one SCC iteration over the na systems listed in dl, of which the first
   // n32 run the FP32 Fock build and products (mixed precision)
+  // (all_eig: every listed system takes the eigensolver; some_eig: some may)
   auto launch_iteration = [&](const std::vector<int>& act, const int* dl, int na, int n32, double cap,
-                              bool timed) {
+                              bool timed, bool all_eig, bool some_eig) {
     const int n64 = na - n32;
     const int* dl64 = dl + n32;
     const std::vector<int> a32(act.begin(), act.begin() + n32), a64(act.begin() + n32, act.end());
@@ -1096,14 +1121,20 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     }
     if (n64 > 0) {
       hipLaunchKernelGGL(k_fock, dim3(n64), dim3(256), 0, stream, ds, db, dl64);
-      // A = C^T F C in the current basis, then Jacobi rotations
-      gemm_batch(b, db, n64, dl64, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(a64), 1);
-      // A = (C^T F) C is symmetric: upper tiles only, mirrored unless the
-      // eigensolver is an LDS kernel (those read the upper triangle only)
-      gemm_batch(b, db, n64, dl64, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(a64), 1, sym_A);
+      if (ov && !all_eig) launch_ov(b, db, dl64, n64);
+      if (some_eig) {
+        const int skip = ov ? 3 : 1;
+        // A = C^T F C in the current basis, then Jacobi rotations
+        gemm_batch(b, db, n64, dl64, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(a64), skip);
+        // A = (C^T F) C is symmetric: upper tiles only, mirrored unless the
+        // eigensolver is an LDS kernel (those read the upper triangle only)
+        gemm_batch(b, db, n64, dl64, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(a64), skip, sym_A);
+      }
     }
-    if (split_ok && cap < 1e299) {
-      const RotShape rs = rot_shape(b, db, dl, na, jp, cap, log_stride, timed);
+    if (!some_eig) {
+      last_split = true;
+    } else if (split_ok && cap < 1e299) {
+      const RotShape rs = rot_shape(b, db, dl, na, jp, cap, log_stride, timed && (all_eig || !ov));
       int ev = timed ? timers.begin(stream) : -1;
       launch_rot(b, db, dl, na, jp.elt, cap, rs, log_stride);
       if (timed) timers.end(stream, ev, kt_rot, 0.0);
@@ -1117,33 +1148,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       // is done, the others start the next pass from C^T F C in the basis
       // this pass left (the Fock matrix is rebuilt: the products overwrite
       // it).  The launch shape is not tuned here but on a warm iteration.
-      const RotShape rs = rot_shape(b, db, dl, na, jp, cap, cold_stride, false);
-      std::vector<int> todo(na), nlog;
-      check(hipMemcpyAsync(todo.data(), dl, sizeof(int) * na, hipMemcpyDeviceToHost, stream), "list copy");
-      const int* dt = dl;
-      const int max_pass = (jacobi_max_sweeps + jacobi_cold_log - 1) / jacobi_cold_log;
-      for (int pass = 0; pass < max_pass && !todo.empty(); ++pass) {
-        const int nt = (int)todo.size();
-        if (pass > 0) {
-          cold_list.upload(todo);
-          dt = cold_list.p;
-          hipLaunchKernelGGL(k_fock, dim3(nt), dim3(256), 0, stream, ds, db, dt);
-          gemm_batch(b, db, nt, dt, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, 0.0, 1);
-          gemm_batch(b, db, nt, dt, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, 0.0, 1, sym_A);
-        }
-        int ev = timed ? timers.begin(stream) : -1;
-        launch_rot(b, db, dt, nt, jp.elt, cap, rs, cold_stride, jacobi_cold_log);
-        if (timed) timers.end(stream, ev, kt_rot, 0.0);
-        ev = timed ? timers.begin(stream) : -1;
-        launch_apply(b, db, dt, nt, cold_stride);
-        if (timed) timers.end(stream, ev, kt_app, 0.0);
-        b.nlog.download(nlog, stream);
-        sync();
-        std::vector<int> next;
-        for (int s : todo)
-          if (nlog[s] >= jacobi_cold_log) next.push_back(s);
-        todo.swap(next);
-      }
+      rot_passes(b, db, dl, na, jp, cap, rot_shape(b, db, dl, na, jp, cap, cold_stride, false), cold_stride, timed);
       last_split = true;
     } else {
       last_split = false;
@@ -1159,7 +1164,10 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
                          jacobi_thr_scale, cap, b.sweeps.p);
     if (timed) timers.end(stream, ev, kt_jac, 0.0);
     }
-    hipLaunchKernelGGL(k_fermi, dim3(na), dim3(256), 0, stream, ds, db, dl);
+    if (some_eig) {
+      if (n32 > 0) hipLaunchKernelGGL(k_fermi, dim3(n32), dim3(256), 0, stream, ds, db, dl, 0);
+      if (n64 > 0) hipLaunchKernelGGL(k_fermi, dim3(n64), dim3(256), 0, stream, ds, db, dl64, ov ? 1 : 0);
+    }
     if (n32 > 0)
       gemm_batch_f32(b, db, n32, dl, 2, b.Ct.p, b.Ct.p, b.Pm.p, b.occ.p, b.gemm_gflop_occ(a32), 1, 1, true);
     if (n64 > 0)
@@ -1169,10 +1177,10 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     // a system converges only in an FP64 iteration
     const double beta = b.has_pre ? precond_beta : mix_beta;
     if (n32 > 0)
-      hipLaunchKernelGGL(k_charges_mix, dim3(n32), dim3(256), 0, stream, ds, db, dl, -1.0, -1.0,
+      hipLaunchKernelGGL(k_charges_mix, dim3(n32), dim3(256), 0, stream, ds, db, dl, 1, -1.0, -1.0,
                          single ? 1 : opt.max_iter, beta);
     if (n64 > 0)
-      hipLaunchKernelGGL(k_charges_mix, dim3(n64), dim3(256), 0, stream, ds, db, dl64,
+      hipLaunchKernelGGL(k_charges_mix, dim3(n64), dim3(256), 0, stream, ds, db, dl64, some_eig ? 1 : 0,
                          scc_tol_cur > 0 ? scc_tol_cur : opt.scc_tol, etol_cur > 0 ? etol_cur : opt.energy_tol,
                          single ? 1 : opt.max_iter, beta);
     check(hipGetLastError(), "scc iteration");
@@ -1190,6 +1198,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   // converged systems in the slots beyond it return at once)
   const bool async = opt.schedule == FX_BATCHED && !single && !f32_ok && !verbose && split_ok;
   int ub = nl;
+  int neig = 1;  // systems that the eigensolver takes next, by the latest count
   std::deque<int> pending;
   const std::vector<int> no_list;
   if (async) {
@@ -1223,7 +1232,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         stream = gstream;
         capturing = true;
         check(hipStreamBeginCapture(gstream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-        launch_iteration(list, b.d_list.p, nl, 0, jacobi_cap_err, false);
+        launch_iteration(list, b.d_list.p, nl, 0, jacobi_cap_err, false, false, true);
         const hipError_t ec = hipStreamEndCapture(gstream, &graph);
         capturing = false;
         stream = saved;
@@ -1245,7 +1254,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     }
     if (async) {
       if (want_tune(it)) tune_fused(d_act.p, ub, cap);
-      launch_iteration(no_list, d_act.p, ub, 0, cap, true);
+      launch_iteration(no_list, d_act.p, ub, 0, cap, true, it == 0, it == 0 || neig != 0);
       if (first_solve && it == 0) {
         // median first-iteration residual over the batch (all listed systems
         // took part in iteration 0)
@@ -1265,9 +1274,9 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       }
       const int slot = it % CNT_RING;
       hipLaunchKernelGGL(k_compact_active, dim3(1), dim3(1024), 0, stream, (const int*)b.status.p,
-                         (const int*)b.d_list.p, nl, d_act.p, cnt_dev.p + slot);
+                         (const int*)b.mode.p, (const int*)b.d_list.p, nl, d_act.p, cnt_dev.p + 2 * slot);
       check(hipGetLastError(), "k_compact_active");
-      check(hipMemcpyAsync(cnt_host + slot, cnt_dev.p + slot, sizeof(int), hipMemcpyDeviceToHost, stream),
+      check(hipMemcpyAsync(cnt_host + 2 * slot, cnt_dev.p + 2 * slot, 2 * sizeof(int), hipMemcpyDeviceToHost, stream),
             "count copy");
       check(hipEventRecord(cnt_ev[slot], stream), "hipEventRecord");
       pending.push_back(slot);
@@ -1285,7 +1294,8 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         } else {
           check(hipEventSynchronize(cnt_ev[k]), "hipEventSynchronize");
         }
-        ub = std::min(ub, cnt_host[k]);
+        ub = std::min(ub, cnt_host[2 * k]);
+        neig = cnt_host[2 * k + 1];
         pending.pop_front();
       }
       if (ub == 0) break;
@@ -1310,7 +1320,8 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       switched.clear();
     }
     if (want_tune(it)) tune_fused(d_act.p, na, cap);
-    launch_iteration(active, d_act.p, na, n32, cap, true);
+    launch_iteration(active, d_act.p, na, n32, cap, true, it == 0 && !(single && !refresh),
+                     !single || refresh || mono_eig || !ov);
     res.iters_fp32 += n32;
     if (first_solve && it == 0) {
       // median first-iteration residual over the batch
@@ -1385,6 +1396,15 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     hipLaunchKernelGGL(k_mirror_tiles, dim3(nl), dim3(256), 0, stream, db, (const int*)b.d_list.p, b.Pm.p);
     check(hipGetLastError(), "k_mirror_tiles");
   }
+  DevBuf<int> d_open;
+  std::vector<int> open(1, 0), modes;
+  if (ov && !single) {
+    d_open.upload(open);
+    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(256), 0, stream, db, (const int*)b.d_list.p, P.g.kT, d_open.p);
+    check(hipGetLastError(), "k_ov_gap");
+    d_open.download(open, stream);
+    b.mode.download(modes, stream);
+  }
   b.status.download(status, stream);
   b.niter.download(niter, stream);
   sync();
@@ -1398,13 +1418,21 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     for (int s : list) {
       const int its = niter[s];
       if (its <= 0) continue;
-      const int n_full = cold_full ? 1 : 0, n_split = its - n_full;
+      const int n_full = cold_full ? 1 : 0;
+      // (a system on the rotation route had the eigensolver once, at the start)
+      const int n_rot = ov && modes[s] == 1 ? its - 1 : 0, n_split = its - n_full - n_rot;
       const double n = b.h_desc[s].nao, n3 = 1e-9 * n * n * n;
       kt_jac->gflop += 3.3 * n3 * n_full;
       kt_rot->gflop += 1.3 * n3 * n_split;
       kt_app->gflop += 2.0 * n3 * n_split;
       const std::vector<int> one{s};
-      kt_g->gflop += its * (b.gemm_gflop(one) + b.gemm_gflop_sym(one) + b.gemm_gflop_occ(one));
+      kt_g->gflop += (its - n_rot) * (b.gemm_gflop(one) + b.gemm_gflop_sym(one)) + its * b.gemm_gflop_occ(one);
+      if (n_rot > 0) {
+        // C_o F and C_v (C_o F)^T; two products with the rotation
+        const double no = std::ceil(0.5 * b.h_desc[s].nel), nv = n - no;
+        kt("fx::k_ov_grad")->gflop += 2e-9 * n_rot * (n * n * no + n * no * nv);
+        kt("fx::k_ov_apply")->gflop += 8e-9 * n_rot * n * no * nv;
+      }
     }
   }
   if (verbose) {
@@ -1422,12 +1450,120 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   }
   int failed = 0;
   long long iters = 0;
+  std::vector<int> again;
   for (int s : list) {
-    if (status[s] != 1) ++failed;
+    if (status[s] == 0 && open[0] > 0) again.push_back(s);
+    else if (status[s] != 1) ++failed;
     iters += niter[s];
   }
   if (iters_out) *iters_out += iters;
+  // (systems whose gap closed on the way: the eigensolver from here on)
+  if (!again.empty()) failed += run_scc(b, again, false, iters_out);
   return single ? 0 : failed;
+}
+
+// Passes of up to jacobi_cold_log logged sweeps over the na systems listed in
+// dl, whose A = C^T F C is in F; a system whose pass ended on a sweep without
+// rotations (fewer logged sweeps than the pass allows) is done, the others
+// start the next pass from C^T F C in the basis this pass left (the Fock
+// matrix is rebuilt: the products overwrite it).
+void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
+                     const RotShape& rs, long long stride, bool timed) {
+  const DevSystem ds = dev_system();
+  KernelTimer* kt_rot = kt(jp.elt == 8 ? "fx::k_jacobi_rot<double>" : "fx::k_jacobi_rot<float>");
+  KernelTimer* kt_app = kt(apply_dual(b.max_nao) ? "fx::k_apply_rot_dual" : "fx::k_apply_rot");
+  const int sym_A = jp.elt != 0 ? 2 : 1;
+  std::vector<int> todo(na), nlog;
+  check(hipMemcpyAsync(todo.data(), dl, sizeof(int) * na, hipMemcpyDeviceToHost, stream), "list copy");
+  const int* dt = dl;
+  DevBuf<int> pass_list;
+  const int max_pass = (jacobi_max_sweeps + cold_log() - 1) / cold_log();
+  for (int pass = 0; pass < max_pass && !todo.empty(); ++pass) {
+    const int nt = (int)todo.size();
+    if (pass > 0) {
+      pass_list.upload(todo);
+      dt = pass_list.p;
+      hipLaunchKernelGGL(k_fock, dim3(nt), dim3(256), 0, stream, ds, db, dt);
+      gemm_batch(b, db, nt, dt, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, 0.0, 1);
+      gemm_batch(b, db, nt, dt, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, 0.0, 1, sym_A);
+    }
+    int ev = timed ? timers.begin(stream) : -1;
+    launch_rot(b, db, dt, nt, jp.elt, cap, rs, stride, cold_log());
+    if (timed) timers.end(stream, ev, kt_rot, 0.0);
+    ev = timed ? timers.begin(stream) : -1;
+    launch_apply(b, db, dt, nt, stride);
+    if (timed) timers.end(stream, ev, kt_app, 0.0);
+    b.nlog.download(nlog, stream);
+    sync();
+    std::vector<int> next;
+    for (int s : todo)
+      if (nlog[s] >= cold_log()) next.push_back(s);
+    todo.swap(next);
+  }
+}
+
+// One rotation of the basis of the listed systems in rotation mode: X into P
+// (the density product overwrites it), then the rows of C^T.
+void Ctx::launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na) {
+  const int tg = std::max(1, (b.max_occ + OV_ROWS - 1) / OV_ROWS);
+  // 32 columns of C^T per work-group where the batch then still covers the
+  // chip twice, else 16 (8 pentacene dimers: 64 against 120 work-groups)
+  // (16 too for three row blocks per wave: 32 columns would not fit in the
+  // registers of two work-groups per CU)
+  const bool wide = b.max_ovb <= 2 * OV_WAVES && (long long)na * ((b.max_nao + 31) / 32) >= 2LL * n_cu;
+  const int ta = wide ? (b.max_nao + 31) / 32 : (b.max_nao + 15) / 16;
+  const bool timed = !capturing;
+  int ev = timed ? timers.begin(stream) : -1;
+  hipLaunchKernelGGL(k_ov_grad, dim3((unsigned)xcd_grid(na, tg)), dim3(64 * OV_WAVES), ov_grad_lds_bytes(b.max_nao),
+                     stream, db, dl, na, tg, b.Pm.p, b.xpart.p);
+  if (timed) timers.end(stream, ev, kt("fx::k_ov_grad"), 0.0);
+  ev = timed ? timers.begin(stream) : -1;
+  auto* apply = wide ? k_ov_apply<2, 2> : b.max_ovb <= 2 * OV_WAVES ? k_ov_apply<1, 2> : k_ov_apply<1, 3>;
+  hipLaunchKernelGGL(apply, dim3((unsigned)xcd_grid(na, ta)), dim3(64 * OV_WAVES),
+                     ov_apply_lds_bytes(b.max_nao, wide ? 2 : 1), stream, db, dl, na, ta, (const double*)b.Pm.p,
+                     (const double*)b.xpart.p);
+  if (timed) timers.end(stream, ev, kt("fx::k_ov_apply"), 0.0);
+  check(hipGetLastError(), "orbital rotation");
+}
+
+bool Ctx::canonical_basis(Batch& b) {
+  if (!ov_batch(b) || b.nsys == 0) return true;
+  std::vector<double> xn;
+  b.xn.download(xn, stream);
+  sync();
+  std::vector<int> l;
+  for (int s = 0; s < b.nsys; ++s)
+    if (xn[s] >= 0.0) l.push_back(s);
+  if (l.empty()) return true;
+  const int nl = (int)l.size();
+  DevBatch db = b.dev();
+  DevSystem ds = dev_system();
+  b.d_list.upload(l);
+  hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl, 1, 0);
+  JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);
+  auto itp = tuned.find(jp_key(b.max_nao, jp.elt));
+  if (itp != tuned.end()) jp = itp->second;
+  const long long stride =
+      (long long)std::max(jacobi_max_log, cold_log()) * jacobi_rot_log_entries(b.max_nao);
+  b.rotlog.alloc((long long)b.nsys * stride);
+  b.nlog.alloc(b.nsys);
+  // (F holds the last iteration's Fock matrix)
+  gemm_batch(b, db, nl, b.d_list.p, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(l), 1);
+  gemm_batch(b, db, nl, b.d_list.p, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(l), 1, jp.elt != 0 ? 2 : 1);
+  rot_passes(b, db, b.d_list.p, nl, jp, 1e300, rot_shape(b, db, b.d_list.p, nl, jp, 1e300, stride, false), stride, true);
+  hipLaunchKernelGGL(k_fermi, dim3(nl), dim3(256), 0, stream, ds, db, b.d_list.p, 1);
+  check(hipGetLastError(), "canonical basis");
+  std::vector<int> mode;
+  b.mode.download(mode, stream);
+  sync();
+  bool gapped = true;
+  for (int s : l)
+    if (mode[s] != 1) {
+      mode[s] = 2;
+      gapped = false;
+    }
+  if (!gapped) b.mode.upload(mode);
+  return gapped;
 }
 
 // The rotation kernel over the na systems listed in dl, one work-group per
@@ -1531,10 +1667,10 @@ Ctx::RotShape Ctx::rot_shape(Batch& b, const DevBatch& db, const int* dl, int na
 
 void Ctx::count_ring_init() {
   if (cnt_host) return;
-  if (cnt_dev.n < CNT_RING) cnt_dev.alloc(CNT_RING);
+  if (cnt_dev.n < 2 * CNT_RING) cnt_dev.alloc(2 * CNT_RING);
   cnt_ev.assign(CNT_RING, nullptr);
   for (auto& e : cnt_ev) check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
-  check(hipHostMalloc((void**)&cnt_host, sizeof(int) * CNT_RING, hipHostMallocDefault), "hipHostMalloc");
+  check(hipHostMalloc((void**)&cnt_host, sizeof(int) * 2 * CNT_RING, hipHostMallocDefault), "hipHostMalloc");
 }
 
 // Automatic retry of the systems of a cluster batch whose SCC did not
@@ -1592,11 +1728,11 @@ int Ctx::solve_batch(Batch& b, bool cold, long long* iters_out) {
   return failed;
 }
 
-void Ctx::max_absdiff(const double* a, const double* b, int n, double* out) {
+void Ctx::max_absdiff(const double* a, const double* b, int n, double* out, const double* extra, int nextra) {
   const int np = std::max(1, std::min(64, (n + 2047) / 2048));
   if (red_part.n < 64LL * 36) red_part.alloc(64LL * 36);
   hipLaunchKernelGGL(k_absdiff_part, dim3(np), dim3(256), 0, stream, a, b, n, red_part.p);
-  hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(256), 0, stream, red_part.p, np, out);
+  hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(256), 0, stream, red_part.p, np, extra, nextra, out);
 }
 
 void Ctx::hist_coef(const double* R, long long n, const Slots& sl, double* coef) {
@@ -2007,6 +2143,10 @@ void Ctx::run(fx_result* out) {
   std::vector<int> all_mono(mb.nsys);
   for (int k = 0; k < mb.nsys; ++k) all_mono[k] = k;
   bool fused_mode = false;
+  // (the first fused step diagonalises: the first solve's rotations started
+  // from the superposition field's orbitals)
+  bool refresh = true;
+  mono_eig = true;
   // mixed precision: FP32 field passes until the monomer charges move by
   // less than 1e-6, FP64 from then on (the fixed point is the FP64 one)
   bool field32 = mixed;
@@ -2024,7 +2164,8 @@ void Ctx::run(fx_result* out) {
       hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_q.p, mb.q_in.p);
       // (FP64 products in the fused steps: FP32 ones there cost more steps
       // than they save)
-      run_scc(mb, all_mono, false, &it_mono, true);
+      run_scc(mb, all_mono, false, &it_mono, true, refresh);
+      refresh = false;
     } else {
       if (cold)
         hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_q.p, mb.q_in.p);
@@ -2056,15 +2197,28 @@ void Ctx::run(fx_result* out) {
     cold = false;
     res.solves_mono += mb.nsys;
     hipLaunchKernelGGL(k_scatter_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, mb.q_out.p, d_qnew.p);
-    max_absdiff(d_qnew.p, d_q.p, Nsh, d_scalar.p);
-    std::vector<double> hs(1);
-    d_scalar.download(hs, stream, 1);
+    max_absdiff(d_qnew.p, d_q.p, Nsh, d_scalar.p, mb.xn.p, mb.nsys);
+    std::vector<double> hs(2);
+    d_scalar.download(hs, stream, 2);
+    std::vector<int> modes;
+    const bool ov = ov_batch(mb) && fused_mode;
+    if (ov && mono_eig) mb.mode.download(modes, stream);
     sync();
     delta = hs[0];
+    if (ov) {
+      // a rotation leaves the orbitals up to a fifth of |X| behind
+      delta = std::max(delta, 0.2 * hs[1]);
+      if (mono_eig)
+        mono_eig = std::any_of(modes.begin(), modes.end(), [](int m) { return m != 1; });
+      else
+        mono_eig = hs[1] > OV_XMAX;
+    }
     if (verbose)
       std::fprintf(stderr, "[fx] monomer %s %d: max |dq_out - dq_in| = %.3e, %.1f ms\n",
                    fused_mode ? "step" : "sweep", macro, delta, now_ms() - t1);
-    if (delta < opt.macro_tol) {
+    if (delta < opt.macro_tol && !canonical_basis(mb)) {
+      mono_eig = true;  // a gap closed on the way: on with the eigensolver
+    } else if (delta < opt.macro_tol) {
       if (failed) all_conv = false;
       check(hipMemcpyAsync(d_q.p, d_qnew.p, sizeof(double) * Nsh, hipMemcpyDeviceToDevice, stream), "copy");
       break;
@@ -2106,6 +2260,7 @@ void Ctx::run(fx_result* out) {
   if (macro > opt.max_macro) {
     all_conv = false;
     macro = opt.max_macro;
+    (void)canonical_basis(mb);
   }
   res.macro_iter = macro;
   res.iters_mono = it_mono;

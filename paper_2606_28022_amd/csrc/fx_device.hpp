@@ -114,6 +114,15 @@ struct DevBatch {
   int* nhist;
   int* occ_idx;  // [ao_off + k]: the orbitals whose occupation exceeds OCC_MIN, ascending
   int* occ_cnt;  // per system: their number
+  // occupied-virtual rotations (fx_orb.hip): route of the next iteration
+  // (0 eigensolver, 1 rotation, 2 eigensolver for the rest of the solve), the
+  // occupied orbitals' number, their indices followed by the virtual ones',
+  // and |X| of the last iteration (-1: it was an eigensolver's, so F holds
+  // C^T F C and the basis is canonical)
+  int* mode;
+  int* ov_no;
+  int* ov_idx;   // [ao_off + k]
+  double* xn;
 };
 // occupations below this bound are left out of the density product: each
 // such term changes an element of P by less than 1e-30, far below the FP64

@@ -36,9 +36,28 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
   // occupation list, whose weights n eps vanish with n), D_S into F
   std::vector<int> all_sys(b.nsys);
   for (int k = 0; k < b.nsys; ++k) all_sys[k] = k;
-  c.gemm_batch(b, db, (int)b.nsys, b.d_list.p, 2, b.Ct.p, b.Ct.p, b.Tm.p, (const double*)wvec.p,
-               b.gemm_gflop_occ(all_sys), 0, 1, true);
-  hipLaunchKernelGGL(k_make_DS, dim3(b.nsys), dim3(256), 0, c.stream, db, b.Pm.p, b.Tm.p, b.Fm.p);
+  // (systems whose last iteration rotated the orbitals have no eigenvalues of
+  // this F, which is still in F: 2 W = P F P over it)
+  std::vector<int> rot;
+  if (c.ov_batch(b)) {
+    std::vector<double> xn;
+    b.xn.download(xn, c.stream);
+    c.sync();
+    std::vector<int> eig;
+    for (int k = 0; k < b.nsys; ++k) (xn[k] >= 0.0 ? rot : eig).push_back(k);
+    if (!rot.empty()) {
+      all_sys = eig;
+      all = eig;
+      all.insert(all.end(), rot.begin(), rot.end());
+      b.d_list.upload(all);
+    }
+  }
+  const int ne = (int)all_sys.size(), nr = (int)rot.size();
+  c.gemm_batch(b, db, ne, b.d_list.p, 2, b.Ct.p, b.Ct.p, b.Tm.p, (const double*)wvec.p, b.gemm_gflop_occ(all_sys), 0,
+               1, true);
+  c.gemm_batch(b, db, nr, b.d_list.p + ne, 0, b.Pm.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(rot));
+  c.gemm_batch(b, db, nr, b.d_list.p + ne, 1, b.Tm.p, b.Pm.p, b.Fm.p, nullptr, b.gemm_gflop_sym(rot), 0, 1);
+  hipLaunchKernelGGL(k_make_DS, dim3(b.nsys), dim3(256), 0, c.stream, db, b.Pm.p, b.Tm.p, b.Fm.p, nr > 0 ? 1 : 0);
   if (b.has_hop)
     hipLaunchKernelGGL(k_hop_grad, dim3(b.nsys), dim3(256), 0, c.stream, ds, db, (const double*)b.Pm.p, b.Fm.p, wsys,
                        (const int*)c.d_bonds.p, c.P.g.VHOP, slot_base, hop_f);

@@ -756,15 +756,19 @@ __global__ void k_final_shift(DevSystem sys, DevBatch bt, double* wvec) {
 }
 
 // D_S = 1/2 (sigma_mu + sigma_nu) P - W  (eq. W_matrix with the embedding in sigma)
-__global__ void k_make_DS(DevBatch bt, const double* P, const double* W, double* out) {
+// (rotated: a system whose last iteration was an orbital rotation has
+// P F P = 2 W in out instead of W)
+__global__ void k_make_DS(DevBatch bt, const double* P, const double* W, double* out, int rotated) {
   const int si = blockIdx.x;
+  const bool half = rotated && bt.xn[si] >= 0.0;
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
   const int* aosh = bt.sys_ao_sh + d.ao_off;
   const double* sg = bt.sig + d.sh_off;
   for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
     int i = (int)(idx / n), j = (int)(idx % n);
-    out[d.mat_off + idx] = 0.5 * (sg[aosh[i]] + sg[aosh[j]]) * P[d.mat_off + idx] - W[d.mat_off + idx];
+    const double w = half ? 0.5 * out[d.mat_off + idx] : W[d.mat_off + idx];
+    out[d.mat_off + idx] = 0.5 * (sg[aosh[i]] + sg[aosh[j]]) * P[d.mat_off + idx] - w;
   }
 }
 

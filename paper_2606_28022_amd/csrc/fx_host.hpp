@@ -244,6 +244,8 @@ HostParams load_params(const std::string& path);
 struct Batch {
   int nsys = 0;
   int max_nao = 0;
+  int max_occ = 0;  // largest ceil(N_el / 2)
+  int max_ovb = 0;  // largest number of 16-row blocks of the occupied and virtual orbitals
   // what the tables were last built for (build_batch keeps them when the
   // same clusters of the same system come again)
   std::vector<std::array<int, 3>> h_clusters;
@@ -259,6 +261,8 @@ struct Batch {
   DevBuf<int> d_atoms, d_atom_ao0, d_atom_sh0, d_sh_global, d_sh_atom, d_ao_sh, d_all, d_list;
   DevBuf<double> S, H0, Fm, Ct, Pm, Tm, gam, q_in, q_out, phi, sig, hx, hr, eps, occ;
   DevBuf<int> occ_idx, occ_cnt;  // significant orbitals of the last occupation (k_fermi)
+  DevBuf<int> mode, ov_no, ov_idx;  // occupied-virtual rotations (DevBatch)
+  DevBuf<double> xn, xpart;
   DevBuf<double> erep, e_int, e_prev, mts, err;
   DevBuf<int> status, niter, nhist, sweeps;
   // Newton preconditioner (1 + M G)^-1 of the Anderson residuals (FP32,
@@ -507,10 +511,11 @@ struct Ctx {
                   const int32_t* fchg, int32_t n_bonds, const int32_t* bonds);
   void build_lists_impl();
   void compute_cn();
-  // max |a - b| over n entries into *out (device), and the Anderson mixing
+  // max |a - b| over n entries into out[0] (device), with extra its largest
+  // entry into out[1], and the Anderson mixing
   // coefficients of the history residuals R (slots sl, n entries each)
   DevBuf<double> red_part;
-  void max_absdiff(const double* a, const double* b, int n, double* out);
+  void max_absdiff(const double* a, const double* b, int n, double* out, const double* extra = nullptr, int nextra = 0);
   void hist_coef(const double* R, long long n, const Slots& sl, double* coef);
   // compensated sum of the arrays into *out (device)
   void sum_arrays(const SumArrays& a, double* out);
@@ -539,6 +544,7 @@ struct Ctx {
   // C^T F C, until every system has had a sweep without rotations
   // (FX_JACOBI_COLD_LOG=0: the fused kernel)
   int jacobi_cold_log = std::getenv("FX_JACOBI_COLD_LOG") ? std::atoi(std::getenv("FX_JACOBI_COLD_LOG")) : 8;
+  int cold_log() const { return jacobi_cold_log > 0 ? jacobi_cold_log : 8; }
   std::map<long long, JacobiPlan> tuned;
   static long long jp_key(int n, int elt) { return (long long)n * 16 + elt; }
   // launch shape of the rotation kernel per size bucket: work-group size and
@@ -561,6 +567,23 @@ struct Ctx {
   // (FX_APPLY_DUAL=0: the one-quartet kernel everywhere)
   bool apply_dual_on = !(std::getenv("FX_APPLY_DUAL") && std::atoi(std::getenv("FX_APPLY_DUAL")) == 0);
   bool apply_dual(int max_nao) const { return apply_dual_on && max_nao > 128 && max_nao <= 256; }
+  // occupied-virtual rotations in place of the warm eigensolves of gapped
+  // systems (FX_OV=0: the eigensolver throughout).  Not with hybrid-orbital
+  // projectors, whose 1e6 Eh leave rounding of 1e-10 in the couplings; not for
+  // systems within one 32 x 32 tile, whose Jacobi sweeps cost less than the
+  // launches; up to 256 AOs by the kernels' LDS and register tiles.
+  bool ov_on = !(std::getenv("FX_OV") && std::atoi(std::getenv("FX_OV")) == 0);
+  bool ov_batch(const Batch& b) const { return ov_on && !b.has_hop && b.max_nao > 32 && b.max_nao <= OV_MAXN; }
+  // monomer loop: whether some monomer's next iteration is an eigensolver's
+  bool mono_eig = true;
+  void launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na);
+  // eigenvectors and eigenvalues of the systems of b whose last iteration was
+  // a rotation; false when one of them has no gap any more (it is then left to
+  // the eigensolver, mode 2)
+  bool canonical_basis(Batch& b);
+  // passes of logged sweeps to convergence (cold solves by the split form)
+  void rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
+                  const RotShape& rs, long long stride, bool timed);
   void launch_apply(const Batch& b, const DevBatch& db, const int* dl, int na, long long log_stride);
   RotShape rot_shape(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
                      long long log_stride, bool may_tune);
@@ -581,11 +604,12 @@ struct Ctx {
   // at most async_lag iterations behind the launches
   static constexpr int CNT_RING = 8;
   int async_lag = 2;
-  int* cnt_host = nullptr;  // [CNT_RING], pinned
+  int* cnt_host = nullptr;  // [CNT_RING][2], pinned
   std::vector<hipEvent_t> cnt_ev;
   DevBuf<int> cnt_dev;
   void count_ring_init();
-  int run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single = false);
+  int run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single = false,
+              bool refresh = false);
   int solve_batch(Batch& b, bool cold, long long* iters_out);
   int retry_failed(Batch& b, long long* iters_out);
   // iteration cap of the damped retry stage (0: max(max_iter, 200));

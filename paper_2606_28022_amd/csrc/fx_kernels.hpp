@@ -28,12 +28,12 @@ __global__ void k_cluster_healed(DevSystem sys, DevBatch bt, const double* Phi, 
                                  double* dE);
 __global__ void k_vhop(DevBatch bt, double vhop);
 __global__ void k_ghost_cn(DevSystem sys, const int* bonds, int nbonds, double* cn);
-__global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err);
+__global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err, int route);
 __global__ void k_hist_reset(DevBatch bt, const int* list, int nl);
 // work-groups of a launch over nl systems of tps tiles each, numbered by
 // xcd_slot_tile: 8 ceil(nl / 8) tps
 inline long long xcd_grid(int nl, int tps) { return 8LL * ((nl + 7) / 8) * tps; }
-__global__ void k_compact_active(const int* status, const int* list, int nl, int* act, int* count);
+__global__ void k_compact_active(const int* status, const int* mode, const int* list, int nl, int* act, int* count);
 __global__ void k_precond_step(DevBatch bt, double* out);
 __global__ void k_cholinv(DevBatch bt, const int* list, const double* Apool, double* Lpool, double* Xpool);
 __global__ void k_cluster_init_ct(DevBatch bt, const int* list, DevBatch mono, const long long* warm_off);
@@ -61,6 +61,23 @@ __global__ void k_gemm_mfma(DevBatch bt, const int* list, int nl, int tiles_per_
                             int occ_list);
 __global__ void k_gemm(DevBatch bt, const int* list, int mode, const double* A, const double* B, double* C,
                        const double* w, int skip_done);
+// occupied-virtual rotations (fx_orb.hip): systems of up to OV_MAXN AOs, 32
+// occupied orbitals per work-group of eight waves, rotations of |X| up to
+// OV_XMAX while the SCC residual is below OV_ERRMAX (above them the
+// eigensolver: a monomer's first iterations from superposition charges, with
+// residuals near 1, did not settle for up to 62 iterations by rotations)
+constexpr int OV_MAXN = 256, OV_ROWS = 32, OV_WAVES = 8;
+constexpr double OV_XMAX = 0.1, OV_ERRMAX = 0.1;
+__host__ __device__ inline unsigned ov_grad_lds_bytes(int n) { return 8u * 2u * 16u * (((unsigned)n + 15u) & ~15u); }
+// (both classes padded to 16: at most 30 rows more than n)
+__host__ __device__ inline unsigned ov_apply_lds_bytes(int n, int cb) {
+  return 8u * 16u * (unsigned)cb * (((unsigned)n + 30u) & ~15u);
+}
+__global__ void k_ov_grad(DevBatch bt, const int* list, int nl, int tiles_per_sys, double* Xpool, double* xpart);
+template <int CB, int BLK>
+__global__ void k_ov_apply(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* Xpool,
+                           const double* xpart);
+__global__ void k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened);
 __global__ void k_jacobi(DevBatch bt, const int* list, int max_sweeps, double rel_tol, double thr_scale,
                          double cap_err, int* sweeps_out);
 // LDS layout of k_jacobi_lds for an n x n system: packed strict upper
@@ -146,15 +163,15 @@ __global__ void k_jacobi_lds(DevBatch bt, const int* list, int max_sweeps, doubl
                              double cap_err, int* sweeps_out, int chunk);
 __global__ void k_eigh_batched(const int* nvec, const long long* off, double* Abuf, double* Vbuf, double* wbuf,
                                const long long* woff, int max_sweeps, double rel_tol);
-__global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list);
-__global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, double tol, double etol, int max_iter,
+__global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate);
+__global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol, int max_iter,
                               double beta);
 
 // FMO assembly (fx_fmo.hip)
 __global__ void k_gather_shell(DevBatch bt, const double* src_global, double* dst_local);
 __global__ void k_scatter_shell(DevBatch bt, const double* src_local, double* dst_global);
 __global__ void k_absdiff_part(const double* a, const double* b, int n, double* part);
-__global__ void k_max_reduce(const double* part, int np, double* out);
+__global__ void k_max_reduce(const double* part, int np, const double* extra, int nextra, double* out);
 __global__ void k_cluster_terms(DevBatch bt, const double* qmono, const double* e_mono, double* ddq, double* dEV,
                                 double* dE);
 // the arrays of one compensated sum
@@ -221,7 +238,7 @@ __global__ void k_gather_atoms(int N, const int* rowptr, const int* ent_batch, c
                                const double* const* g_batches, const double* const* F_batches, double* g_tot,
                                double* F_tot, int mode);
 __global__ void k_final_shift(DevSystem sys, DevBatch bt, double* wvec);
-__global__ void k_make_DS(DevBatch bt, const double* P, const double* W, double* out);
+__global__ void k_make_DS(DevBatch bt, const double* P, const double* W, double* out, int rotated);
 
 // learned initial guess
 __global__ void k_mlp_features(DevSystem sys, float* out);

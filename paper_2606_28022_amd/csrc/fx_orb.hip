@@ -8,7 +8,7 @@
 // each class change no density, and the next iteration's A_vo carries what
 // this one left.  The fixed point, A_vo = 0, is exact whatever the
 // denominators.  The rotation K = [[0, -X^T], [X, 0]] is applied as
-//     U = 1 + K + K^2/2 + K^3/8 - K^5/128,
+//     U = 1 + K + K^2/2 + K^3/8 - K^5/128 + K^7/1024,
 // whose even part 1 + K^2/2 fixes the odd part by U^T U = 1 (the square root
 // of K^2 + K^4/4, as a series); it is cut where |K| makes the next term
 // vanish in FP64, so C stays S-orthonormal to rounding without a
@@ -24,6 +24,8 @@
 #include "fx_device.hpp"
 #include "fx_kernels.hpp"
 
+#include <type_traits>
+
 namespace fx {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -33,11 +35,37 @@ namespace {
 // k values feed four successive matrix instructions: instruction m then reads
 // the four consecutive positions 4 m .. 4 m + 3
 __device__ inline int perm16(int r) { return (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3); }
+
+// the chunks 0 .. nch - 1 of a contraction: load(t, c) fetches a chunk's four
+// operand values, mul(t, c) multiplies it.  Loads run D chunks ahead and, but
+// for the last ones, without a condition, so that each multiplication waits
+// for its own chunk only: the operands come from HBM for a system's first
+// work-group, and one chunk of matrix instructions does not cover that.
+template <int D, typename Load, typename Mul>
+__device__ inline void chunk_pipeline(int nch, Load load, Mul mul) {
+  double t[D + 1][4];
+#pragma unroll
+  for (int j = 0; j < D; ++j) load(t[j], min(j, nch - 1));
+  int c = 0;
+  for (; c + D + 1 <= nch; c += D + 1)
+#pragma unroll
+    for (int j = 0; j <= D; ++j) {
+      load(t[(j + D) % (D + 1)], min(c + j + D, nch - 1));
+      __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink the loads)
+      mul(t[j], c + j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+    if (c + j < nch) mul(t[j], c + j);
+}
 }  // namespace
 
-// X = -A_vo / (eps_v - eps_o) of the listed systems in rotation mode, into
-// Xpool (mat offsets; nvp x nop row-major, both dimensions rounded up to 16
-// and zero there).  A work-group of eight waves takes 32 occupied orbitals:
+// X = -A_vo / (eps_v - eps_o) of the listed systems in rotation mode, both
+// dimensions rounded up to 16 with zeros, as 16 x 16 blocks [virtual][occupied]
+// (mat offsets), each stored by occupied columns: element (v, o) of a block at
+// 16 o + v, which is the order of the matrix instructions' operands, so that a
+// block is 2 KB read in one piece by X Z_o and by X^T Z_v alike.  A work-group of eight waves takes 32 occupied orbitals:
 // T = (C_o F)^T first (wave = 16 AO columns; F from L2, the orbitals staged in
 // LDS), T then takes the orbitals' place in LDS and A_vo = C_v T follows (16
 // virtual x 16 occupied blocks dealt to the waves), so the intermediate never
@@ -60,21 +88,45 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
   const int nrb = min(OV_ROWS, nop - o0) >> 4;  // 16-orbital blocks of this tile: 1 or 2
   const double* __restrict__ Ct = bt.Ct + d.mat_off;
   const double* __restrict__ F = bt.F + d.mat_off;
-  const double* eps = bt.eps + d.ao_off;
-  const int* ox = bt.ov_idx + d.ao_off;
-  const int* vx = ox + no;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, g = lane >> 4;
   double* B0 = ov_lds;            // [np][16], first 16 orbitals
   double* B1 = ov_lds + np * 16;  // second 16
-  // the orbitals, transposed: [k][orbital], zero past n and past no
-  for (int u = wave; u < nrb * (np >> 4); u += OV_WAVES) {
-    const int rb = u >= (np >> 4) ? 1 : 0, c = u - rb * (np >> 4);
-    const int o = o0 + 16 * rb + i, k = 16 * c + 4 * g;
-    const double* row = Ct + (long long)(o < no ? ox[o] : 0) * n;
-    double* dst = (rb ? B1 : B0) + k * 16 + i;
+  // the class lists and their eigenvalues, staged once (their use in each
+  // block would be two dependent memory accesses)
+  __shared__ int ox[OV_MAXN];
+  __shared__ double eps[OV_MAXN];
+  if ((int)threadIdx.x < n) {
+    const int o = bt.ov_idx[d.ao_off + threadIdx.x];
+    ox[threadIdx.x] = o;
+    eps[threadIdx.x] = bt.eps[d.ao_off + o];
+  }
+  __syncthreads();
+  const int* vx = ox + no;
+  // the orbitals, transposed: [k][orbital], zero past n and past no.  All of a
+  // wave's loads are issued before the first is used (clamped addresses, no
+  // branch): the chain of HBM accesses would otherwise be the longest part.
+  {
+    constexpr int UN = 2 * (OV_MAXN / 16) / OV_WAVES;
+    const int nc = np >> 4, nu = nrb * nc;
+    double v[UN][4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) dst[16 * m] = (o < no && k + m < n) ? row[k + m] : 0.0;
+    for (int j = 0; j < UN; ++j) {
+      const int u = min(wave + OV_WAVES * j, nu - 1), rb = u >= nc ? 1 : 0;
+      const int o = min(o0 + 16 * rb + i, no - 1), k = 16 * (u - rb * nc) + 4 * g;
+      const double* row = Ct + ox[o] * n;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) v[j][m] = row[min(k + m, n - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < UN; ++j) {
+      const int u = wave + OV_WAVES * j, rb = u >= nc ? 1 : 0;
+      if (u >= nu) continue;
+      const int k = 16 * (u - rb * nc) + 4 * g;
+      double* dst = (rb ? B1 : B0) + k * 16 + i;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) dst[16 * m] = (o0 + 16 * rb + i < no && k + m < n) ? v[j][m] : 0.0;
+    }
   }
   __syncthreads();
   // T[mu][o] = sum_k F[k][mu] C_o[k]; F is symmetric, rows past n are read
@@ -87,23 +139,35 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
     acc[r][1] = (v4d){0.0, 0.0, 0.0, 0.0};
     const int mu0 = 16 * (wave + OV_WAVES * r);
     if (mu0 >= n) continue;
-    const double* Fc = F + min(mu0 + i, n - 1);
-    double a[4], an[4];
+    // (32-bit byte offsets from the matrix)
+    const char* Fb = reinterpret_cast<const char*>(F);
+    const unsigned colb = 8u * (unsigned)min(mu0 + i, n - 1), rowb = 8u * (unsigned)n;
+    auto load = [&](double* t, int c) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = Fc[(long long)min(4 * m + g, n - 1) * n];
-    for (int k0 = 0; k0 < np; k0 += 16) {
-      if (k0 + 16 < np)
+      for (int m = 0; m < 4; ++m)
+        t[m] = *reinterpret_cast<const double*>(Fb + (colb + (unsigned)min(16 * c + 4 * m + g, n - 1) * rowb));
+    };
+    // (one or two orbital blocks: two code paths, so that no branch separates
+    // a chunk's LDS reads from its matrix instructions)
+    auto run = [&](auto two) {
+      constexpr bool TWO = decltype(two)::value;
+      chunk_pipeline<3>(np >> 4, load, [&](const double* t, int c) {
+        const int row = (16 * c + g) * 16 + i;
+        double x[4], y[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) an[m] = Fc[(long long)min(k0 + 16 + 4 * m + g, n - 1) * n];
+        for (int m = 0; m < 4; ++m) {
+          x[m] = B0[row + 64 * m];
+          y[m] = TWO ? B1[row + 64 * m] : 0.0;
+        }
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int row = (k0 + 4 * m + g) * 16 + i;
-        acc[r][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], B0[row], acc[r][0], 0, 0, 0);
-        if (nrb > 1) acc[r][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], B1[row], acc[r][1], 0, 0, 0);
-      }
-#pragma unroll
-      for (int m = 0; m < 4; ++m) a[m] = an[m];
-    }
+        for (int m = 0; m < 4; ++m) {
+          acc[r][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[m], x[m], acc[r][0], 0, 0, 0);
+          if (TWO) acc[r][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[m], y[m], acc[r][1], 0, 0, 0);
+        }
+      });
+    };
+    if (nrb > 1) run(std::true_type{});
+    else run(std::false_type{});
   }
   __syncthreads();
 #pragma unroll
@@ -120,43 +184,43 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
     }
   }
   __syncthreads();
+  // A_vo^T: 16 occupied rows x 16 virtual columns per block
   double* X = Xpool + d.mat_off;
   double xs = 0.0;
-  const int nunit = (nvp >> 4) * nrb;
+  const int nvb = nvp >> 4, nob = nop >> 4;
+  const int nunit = nvb * nrb;
   for (int u = wave; u < nunit; u += OV_WAVES) {
     const int vb = nrb > 1 ? u >> 1 : u, rb = nrb > 1 ? u & 1 : 0;
     const double* Bt = rb ? B1 : B0;
-    const int v = 16 * vb + i;
-    const double* row = Ct + (long long)vx[min(v, nv - 1)] * n;
+    const int v = 16 * vb + i, ov = vx[min(v, nv - 1)];
+    const double ev = eps[no + min(v, nv - 1)];
+    const char* Cb = reinterpret_cast<const char*>(Ct);
+    const unsigned rowb = 8u * (unsigned)(ov * n);
     v4d c = (v4d){0.0, 0.0, 0.0, 0.0};
-    double a[8], an[8];
-    auto fetch = [&](double* t, int k0) {
+    auto load = [&](double* t, int ch) {
+      // four consecutive elements of the lane's row (the last chunk clamped)
+      const int k = 16 * ch + 4 * g;
+      if (16 * ch + 16 <= n) {
+        __builtin_memcpy(t, Cb + (rowb + 8u * (unsigned)k), 32);
+      } else {
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) t[4 * h + m] = row[min(k0 + 16 * h + 4 * g + m, n - 1)];
-    };
-    fetch(a, 0);
-    for (int k0 = 0; k0 < np; k0 += 32) {
-      if (k0 + 32 < np) fetch(an, k0 + 32);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (k0 + 16 * h < np)
-#pragma unroll
-          for (int m = 0; m < 4; ++m)
-            c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[4 * h + m], Bt[(k0 + 16 * h + 4 * m + g) * 16 + i], c, 0, 0, 0);
+        for (int m = 0; m < 4; ++m)
+          t[m] = *reinterpret_cast<const double*>(Cb + (rowb + 8u * (unsigned)min(k + m, n - 1)));
       }
+    };
+    auto mul = [&](const double* t, int ch) {
 #pragma unroll
-      for (int m = 0; m < 8; ++m) a[m] = an[m];
-    }
-    const int o = o0 + 16 * rb + i;
-    const double eo = o < no ? eps[ox[o]] : 0.0;
+      for (int m = 0; m < 4; ++m)
+        c = __builtin_amdgcn_mfma_f64_16x16x4f64(Bt[(16 * ch + 4 * m + g) * 16 + i], t[m], c, 0, 0, 0);
+    };
+    chunk_pipeline<3>(np >> 4, load, mul);
+    const int ob = (o0 >> 4) + rb;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int vr = 16 * vb + g + 4 * q;
+      const int o = 16 * ob + g + 4 * q;
       double x = 0.0;
-      if (vr < nv && o < no) x = -c[q] / (eps[vx[vr]] - eo);
-      X[vr * nop + o] = x;
+      if (v < nv && o < no) x = -c[q] / (ev - eps[o]);
+      X[((vb * nob + ob) * 4 + q) * 64 + lane] = x;
       xs = fma(x, x, xs);
     }
   }
@@ -173,14 +237,15 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
 
 // Rows of C^T (in place) times U for the listed systems in rotation mode.  A
 // work-group of eight waves takes 16 CB columns: the rows live in LDS by class
-// (occupied first, then virtual, each padded to 16 with zeros) and the wave's
-// own 16-row blocks in registers; each product with K is two blocks of
-// X Z_o and X^T Z_v per wave with X from L2 (shared by the system's tiles on
-// one XCD), so the series costs no pass over HBM beyond C^T once in and out.
+// (occupied first, then virtual, each padded to 16 with zeros); each product
+// with K is BLK 16-row blocks of X Z_o or X^T Z_v per wave with X from L2
+// (shared by the system's tiles on one XCD), so the series costs no pass over
+// HBM beyond C^T once in and out.
 // CB is the launch's choice (2 where the batch fills the chip, else 1: more
 // work-groups per system); the sums are the same.
-template <int CB>
-__global__ void __launch_bounds__(64 * OV_WAVES)
+// BLK 16-row blocks per wave: 2 serve up to 256 padded rows.
+template <int CB, int BLK>
+__global__ void __launch_bounds__(64 * OV_WAVES) __attribute__((amdgpu_waves_per_eu(4)))
     k_ov_apply(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* __restrict__ Xpool,
                const double* xpart) {
   extern __shared__ double ov_lds[];
@@ -200,7 +265,8 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
   const int* vx = ox + no;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, g = lane >> 4;
-  const double* __restrict__ X = Xpool + d.mat_off;
+  const double* X = Xpool + d.mat_off;
+  const int nob = nop >> 4;
   // |X| and, where it exceeds OV_XMAX (the couplings are too large for this
   // route; the mixer sends the system back to the eigensolver), a shorter step
   double x2 = 0.0;
@@ -209,115 +275,102 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
   const double sc = xn > OV_XMAX ? OV_XMAX / xn : 1.0;
   const double xk = xn * sc;
   if (tile == 0 && threadIdx.x == 0) bt.xn[si] = xn;
-  // terms of U kept: the first one left out is below 1e-15 (5: |K|^8 / 512,
-  // 3: |K|^6 / 64, 2: |K|^4 / 4, 1: |K|^2)
-  const int order = xk < 1e-8 ? 1 : xk < 2e-4 ? 2 : xk < 6e-3 ? 3 : 5;
-  // block b of the wave: virtual blocks first, then occupied ones
-  constexpr int U = OV_BLK;
-  v4d c[U][CB], z[U][CB];
-#pragma unroll
-  for (int t = 0; t < U; ++t) {
+  // products with K: the first term of U^T U left out stays below 1e-15 (7:
+  // 3e-4 |K|^10 at the two-norm, a fraction of the Frobenius norm at hand; 5:
+  // |K|^8 / 512; 3: |K|^6 / 64; 2: |K|^4 / 4; 1: |K|^2)
+  const int order = xk < 1e-8 ? 1 : xk < 2e-4 ? 2 : xk < 6e-3 ? 3 : xk < 0.03 ? 5 : 7;
+  // element q of the lane in block t of the wave (virtual blocks first, then
+  // occupied ones): offset of its row of C^T (-1: padding), position in LDS.
+  // All loads are issued before the first is used (clamped, no branch).
+  int ro[BLK][4];
+  v4d c[BLK][CB];
+  auto lds_row = [&](int t, int q) {
     const int b = wave + OV_WAVES * t;
-    if (b >= nbk) continue;
+    return b < nvb ? nop + perm16(16 * b + g + 4 * q) : 16 * (b - nvb) + g + 4 * q;
+  };
+#pragma unroll
+  for (int t = 0; t < BLK; ++t) {
+    const int b = min(wave + OV_WAVES * t, nbk - 1);
     const bool vir = b < nvb;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r = g + 4 * q;
-      const int k = 16 * (vir ? b : b - nvb) + r;
-      const bool in = k < (vir ? nv : no);
-      const double* row = Ct + (long long)(in ? (vir ? vx[k] : ox[k]) : 0) * n;
-      const int at = vir ? nop + k : perm16(k);
+      const int k = 16 * (vir ? b : b - nvb) + g + 4 * q, last = (vir ? nv : no) - 1;
+      const int idx = (vir ? vx : ox)[min(k, last)];
+      ro[t][q] = k <= last ? idx * n : -1;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < BLK; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int w = 0; w < CB; ++w) c[t][w][q] = Ct[max(ro[t][q], 0) + min(c0 + 16 * w + i, n - 1)];
+#pragma unroll
+  for (int t = 0; t < BLK; ++t) {
+    if (wave + OV_WAVES * t >= nbk) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int w = 0; w < CB; ++w) {
-        const int col = c0 + 16 * w + i;
-        const double e = in && col < n ? row[col] : 0.0;
-        c[t][w][q] = e;
-        ov_lds[(w * R + at) * 16 + i] = e;
+        if (ro[t][q] < 0 || c0 + 16 * w + i >= n) c[t][w][q] = 0.0;
+        ov_lds[(w * R + lds_row(t, q)) * 16 + i] = c[t][w][q];
       }
-    }
   }
   __syncthreads();
   for (int p = order; p >= 1; --p) {
-    // Z <- C + f K Z (order 5 starts with -K/16 C alone)
-    const double f = sc * (p >= 4 ? (p == 5 ? -1.0 / 16.0 : 1.0) : p == 3 ? 0.25 : p == 2 ? 0.5 : 1.0);
-    const double keep = p == 5 ? 0.0 : 1.0;
+    // Z <- keep C + f K Z, by Horner's rule from the highest term
+    const double f = sc * (p == 1 || p == 4 || p == 6 ? 1.0 : p == 2 ? 0.5 : p == 3 ? 0.25 : p == 5 ? -1.0 / 16.0 : -0.125);
+    const bool keep = p != 5 && p != 7;
+    v4d z[BLK][CB];
 #pragma unroll
-    for (int t = 0; t < U; ++t) {
+    for (int t = 0; t < BLK; ++t) {
       const int b = wave + OV_WAVES * t;
 #pragma unroll
       for (int w = 0; w < CB; ++w) z[t][w] = (v4d){0.0, 0.0, 0.0, 0.0};
       if (b >= nbk) continue;
-      if (b < nvb) {
-        // - X Z_o: four consecutive occupied columns of X per lane and chunk
-        const double* xr = X + (long long)(16 * b + i) * nop + 4 * g;
-        double a[4], an[4];
+      // virtual rows: X Z_o, instruction m takes columns 4 m + g of the chunk's
+      // block; occupied rows: X^T Z_v, it takes rows 4 g + m (Z_v's rows are
+      // permuted to match), a lane's four being consecutive
+      const bool vir = b < nvb;
+      const int nch = vir ? nob : nvb;
+      const double* xb = X + (vir ? 256 * (b * nob) + lane : 256 * (b - nvb) + 16 * i + 4 * g);
+      const int es = vir ? 64 : 1, cs = vir ? 256 : 256 * nob;
+      const double* zl = ov_lds + (vir ? 0 : nop * 16) + lane;
+      auto load = [&](double* x, int c) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) a[m] = xr[m];
-        for (int k0 = 0; k0 < nop; k0 += 16) {
-          if (k0 + 16 < nop)
+        for (int m = 0; m < 4; ++m) x[m] = xb[cs * c + es * m];
+      };
+      auto mul = [&](const double* x, int c) {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) an[m] = xr[k0 + 16 + m];
+        for (int m = 0; m < 4; ++m)
 #pragma unroll
-          for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int w = 0; w < CB; ++w)
-              z[t][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], ov_lds[(w * R + k0 + 4 * m + g) * 16 + i], z[t][w],
-                                                             0, 0, 0);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) a[m] = an[m];
-        }
-#pragma unroll
-        for (int w = 0; w < CB; ++w) z[t][w] = keep * c[t][w] - f * z[t][w];
-      } else {
-        // X^T Z_v
-        const double* xr = X + (long long)g * nop + 16 * (b - nvb) + i;
-        double a[4], an[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) a[m] = xr[4 * m * nop];
-        for (int k0 = 0; k0 < nvp; k0 += 16) {
-          if (k0 + 16 < nvp)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) an[m] = xr[(k0 + 16 + 4 * m) * nop];
-#pragma unroll
-          for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int w = 0; w < CB; ++w)
-              z[t][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                  a[m], ov_lds[(w * R + nop + k0 + 4 * m + g) * 16 + i], z[t][w], 0, 0, 0);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) a[m] = an[m];
-        }
-#pragma unroll
-        for (int w = 0; w < CB; ++w) z[t][w] = keep * c[t][w] + f * z[t][w];
-      }
+          for (int w = 0; w < CB; ++w)
+            z[t][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m], zl[w * R * 16 + 256 * c + 64 * m], z[t][w], 0, 0, 0);
+      };
+      chunk_pipeline<1>(nch, load, mul);
     }
     if (p > 1) __syncthreads();  // Z has been read
 #pragma unroll
-    for (int t = 0; t < U; ++t) {
+    for (int t = 0; t < BLK; ++t) {
       const int b = wave + OV_WAVES * t;
       if (b >= nbk) continue;
-      const bool vir = b < nvb;
+      const double fb = b < nvb ? -f : f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = 16 * (vir ? b : b - nvb) + g + 4 * q;
-        if (p > 1) {
-          const int at = vir ? nop + k : perm16(k);
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int w = 0; w < CB; ++w) ov_lds[(w * R + at) * 16 + i] = z[t][w][q];
-        } else if (k < (vir ? nv : no)) {
-          double* row = Ct + (long long)(vir ? vx[k] : ox[k]) * n;
-#pragma unroll
-          for (int w = 0; w < CB; ++w)
-            if (c0 + 16 * w + i < n) row[c0 + 16 * w + i] = z[t][w][q];
+        for (int w = 0; w < CB; ++w) {
+          const double v = fma(fb, z[t][w][q], keep ? c[t][w][q] : 0.0);
+          if (p > 1) ov_lds[(w * R + lds_row(t, q)) * 16 + i] = v;
+          else if (ro[t][q] >= 0 && c0 + 16 * w + i < n) Ct[ro[t][q] + c0 + 16 * w + i] = v;
         }
-      }
     }
     if (p > 1) __syncthreads();
   }
 }
 
-template __global__ void k_ov_apply<1>(DevBatch, const int*, int, int, const double*, const double*);
-template __global__ void k_ov_apply<2>(DevBatch, const int*, int, int, const double*, const double*);
+template __global__ void k_ov_apply<1, 2>(DevBatch, const int*, int, int, const double*, const double*);
+template __global__ void k_ov_apply<1, 3>(DevBatch, const int*, int, int, const double*, const double*);
+template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const double*, const double*);
 
 // After a solve: the gap of the systems that converged in a rotation from the
 // expectation values C_i^T F C_i of the orbitals whose last eigenvalue lies

@@ -75,7 +75,9 @@ __device__ inline double block_max_waves(double v, double* red) {
 // start of a solve: clear the iteration state of the listed systems
 // (keep_err: the residual of the previous pass stays, so the eigensolver's
 // rotation threshold follows the outer iteration)
-__global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err) {
+// route: 0 the first iteration is an eigensolver's (a system taken off the
+// rotations stays off them), 1 also for those, 2 as the last solve left it
+__global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err, int route) {
   int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nl) return;
   int si = list[k];
@@ -84,6 +86,8 @@ __global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err
   bt.nhist[si] = 0;
   bt.e_prev[si] = 0.0;
   if (!keep_err) bt.err[si] = 1e-2;
+  if (route == 1 || (route == 0 && bt.mode[si] != 2)) bt.mode[si] = 0;
+  if (route != 2) bt.xn[si] = -1.0;
 }
 
 // clear the Anderson history of the listed systems
@@ -94,18 +98,27 @@ __global__ void k_hist_reset(DevBatch bt, const int* list, int nl) {
 
 // Stable partition of the list by status, on the device: the systems still
 // iterating (status 0) first, in list order, then the others, in list order;
-// *count = the number of the former.  One work-group of 1024 threads: each
+// count[0] = the number of the former, count[1] = how many of these the
+// eigensolver (not an orbital rotation) takes next.  One work-group of 1024 threads: each
 // thread takes a contiguous chunk of the list, and a scan over the chunk
 // counts places it.  Every list entry is written, so a kernel launched over
 // more slots than *count finds converged systems there and returns.
-__global__ void __launch_bounds__(1024) k_compact_active(const int* status, const int* list, int nl, int* act,
-                                                         int* count) {
+__global__ void __launch_bounds__(1024) k_compact_active(const int* status, const int* mode, const int* list, int nl,
+                                                         int* act, int* count) {
   __shared__ int part[1024];
+  __shared__ int neig;
+  if (threadIdx.x == 0) neig = 0;
+  __syncthreads();
   const int t = threadIdx.x, nt = blockDim.x;
   const int per = (nl + nt - 1) / nt;
   const int lo = min(nl, t * per), hi = min(nl, lo + per);
-  int na = 0;
-  for (int i = lo; i < hi; ++i) na += status[list[i]] == 0 ? 1 : 0;
+  int na = 0, ne = 0;
+  for (int i = lo; i < hi; ++i) {
+    const bool on = status[list[i]] == 0;
+    na += on ? 1 : 0;
+    ne += on && mode[list[i]] != 1 ? 1 : 0;
+  }
+  if (ne) atomicAdd(&neig, ne);
   part[t] = na;
   __syncthreads();
   for (int off = 1; off < nt; off <<= 1) {
@@ -124,7 +137,10 @@ __global__ void __launch_bounds__(1024) k_compact_active(const int* status, cons
     else
       act[pi++] = si;
   }
-  if (t == 0) *count = total;
+  if (t == 0) {
+    count[0] = total;
+    count[1] = neig;
+  }
 }
 
 // Preconditioned monomer step of the fused embedding loop, per system:
@@ -552,6 +568,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   if (sl >= nl) return;
   const int si = list[sl];
   if (skip_done && bt.status[si] != 0) return;
+  if ((skip_done & 2) && bt.mode[si] == 1) return;  // (the iteration rotates the orbitals instead)
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
   const int nt = (n + 63) / 64;
@@ -1119,9 +1136,14 @@ __global__ void k_eigh_batched(const int* nvec, const long long* off, double* Ab
 // sum n_i - N_el suffers inside a gap, so that Newton's method from the
 // middle of the gap takes two or three: 5 us.  Levels without a gap of 8 kT
 // (or an odd electron) keep the bisection.
-__global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list) {
+//
+// rotate: a system whose occupations are 0 and 2 to 1e-11 (a gap of 51 kT)
+// continues with orbital rotations (mode 1), over the class lists written
+// here; the others stay with the eigensolver.
+__global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate) {
   int si = list[blockIdx.x];
-  if (bt.status[si] != 0) return;  // converged or failed: nothing to do
+  // (a system in rotation mode keeps its occupations)
+  if (bt.status[si] != 0 || bt.mode[si] == 1) return;
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
   const double kT = sys.g.kT;
@@ -1240,6 +1262,31 @@ __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list) {
       c += __popcll(m);
     }
     if (lane == 0) bt.occ_cnt[si] = c;
+    // the two classes, each in ascending order
+    int* cx = bt.ov_idx + d.ao_off;
+    int co = 0, cv = 0;
+    bool frac = false;
+    for (int base = 0; rotate && base < n; base += 64) {
+      const int i = base + lane;
+      const double o = i < n ? oc[i] : 0.0;
+      frac = frac || (i < n && fmin(o, 2.0 - o) > 2e-11);
+      const unsigned long long mo = __ballot(i < n && o > 1.0), mv = __ballot(i < n && !(o > 1.0));
+      const unsigned long long below = (1ULL << lane) - 1ULL;
+      if (i < n && even) {
+        if (o > 1.0) cx[co + __popcll(mo & below)] = i;
+        else if (no + cv + __popcll(mv & below) < n) cx[no + cv + __popcll(mv & below)] = i;
+      }
+      co += __popcll(mo);
+      cv += __popcll(mv);
+    }
+    frac = __ballot(frac) != 0;
+    // (the padded X takes the place of P: the smallest systems have no room)
+    const bool fits = ((no + 15) & ~15) * ((n - no + 15) & ~15) <= n * n;
+    if (lane == 0) {
+      bt.xn[si] = -1.0;
+      bt.ov_no[si] = no;
+      if (bt.mode[si] != 2) bt.mode[si] = rotate && even && !frac && fits && co == no ? 1 : 0;
+    }
   }
 }
 
@@ -1277,10 +1324,11 @@ __device__ void solve_small(double* M, double* rhs, int m) {
   }
 }
 
-__global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, double tol, double etol, int max_iter,
-                              double beta) {
+// eig 0: this iteration launched no eigensolver; the systems that need one wait
+__global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol,
+                              int max_iter, double beta) {
   int si = list[blockIdx.x];
-  if (bt.status[si] != 0) return;
+  if (bt.status[si] != 0 || (!eig && bt.mode[si] != 1)) return;
   const SysDesc d = bt.desc[si];
   const int n = d.nao, ns = d.nsh;
   __shared__ double red[256];
@@ -1391,9 +1439,14 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, doubl
   double e = eh + e2 + e3 + bt.mts[si] + bt.erep[si];
   int it = bt.niter[si] + 1;
   double de = fabs(e - bt.e_prev[si]);
-  bool conv = (err < tol) && (de < etol) && (it > 1);
+  // a rotation of |X| leaves the orbitals a fraction of |X| from the
+  // eigensolver's (first order in the couplings inside the classes, a tenth to
+  // a fifth for the pentacene dimers): it has to be small too
+  const double xn = bt.xn[si];
+  bool conv = (err < tol) && (de < etol) && (it > 1) && (xn < 5.0 * tol);
   __syncthreads();
   if (threadIdx.x == 0) {
+    if (bt.mode[si] == 1 && (xn > OV_XMAX || err > OV_ERRMAX)) bt.mode[si] = 0;
     bt.e_int[si] = e;
     bt.e_prev[si] = e;
     bt.err[si] = err;
@@ -2292,7 +2345,7 @@ __device__ inline void jacobi_rot_system(const DevBatch& bt, int si, int max_swe
   typedef typename JtVec<T>::type V4;
   extern __shared__ double2 lds_raw[];
   unsigned char* lds = reinterpret_cast<unsigned char*>(lds_raw);
-  if (bt.status[si] != 0) return;
+  if (bt.status[si] != 0 || bt.mode[si] == 1) return;
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
   const int m = (n + 3) & ~3, nb2 = m / 2, nq = m / 4;
@@ -2534,7 +2587,7 @@ __global__ void __launch_bounds__(1024)
   xcd_slot_tile(blockIdx.x, tiles_per_sys, sl, tcol);
   if (sl >= nl) return;
   const int si = list[sl];
-  if (bt.status[si] != 0) return;
+  if (bt.status[si] != 0 || bt.mode[si] == 1) return;
   const int nsw = nlog[si];
   if (nsw <= 0) return;
   const SysDesc d = bt.desc[si];
@@ -2703,7 +2756,7 @@ __global__ void __launch_bounds__(64 * APPLY2_WAVES)
   xcd_slot_tile(blockIdx.x, tiles_per_sys, sl, tcol);
   if (sl >= nl) return;
   const int si = list[sl];
-  if (bt.status[si] != 0) return;
+  if (bt.status[si] != 0 || bt.mode[si] == 1) return;
   const int nsw = nlog[si];
   if (nsw <= 0) return;
   const SysDesc d = bt.desc[si];
