@@ -392,6 +392,11 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
   b.ov_idx.alloc(ao_off);
   b.xn.alloc(ns);
   b.xpart.alloc(16LL * ns);
+  {
+    const int nt = (b.max_nao + 63) / 64;
+    b.pop_stride = nt * (nt + 1) / 2 * POP_TILE;
+    if (b.max_nao > 32) b.pop_part.alloc((long long)ns * b.pop_stride);
+  }
   b.max_occ = 0;
   b.max_ovb = 0;
   for (const SysDesc& d : b.h_desc) {
@@ -1120,7 +1125,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       gemm_batch_f32(b, db, n32, dl, 1, b.Tf.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(a32), 1, 1, false);
     }
     if (n64 > 0) {
-      hipLaunchKernelGGL(k_fock, dim3(n64), dim3(256), 0, stream, ds, db, dl64);
+      launch_fock(b, ds, db, dl64, n64);
       if (ov && !all_eig) launch_ov(b, db, dl64, n64);
       if (some_eig) {
         const int skip = ov ? 3 : 1;
@@ -1170,19 +1175,20 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     }
     if (n32 > 0)
       gemm_batch_f32(b, db, n32, dl, 2, b.Ct.p, b.Ct.p, b.Pm.p, b.occ.p, b.gemm_gflop_occ(a32), 1, 1, true);
-    if (n64 > 0)
-      // (the upper tiles only: the mixer reads those; the lower ones are
-      // filled once the solve ends)
-      gemm_batch(b, db, n64, dl64, 2, b.Ct.p, b.Ct.p, b.Pm.p, b.occ.p, b.gemm_gflop_occ(a64), 1, 2, true);
+    const bool sums = b.max_nao > 32;
+    if (n64 > 0) {
+      if (sums) density_sums(b, db, n64, dl64, b.gemm_gflop_occ(a64));
+      else gemm_batch(b, db, n64, dl64, 2, b.Ct.p, b.Ct.p, b.Pm.p, b.occ.p, b.gemm_gflop_occ(a64), 1, 2, true);
+    }
     // a system converges only in an FP64 iteration
     const double beta = b.has_pre ? precond_beta : mix_beta;
     if (n32 > 0)
       hipLaunchKernelGGL(k_charges_mix, dim3(n32), dim3(256), 0, stream, ds, db, dl, 1, -1.0, -1.0,
-                         single ? 1 : opt.max_iter, beta);
+                         single ? 1 : opt.max_iter, beta, (const double*)nullptr, 0);
     if (n64 > 0)
       hipLaunchKernelGGL(k_charges_mix, dim3(n64), dim3(256), 0, stream, ds, db, dl64, some_eig ? 1 : 0,
                          scc_tol_cur > 0 ? scc_tol_cur : opt.scc_tol, etol_cur > 0 ? etol_cur : opt.energy_tol,
-                         single ? 1 : opt.max_iter, beta);
+                         single ? 1 : opt.max_iter, beta, sums ? (const double*)b.pop_part.p : nullptr, b.pop_stride);
     check(hipGetLastError(), "scc iteration");
   };
   // FX_BATCHED_GRAPH: after the first (eager) iteration, the iteration over
@@ -1216,7 +1222,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     return split_ok ? (it == 0 && cold && !b.init_from_mono && !cold_split) : it == 1;
   };
   auto tune_fused = [&](const int* dl, int na, double cap) {
-    hipLaunchKernelGGL(k_fock, dim3(na), dim3(256), 0, stream, ds, db, dl);
+    launch_fock(b, ds, db, dl, na);
     gemm_batch(b, db, na, dl, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, 0.0, 1);
     gemm_batch(b, db, na, dl, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, 0.0, 1);
     jp = autotune_jacobi(b, dl, na, jp, cap);
@@ -1391,11 +1397,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   }
   if (gexec) (void)hipGraphExecDestroy(gexec);
   if (graph) (void)hipGraphDestroy(graph);
-  // the density's lower tiles (the iterations write the upper ones)
-  if (b.max_nao > 64) {
-    hipLaunchKernelGGL(k_mirror_tiles, dim3(nl), dim3(256), 0, stream, db, (const int*)b.d_list.p, b.Pm.p);
-    check(hipGetLastError(), "k_mirror_tiles");
-  }
+  b.p_valid = b.max_nao <= 32;
   DevBuf<int> d_open;
   std::vector<int> open(1, 0), modes;
   if (ov && !single) {
@@ -1483,7 +1485,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
     if (pass > 0) {
       pass_list.upload(todo);
       dt = pass_list.p;
-      hipLaunchKernelGGL(k_fock, dim3(nt), dim3(256), 0, stream, ds, db, dt);
+      launch_fock(b, ds, db, dt, nt);
       gemm_batch(b, db, nt, dt, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, 0.0, 1);
       gemm_batch(b, db, nt, dt, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, 0.0, 1, sym_A);
     }
@@ -1526,6 +1528,34 @@ void Ctx::launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na) {
   check(hipGetLastError(), "orbital rotation");
 }
 
+// Fock matrices of the na systems listed in dl: up to eight work-groups per
+// system while that leaves at most two per CU
+void Ctx::launch_fock(const Batch& b, const DevSystem& ds, const DevBatch& db, const int* dl, int na) {
+  int slices = 1;
+  while (slices < 8 && 2LL * slices * na <= 2LL * n_cu && b.max_nao > 32 * slices) slices *= 2;
+  hipLaunchKernelGGL(k_fock, dim3(na, slices), dim3(256), 0, stream, ds, db, dl);
+}
+
+void Ctx::density_sums(const Batch& b, const DevBatch& db, int nl, const int* dl, double gflop) {
+  const int nt = (b.max_nao + 63) / 64;
+  const long long grid = xcd_grid(nl, nt * nt);
+  if (grid > 0x7fffffffLL) throw FxError(FX_E_INVALID, "batched product grid too large");
+  const int ev = capturing ? -1 : timers.begin(stream);
+  hipLaunchKernelGGL((k_gemm_mfma<2, 2>), dim3((unsigned)grid), dim3(256), 0, stream, db, dl, nl, nt * nt,
+                     (const double*)b.Ct.p, (const double*)b.Ct.p, b.pop_part.p, (const double*)b.occ.p, 1,
+                     b.pop_stride, 1);
+  if (!capturing) timers.end(stream, ev, kt("fx::k_gemm_mfma"), gflop);
+  check(hipGetLastError(), "density sums");
+}
+
+void Ctx::ensure_density(Batch& b) {
+  if (b.p_valid || b.nsys == 0) return;
+  std::vector<int> all(b.nsys);
+  for (int k = 0; k < b.nsys; ++k) all[k] = k;
+  gemm_batch(b, b.dev(), b.nsys, b.d_all.p, 2, b.Ct.p, b.Ct.p, b.Pm.p, b.occ.p, b.gemm_gflop_occ(all), 0, 1, true);
+  b.p_valid = true;
+}
+
 bool Ctx::canonical_basis(Batch& b) {
   if (!ov_batch(b) || b.nsys == 0) return true;
   std::vector<double> xn;
@@ -1538,6 +1568,7 @@ bool Ctx::canonical_basis(Batch& b) {
   const int nl = (int)l.size();
   DevBatch db = b.dev();
   DevSystem ds = dev_system();
+  ensure_density(b);  // (of the orbitals that gave the charges)
   b.d_list.upload(l);
   hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl, 1, 0);
   JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);

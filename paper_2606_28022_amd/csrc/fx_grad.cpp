@@ -23,6 +23,7 @@ namespace {
 // hop_f from slot slot_base on)
 void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys, DevBuf<double>& F_sys,
                     double* hop_f, long long slot_base) {
+  c.ensure_density(b);
   DevBatch db = b.dev();
   DevSystem ds = c.dev_system();
   DevBuf<double> wvec;

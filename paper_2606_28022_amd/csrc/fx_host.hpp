@@ -263,6 +263,11 @@ struct Batch {
   DevBuf<int> occ_idx, occ_cnt;  // significant orbitals of the last occupation (k_fermi)
   DevBuf<int> mode, ov_no, ov_idx;  // occupied-virtual rotations (DevBatch)
   DevBuf<double> xn, xpart;
+  // sums over the density's tiles (systems of more than 32 AOs, whose density
+  // is formed only when it is read: p_valid)
+  DevBuf<double> pop_part;
+  int pop_stride = 0;
+  bool p_valid = false;
   DevBuf<double> erep, e_int, e_prev, mts, err;
   DevBuf<int> status, niter, nhist, sweeps;
   // Newton preconditioner (1 + M G)^-1 of the Anderson residuals (FP32,
@@ -577,6 +582,11 @@ struct Ctx {
   // monomer loop: whether some monomer's next iteration is an eigensolver's
   bool mono_eig = true;
   void launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na);
+  // populations and energy sums of the densities (k_gemm_mfma<2, 2>), and the
+  // densities themselves from the last orbitals and occupations
+  void density_sums(const Batch& b, const DevBatch& db, int nl, const int* dl, double gflop);
+  void ensure_density(Batch& b);
+  void launch_fock(const Batch& b, const DevSystem& ds, const DevBatch& db, const int* dl, int na);
   // eigenvectors and eigenvalues of the systems of b whose last iteration was
   // a rotation; false when one of them has no gap any more (it is then left to
   // the eigensolver, mode 2)

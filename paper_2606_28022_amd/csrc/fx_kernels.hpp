@@ -54,7 +54,8 @@ constexpr int PRE_MAXSH = 16 * PRE_ROWS < 64 * PRE_COLS ? 16 * PRE_ROWS : 64 * P
 template <int ROWS>
 __global__ void k_precond_build(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, const double* Mmono,
                                 float* pre, int* ok);
-__global__ void k_mirror_tiles(DevBatch bt, const int* list, double* Abase);
+// doubles per upper 64 x 64 density tile: 64 row sums, 64 column sums, energy
+constexpr int POP_TILE = 130;
 template <int MODE, int WIN>
 __global__ void k_gemm_mfma(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* Abase,
                             const double* Bbase, double* Cbase, const double* wbase, int skip_done, int sym,
@@ -165,7 +166,7 @@ __global__ void k_eigh_batched(const int* nvec, const long long* off, double* Ab
                                const long long* woff, int max_sweeps, double rel_tol);
 __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate);
 __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol, int max_iter,
-                              double beta);
+                              double beta, const double* parts, int pstride);
 
 // FMO assembly (fx_fmo.hip)
 __global__ void k_gather_shell(DevBatch bt, const double* src_global, double* dst_local);

@@ -362,8 +362,13 @@ __device__ inline void matvec_wave_part(const T* M, const X* x, int ns, double* 
   }
 }
 
+// gridDim.y work-groups per system (a power of two): each computes the shifts
+// and builds its share of F.  One work-group keeps too few loads in flight to
+// finish a 232-AO system in less than 69 us; a batch that leaves the chip idle
+// splits them (launch_fock).
 __global__ void k_fock(DevSystem sys, DevBatch bt, const int* list) {
   int si = list[blockIdx.x];
+  const int slice = blockIdx.y, slices = gridDim.y;
   if (bt.status[si] != 0) return;  // converged or failed: nothing to do
   const SysDesc d = bt.desc[si];
   const int n = d.nao, ns = d.nsh;
@@ -397,7 +402,7 @@ __global__ void k_fock(DevSystem sys, DevBatch bt, const int* list) {
     double Gam = sys.elems[sys.elem[A]].Gamma;
     v += -Gam * qa_s[a] * qa_s[a] + bt.phi[d.sh_off + s];
     sig_s[s] = v;
-    bt.sig[d.sh_off + s] = v;
+    if (slice == 0) bt.sig[d.sh_off + s] = v;
   }
   __syncthreads();
   // the shift of each AO (that of its shell)
@@ -422,7 +427,7 @@ __global__ void k_fock(DevSystem sys, DevBatch bt, const int* list) {
     int tile = 0;
     for (int I = 0; I < nt; ++I)
       for (int J = I; J < nt; ++J, ++tile) {
-        if ((tile & 3) != wv) continue;
+        if ((tile & (4 * slices - 1)) != 4 * slice + wv) continue;
         const int j = 32 * J + tx;
 #pragma unroll 8
         for (int r = 0; r < 32; r += 2) {
@@ -453,11 +458,11 @@ __global__ void k_fock(DevSystem sys, DevBatch bt, const int* list) {
   }
   // element idx = i n + j, (i, j) advanced incrementally (no division per
   // element); unrolled so that several loads per thread are in flight
-  const int nn = n * n, step = blockDim.x;
+  const int nn = n * n, step = blockDim.x * slices, first = threadIdx.x + blockDim.x * slice;
   const int di = step / n, dj = step - di * n;
-  int i = threadIdx.x / n, j = threadIdx.x - i * n;
+  int i = first / n, j = first - i * n;
 #pragma unroll 4
-  for (int idx = threadIdx.x; idx < nn; idx += step) {
+  for (int idx = first; idx < nn; idx += step) {
     Fm[idx] = H[idx] + 0.5 * S[idx] * (sig_ao[i] + sig_ao[j]) + (Vh ? Vh[idx] : 0.0);
     i += di;
     j += dj;
@@ -558,6 +563,14 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // runs over the second fragment's AOs in mode 0 (C0^T S: the other terms
 // are zeros of C0) and over the first fragment's in mode 1 ((C0^T S) C0^T^T,
 // the columns of the first factor that mode 0 formed).
+// WIN = 2 (mode 2 only): the SCC iterations need of the density only its
+// populations and its energy, so a tile is contracted with S and H0 where it
+// stands and its 129 sums leave instead of its 4,096 elements (Cbase: sym
+// doubles per system, POP_TILE per upper tile); k_charges_mix adds them.
+// The density itself is formed once, when something reads it.  (Writing the
+// upper tiles and reading them back with S and H0 in the mixer, one work-group
+// per system: 1.13 + 0.71 ms for 3,425 pentacene dimers, 57 us of latency per
+// iteration for 13.)
 template <int MODE, int WIN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     k_gemm_mfma(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* __restrict__ Abase,
@@ -578,7 +591,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   // not (sym 2: the consumer reads the upper triangle only)
   if (sym && ti > tj) return;
   int kbeg = 0, kend = n;
-  if (WIN) {
+  if (WIN == 1) {
     const int a1 = bt.sys_sh_atom[d.sh_off + d.comp_sh[1]];
     const int n1 = bt.sys_atom_ao0[d.atom_off + a1];
     if (ti * 64 + 64 <= n1 || tj * 64 >= n1) return;
@@ -650,7 +663,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     b_step = KS * n;
     b_fix = j0 + kr < n;
   }
-  if (WIN) {  // start at K = kbeg (row-major operands: + kbeg, k-major: + kbeg rows)
+  if (WIN == 1) {  // start at K = kbeg (row-major operands: + kbeg, k-major: + kbeg rows)
     a_off += MODE == 2 ? kbeg * n : kbeg;
     b_off += MODE == 1 ? kbeg : kbeg * n;
   }
@@ -731,6 +744,64 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     }
     __syncthreads();
   }
+  if (WIN == 2) {
+    // the tile's share of the populations (P S)_ii and of Tr(P H0): row sums
+    // and, off the diagonal tiles, column sums, first within the lanes'
+    // 32 x 32 quadrant, then the quadrants in order.  On the diagonal every
+    // element of the tile is there, so row sums suffice.
+    const double* Sm = bt.S + d.mat_off;
+    const double* Hm = bt.H0 + d.mat_off;
+    double rs[2][4], cs[2] = {0.0, 0.0}, eh = 0.0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        rs[u][r] = 0.0;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          const int gi = i0 + wi * 32 + u * 16 + (lane >> 4) + 4 * r;
+          const int gj = j0 + wj * 32 + v * 16 + (lane & 15);
+          const bool in = gi < n && gj < n;
+          const int e = min(gi, n - 1) * n + min(gj, n - 1);
+          const double p = in ? acc[u][v][r] : 0.0;
+          const double x = p * Sm[e];
+          rs[u][r] += x;
+          cs[v] += x;
+          eh = fma(p, Hm[e], eh);
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) rs[u][r] += __shfl_xor(rs[u][r], off);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      cs[v] += __shfl_xor(cs[v], 16);
+      cs[v] += __shfl_xor(cs[v], 32);
+    }
+    eh = wave_sum_f64(eh);
+    // (the K loop ended with a barrier: its slabs are free)
+    double* rr = &As[0][0];  // [2 column halves][64]
+    double* cc = rr + 128;   // [2 row halves][64]
+    double* ee = cc + 128;
+    if ((lane & 15) == 0)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rr[64 * wj + wi * 32 + u * 16 + (lane >> 4) + 4 * r] = rs[u][r];
+    if (lane < 16)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) cc[64 * wi + wj * 32 + v * 16 + lane] = cs[v];
+    if (lane == 0) ee[wave] = eh;
+    __syncthreads();
+    double* part = Cbase + (long long)si * sym + (tj * (tj + 1) / 2 + ti) * POP_TILE;
+    if (tid < 64) part[tid] = rr[tid] + rr[64 + tid];
+    else if (tid < 128) part[tid] = cc[tid - 64] + cc[tid];
+    else if (tid == 128) part[128] = (ti < tj ? 2.0 : 1.0) * ((ee[0] + ee[1]) + (ee[2] + ee[3]));
+    return;
+  }
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -752,43 +823,12 @@ template __global__ void k_gemm_mfma<1, 0>(DevBatch, const int*, int, int, const
                                            const double*, int, int, int);
 template __global__ void k_gemm_mfma<2, 0>(DevBatch, const int*, int, int, const double*, const double*, double*,
                                            const double*, int, int, int);
+template __global__ void k_gemm_mfma<2, 2>(DevBatch, const int*, int, int, const double*, const double*, double*,
+                                           const double*, int, int, int);
 template __global__ void k_gemm_mfma<0, 1>(DevBatch, const int*, int, int, const double*, const double*, double*,
                                            const double*, int, int, int);
 template __global__ void k_gemm_mfma<1, 1>(DevBatch, const int*, int, int, const double*, const double*, double*,
                                            const double*, int, int, int);
-
-// Lower triangle of the listed systems' symmetric matrices from the upper
-// one, for the parts that a product with sym 2 leaves out: every element of
-// a 64 x 64 tile below the diagonal tiles (the diagonal tiles were computed
-// whole).  32 x 32 pieces pass through LDS so that reads and writes are
-// whole rows.
-__global__ void __launch_bounds__(256) k_mirror_tiles(DevBatch bt, const int* list, double* Abase) {
-  const int si = list[blockIdx.x];
-  const SysDesc d = bt.desc[si];
-  const int n = d.nao;
-  double* A = Abase + d.mat_off;
-  __shared__ double tr[32][33];
-  const int nt = (n + 31) / 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int I = 0; I < nt; ++I)
-    for (int J = I + 1; J < nt; ++J) {
-      if ((I >> 1) == (J >> 1)) continue;  // inside one 64 x 64 diagonal tile
-      const int j = 32 * J + tx;
-#pragma unroll
-      for (int r = 0; r < 32; r += 8) {
-        const int i = 32 * I + r + ty;
-        if (i < n && j < n) tr[r + ty][tx] = A[(long long)i * n + j];
-      }
-      __syncthreads();
-      const int ic = 32 * I + tx;
-#pragma unroll
-      for (int r = 0; r < 32; r += 8) {
-        const int jr = 32 * J + r + ty;
-        if (jr < n && ic < n) A[(long long)jr * n + ic] = tr[tx][r + ty];
-      }
-      __syncthreads();  // before the next piece overwrites tr
-    }
-}
 
 // ---------------------------------------------------------------------------
 // The batched products of the mixed-precision form (early SCC iterations) on
@@ -1324,9 +1364,12 @@ __device__ void solve_small(double* M, double* rhs, int m) {
   }
 }
 
-// eig 0: this iteration launched no eigensolver; the systems that need one wait
+// eig 0: this iteration launched no eigensolver; the systems that need one wait.
+// parts: the populations' and Tr(P H0)'s sums over the density's tiles
+// (k_gemm_mfma<2, 2>, pstride doubles per system), or null: from P itself
+// (systems of up to 32 AOs, FP32 iterations).
 __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol,
-                              int max_iter, double beta) {
+                              int max_iter, double beta, const double* parts, int pstride) {
   int si = list[blockIdx.x];
   if (bt.status[si] != 0 || (!eig && bt.mode[si] != 1)) return;
   const SysDesc d = bt.desc[si];
@@ -1349,7 +1392,20 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int e
   __shared__ double cpart[4 * MAXN];  // per-wave column sums, then matrix-vector partials
   const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63, nwv = blockDim.x >> 6;
   double eh = 0.0;
-  {
+  if (parts) {
+    // population of AO j in block J: the row sums of tiles (J, J ..), then the
+    // column sums of tiles (0 .. J - 1, J)
+    const double* pt = parts + (long long)si * pstride;
+    const int nt = (n + 63) >> 6;
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+      const int J = j >> 6, r = j & 63;
+      double v = 0.0;
+      for (int t = J; t < nt; ++t) v += pt[(t * (t + 1) / 2 + J) * POP_TILE + r];
+      for (int t = 0; t < J; ++t) v += pt[(J * (J + 1) / 2 + t) * POP_TILE + 64 + r];
+      pop[j] = v;
+    }
+    if ((int)threadIdx.x < nt * (nt + 1) / 2) eh = pt[threadIdx.x * POP_TILE + 128];
+  } else {
     constexpr int NC = MAXN / 64;
     double colacc[NC];
 #pragma unroll
