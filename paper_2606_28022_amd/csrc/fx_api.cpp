@@ -967,9 +967,11 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   DevBatch db = b.dev();
   DevSystem ds = dev_system();
   const int nl = (int)list.size();
-  // reset per-system iteration state on the device
-  b.d_list.upload(list);
-  hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl,
+  // reset per-system iteration state on the device (the whole batch has its
+  // list there already)
+  if (nl != b.nsys) b.d_list.upload(list);
+  const int* lst = nl == b.nsys ? b.d_all.p : b.d_list.p;
+  hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, lst, nl,
                      single ? 1 : 0, cold || refresh ? 1 : single ? 2 : 0);
   check(hipGetLastError(), "k_reset_state");
   if (cold) {
@@ -990,26 +992,26 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       const int ev = capturing ? -1 : timers.begin(stream);
       if (chol_elt == 8)
         hipLaunchKernelGGL(k_cholinv_lds<double>, dim3(nl), dim3(CHOL_THREADS_HOST), chol_lds, stream, db,
-                           b.d_list.p, A, X);
+                           lst, A, X);
       else if (chol_elt == 4)
         hipLaunchKernelGGL(k_cholinv_lds<float>, dim3(nl), dim3(CHOL_THREADS_HOST), chol_lds, stream, db,
-                           b.d_list.p, A, X);
+                           lst, A, X);
       else
-        hipLaunchKernelGGL(k_cholinv, dim3(nl), dim3(256), 0, stream, db, b.d_list.p, A, b.Pm.p, X);
+        hipLaunchKernelGGL(k_cholinv, dim3(nl), dim3(256), 0, stream, db, lst, A, b.Pm.p, X);
       if (!capturing) timers.end(stream, ev, kt_chol, gf / 3.0);
       check(hipGetLastError(), "k_cholinv");
     };
     // rows Y in Tm (approximately S-orthonormal) -> Ct
     auto refine_rows = [&]() {
-      gemm_batch(b, db, nl, b.d_list.p, 0, b.Tm.p, b.S.p, b.Pm.p, (const double*)nullptr, gf);
-      gemm_batch(b, db, nl, b.d_list.p, 1, b.Pm.p, b.Tm.p, b.Fm.p, (const double*)nullptr, gf, 0, 1);
-      gemm_batch(b, db, nl, b.d_list.p, 1, b.Fm.p, b.Fm.p, b.Pm.p, (const double*)nullptr, gf, 0, 1);
-      hipLaunchKernelGGL(k_ns_poly, dim3(8, nl), dim3(256), 0, stream, db, b.d_list.p, b.Fm.p, b.Pm.p);
-      gemm_batch(b, db, nl, b.d_list.p, 0, b.Fm.p, b.Tm.p, b.Ct.p, (const double*)nullptr, gf);
+      gemm_batch(b, db, nl, lst, 0, b.Tm.p, b.S.p, b.Pm.p, (const double*)nullptr, gf);
+      gemm_batch(b, db, nl, lst, 1, b.Pm.p, b.Tm.p, b.Fm.p, (const double*)nullptr, gf, 0, 1);
+      gemm_batch(b, db, nl, lst, 1, b.Fm.p, b.Fm.p, b.Pm.p, (const double*)nullptr, gf, 0, 1);
+      hipLaunchKernelGGL(k_ns_poly, dim3(8, nl), dim3(256), 0, stream, db, lst, b.Fm.p, b.Pm.p);
+      gemm_batch(b, db, nl, lst, 0, b.Fm.p, b.Tm.p, b.Ct.p, (const double*)nullptr, gf);
     };
     if (b.init_from_mono && mb.nsys > 0) {
       // C0 = blockdiag(monomer C); G = C0^T S C0 = L L^T; C = C0 L^-T
-      hipLaunchKernelGGL(k_cluster_init_ct, dim3(nl), dim3(256), 0, stream, db, b.d_list.p, mb.dev(),
+      hipLaunchKernelGGL(k_cluster_init_ct, dim3(nl), dim3(256), 0, stream, db, lst, mb.dev(),
                          b.has_warm ? (const long long*)b.warm_off.p : nullptr);
       // two-fragment clusters all started from their monomers: the factor
       // of I - X^T X (half the order) gives the same inverse factor, and
@@ -1027,19 +1029,19 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         n2max = std::max(n2max, sd.nao - n1);
       }
       block2 = block2 && (long long)cholinv_block2_lds_bytes(n1max, n2max) <= lds_max;
-      gemm_batch(b, db, nl, b.d_list.p, 0, b.Ct.p, b.S.p, b.Tm.p, (const double*)nullptr, gf, 0, 0, false,
+      gemm_batch(b, db, nl, lst, 0, b.Ct.p, b.S.p, b.Tm.p, (const double*)nullptr, gf, 0, 0, false,
                  block2 ? 1 : 0);
-      gemm_batch(b, db, nl, b.d_list.p, 1, b.Tm.p, b.Ct.p, b.Fm.p, (const double*)nullptr, gf, 0, 1, false,
+      gemm_batch(b, db, nl, lst, 1, b.Tm.p, b.Ct.p, b.Fm.p, (const double*)nullptr, gf, 0, 1, false,
                  block2 ? 1 : 0);
       if (chol_elt == 0) {
         cholinv(b.Fm.p, b.Tm.p);  // (k_cholinv uses Pm as its workspace)
-        gemm_batch(b, db, nl, b.d_list.p, 0, b.Tm.p, b.Ct.p, b.Fm.p, (const double*)nullptr, gf);
+        gemm_batch(b, db, nl, lst, 0, b.Tm.p, b.Ct.p, b.Fm.p, (const double*)nullptr, gf);
         check(hipMemcpyAsync(b.Ct.p, b.Fm.p, sizeof(double) * b.tot_mat, hipMemcpyDeviceToDevice, stream), "copy");
       } else {
         if (block2) {
           const int ev = capturing ? -1 : timers.begin(stream);
           hipLaunchKernelGGL(k_cholinv_block2, dim3(nl), dim3(CHOL_THREADS_HOST),
-                             (unsigned)cholinv_block2_lds_bytes(n1max, n2max), stream, db, b.d_list.p, mb.dev(),
+                             (unsigned)cholinv_block2_lds_bytes(n1max, n2max), stream, db, lst, mb.dev(),
                              (const double*)b.Fm.p, b.Pm.p);
           // the factor and inverse of the n/2 block plus the two n/2 products: about n^3 / 6
           double g2 = 0.0;
@@ -1049,7 +1051,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         } else {
           cholinv(b.Fm.p, b.Pm.p);
         }
-        gemm_batch(b, db, nl, b.d_list.p, 0, b.Pm.p, b.Ct.p, b.Tm.p, (const double*)nullptr, gf);
+        gemm_batch(b, db, nl, lst, 0, b.Pm.p, b.Ct.p, b.Tm.p, (const double*)nullptr, gf);
         if (chol_elt == 4)
           refine_rows();
         else
@@ -1064,6 +1066,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     }
     check(hipGetLastError(), "initial basis");
   }
+  if (small_batch(b)) return run_scc_small(b, db, lst, list, cold, iters_out, single);
   JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);
   {
     auto itp = tuned.find(jp_key(b.max_nao, jp.elt));
@@ -1210,7 +1213,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   if (async) {
     count_ring_init();
     d_act.alloc(nl);
-    check(hipMemcpyAsync(d_act.p, b.d_list.p, sizeof(int) * nl, hipMemcpyDeviceToDevice, stream), "copy");
+    check(hipMemcpyAsync(d_act.p, lst, sizeof(int) * nl, hipMemcpyDeviceToDevice, stream), "copy");
   }
   // launch shape of the fused LDS eigensolver, tuned once per size bucket on
   // the first iteration that runs it (the cold iteration of a solve from the
@@ -1228,6 +1231,24 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     jp = autotune_jacobi(b, dl, na, jp, cap);
     tuned[jp_key(b.max_nao, jp.elt)] = jp;
   };
+  if (single && !f32_ok && !verbose && split_ok) {
+    // one iteration of every listed system: nothing comes back to the host
+    launch_iteration(list, lst, nl, 0, jacobi_cap_err, true, refresh, refresh || mono_eig || !ov);
+    b.p_valid = b.max_nao <= 32;
+    for (int s : list) {
+      const double n = b.h_desc[s].nao, n3 = 1e-9 * n * n * n;
+      if (ov && !refresh && !mono_eig) {
+        const double no = std::ceil(0.5 * b.h_desc[s].nel), nv = n - no;
+        kt("fx::k_ov_grad")->gflop += 2e-9 * (n * n * no + n * no * nv);
+        kt("fx::k_ov_apply")->gflop += 8e-9 * n * no * nv;
+      } else {
+        kt_rot->gflop += 1.3 * n3;
+        kt_app->gflop += 2.0 * n3;
+      }
+    }
+    if (iters_out) *iters_out += nl;
+    return 0;
+  }
   for (int it = 0; it < max_it && !active.empty(); ++it) {
     const double cap = (cold && it == 0 && !b.init_from_mono) ? 1e300 : jacobi_cap_err;
     if (graph_mode && it >= 1) {
@@ -1238,7 +1259,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         stream = gstream;
         capturing = true;
         check(hipStreamBeginCapture(gstream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-        launch_iteration(list, b.d_list.p, nl, 0, jacobi_cap_err, false, false, true);
+        launch_iteration(list, lst, nl, 0, jacobi_cap_err, false, false, true);
         const hipError_t ec = hipStreamEndCapture(gstream, &graph);
         capturing = false;
         stream = saved;
@@ -1280,7 +1301,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       }
       const int slot = it % CNT_RING;
       hipLaunchKernelGGL(k_compact_active, dim3(1), dim3(1024), 0, stream, (const int*)b.status.p,
-                         (const int*)b.mode.p, (const int*)b.d_list.p, nl, d_act.p, cnt_dev.p + 2 * slot);
+                         (const int*)b.mode.p, (const int*)lst, nl, d_act.p, cnt_dev.p + 2 * slot);
       check(hipGetLastError(), "k_compact_active");
       check(hipMemcpyAsync(cnt_host + 2 * slot, cnt_dev.p + 2 * slot, 2 * sizeof(int), hipMemcpyDeviceToHost, stream),
             "count copy");
@@ -1402,7 +1423,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   std::vector<int> open(1, 0), modes;
   if (ov && !single) {
     d_open.upload(open);
-    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(256), 0, stream, db, (const int*)b.d_list.p, P.g.kT, d_open.p);
+    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(256), 0, stream, db, (const int*)lst, P.g.kT, d_open.p);
     check(hipGetLastError(), "k_ov_gap");
     d_open.download(open, stream);
     b.mode.download(modes, stream);
@@ -1462,6 +1483,94 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   // (systems whose gap closed on the way: the eigensolver from here on)
   if (!again.empty()) failed += run_scc(b, again, false, iters_out);
   return single ? 0 : failed;
+}
+
+// The same for a batch of systems of up to 32 AOs: whole solves in one kernel
+// (fx_small.hip).  Its sums are those of one system, so every schedule gives
+// the same bits.
+int Ctx::run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::vector<int>& list, bool cold,
+                       long long* iters_out, bool single) {
+  const int nl = (int)list.size();
+  SmallScc p{};
+  p.max_sweeps = jacobi_max_sweeps;
+  p.max_iter = single ? 1 : opt.max_iter;
+  p.rel_tol = jacobi_tol;
+  p.thr_scale = jacobi_thr_scale;
+  p.early_err = b.init_from_mono ? jacobi_early_err : 1e300;
+  p.cap_err = jacobi_cap_err;
+  p.tol = scc_tol_cur > 0 ? scc_tol_cur : opt.scc_tol;
+  p.etol = etol_cur > 0 ? etol_cur : opt.energy_tol;
+  p.beta = b.has_pre ? precond_beta : mix_beta;
+  p.cold = cold && !b.init_from_mono ? 1 : 0;
+  const DevSystem ds = dev_system();
+  auto launch = [&](int passes) {
+    p.passes = passes;
+    const int ev = timers.begin(stream);
+    auto* k = b.max_nao <= 16 ? k_scc_small<16> : k_scc_small<32>;
+    hipLaunchKernelGGL(k, dim3(nl), dim3(64), 0, stream, ds, db, lst, p);
+    timers.end(stream, ev, kt("fx::k_scc_small"), 0.0);
+    check(hipGetLastError(), "k_scc_small");
+    p.cold = 0;
+  };
+  b.p_valid = false;
+  if (single) {
+    launch(1);
+    kt("fx::k_scc_small")->gflop += small_gflop(b, list, {});
+    if (iters_out) *iters_out += nl;
+    return 0;
+  }
+  int left = opt.max_iter;
+  if (first_solve) {
+    // median first-iteration residual, learned-guess fallback
+    launch(1);
+    --left;
+    std::vector<double> e;
+    b.err.download(e, stream);
+    sync();
+    std::vector<double> v;
+    for (int s : list) v.push_back(e[s]);
+    std::nth_element(v.begin(), v.begin() + v.size() / 2, v.end());
+    res.first_residual_median = v[v.size() / 2];
+    auto fallback = [&](int phase) {
+      hipLaunchKernelGGL(k_guess_fallback, dim3(nl), dim3(64), 0, stream, db, lst, nl, phase, opt.guess_tau,
+                         fallback_flag.p);
+      check(hipGetLastError(), "k_guess_fallback");
+    };
+    if (opt.guess == FX_GUESS_LEARNED) {
+      if (opt.guess_tau > 0) fallback(0);
+      if (opt.guess_max_iter == 1) fallback(1);
+      if (opt.guess_max_iter > 1 && opt.guess_max_iter - 1 < left) {
+        launch(opt.guess_max_iter - 1);
+        left -= opt.guess_max_iter - 1;
+        fallback(1);
+      }
+    }
+  }
+  if (left > 0) launch(left);
+  std::vector<int> status, niter;
+  b.status.download(status, stream);
+  b.niter.download(niter, stream);
+  sync();
+  timers.resolve();
+  kt("fx::k_scc_small")->gflop += small_gflop(b, list, niter);
+  int failed = 0;
+  for (int s : list) {
+    if (status[s] != 1) ++failed;
+    if (iters_out) *iters_out += niter[s];
+  }
+  if (verbose) std::fprintf(stderr, "[fx] scc batch of %d systems (nao<=%d), one wave each\n", nl, b.max_nao);
+  return failed;
+}
+
+// algorithmic work of the listed systems' iterations (one each where niter is
+// empty): a dense symmetric eigensolve and the products
+double Ctx::small_gflop(const Batch& b, const std::vector<int>& list, const std::vector<int>& niter) const {
+  double g = 0.0;
+  for (int s : list) {
+    const double n = b.h_desc[s].nao;
+    g += (niter.empty() ? 1 : niter[s]) * (3.3 * n * n * n + 4.0 * n * n * n + n * n * b.h_desc[s].nel) * 1e-9;
+  }
+  return g;
 }
 
 // Passes of up to jacobi_cold_log logged sweeps over the na systems listed in

@@ -620,6 +620,13 @@ struct Ctx {
   void count_ring_init();
   int run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single = false,
               bool refresh = false);
+  // batches of systems of up to 32 AOs without projectors: one wave per system
+  // from Fock matrix to mixing (FX_SMALL=0: the batched kernels)
+  bool small_on = !(std::getenv("FX_SMALL") && std::atoi(std::getenv("FX_SMALL")) == 0);
+  bool small_batch(const Batch& b) const { return small_on && !b.has_hop && b.max_nao <= 32; }
+  int run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::vector<int>& list, bool cold,
+                    long long* iters_out, bool single);
+  double small_gflop(const Batch& b, const std::vector<int>& list, const std::vector<int>& niter) const;
   int solve_batch(Batch& b, bool cold, long long* iters_out);
   int retry_failed(Batch& b, long long* iters_out);
   // iteration cap of the damped retry stage (0: max(max_iter, 200));

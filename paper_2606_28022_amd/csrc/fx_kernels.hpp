@@ -62,6 +62,18 @@ __global__ void k_gemm_mfma(DevBatch bt, const int* list, int nl, int tiles_per_
                             int occ_list);
 __global__ void k_gemm(DevBatch bt, const int* list, int mode, const double* A, const double* B, double* C,
                        const double* w, int skip_done);
+// whole SCC solves of systems of up to 32 AOs, one wave each (fx_small.hip)
+struct SmallScc {
+  int passes;      // iterations of this launch at most
+  int cold;        // the first one starts from a basis that is no eigenbasis
+  int max_sweeps;  // Jacobi sweeps of a cold iteration
+  int max_iter;
+  double rel_tol, thr_scale;  // rotation threshold: times |A|, times the residual
+  double early_err, cap_err;  // two sweeps above the one and from the other on, else one
+  double tol, etol, beta;
+};
+template <int NP>
+__global__ void k_scc_small(DevSystem sys, DevBatch bt, const int* list, SmallScc p);
 // occupied-virtual rotations (fx_orb.hip): systems of up to OV_MAXN AOs, 32
 // occupied orbitals per work-group of eight waves, rotations of |X| up to
 // OV_XMAX while the SCC residual is below OV_ERRMAX (above them the
