@@ -971,9 +971,11 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   // list there already)
   if (nl != b.nsys) b.d_list.upload(list);
   const int* lst = nl == b.nsys ? b.d_all.p : b.d_list.p;
-  hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, lst, nl,
-                     single ? 1 : 0, cold || refresh ? 1 : single ? 2 : 0);
-  check(hipGetLastError(), "k_reset_state");
+  // (a fused monomer step: k_mono_begin has done it)
+  if (!single) {
+    hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, lst, nl, 0, cold ? 1 : 0);
+    check(hipGetLastError(), "k_reset_state");
+  }
   if (cold) {
     const int nt = (b.max_nao + 31) / 32;
     // inverse Cholesky factor in LDS: FP64 where the packed triangle fits,
@@ -1805,6 +1807,21 @@ Ctx::RotShape Ctx::rot_shape(Batch& b, const DevBatch& db, const int* dl, int na
   return best;
 }
 
+void Ctx::step_send() {
+  if (!step_host) {
+    check(hipEventCreateWithFlags(&step_ev, hipEventDisableTiming), "hipEventCreate");
+    check(hipHostMalloc((void**)&step_host, 2 * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+  }
+  check(hipMemcpyAsync(step_host, step_max.p, 2 * sizeof(double), hipMemcpyDeviceToHost, stream), "maxima copy");
+  check(hipEventRecord(step_ev, stream), "hipEventRecord");
+}
+
+void Ctx::step_wait(double* maxima) {
+  check(hipEventSynchronize(step_ev), "hipEventSynchronize");
+  maxima[0] = step_host[0];
+  maxima[1] = step_host[1];
+}
+
 void Ctx::count_ring_init() {
   if (cnt_host) return;
   if (cnt_dev.n < 2 * CNT_RING) cnt_dev.alloc(2 * CNT_RING);
@@ -2274,12 +2291,13 @@ void Ctx::run(fx_result* out) {
   hX.alloc((long long)HIST * Nsh);
   hR.alloc((long long)HIST * Nsh);
   hC.alloc(HIST);
+  DevBuf<double> hG;  // Gram matrix of the fused steps' residuals, by slot
+  hG.alloc(HIST * HIST);
+  step_part.alloc((long long)HIST * mb.nsys);
+  step_max.alloc(2);
   std::vector<int> slots;
   int next_slot = 0;
   const unsigned gN = (unsigned)((Nsh + 255) / 256);
-  mono_tmp.alloc(Nsh);
-  DevBuf<double> d_tmp_local;
-  d_tmp_local.alloc(mb.tot_sh);
   std::vector<int> all_mono(mb.nsys);
   for (int k = 0; k < mb.nsys; ++k) all_mono[k] = k;
   bool fused_mode = false;
@@ -2297,16 +2315,71 @@ void Ctx::run(fx_result* out) {
       next_slot = 0;
     }
     field(d_q.p, d_phi.p, field32);
-    hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_phi.p, mb.phi.p);
     int failed = 0;
+    Slots sl;
+    auto next_history = [&]() {
+      int slot;
+      if ((int)slots.size() < HIST) {
+        slot = next_slot++;
+      } else {
+        slot = slots.front();
+        slots.erase(slots.begin());
+      }
+      slots.push_back(slot);
+      sl.m = (int)slots.size();
+      for (int k = 0; k < sl.m; ++k) sl.id[k] = slots[k];
+      return slot;
+    };
     if (fused_mode) {
-      // one SCC iteration of every monomer at the globally mixed charges
-      hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_q.p, mb.q_in.p);
-      // (FP64 products in the fused steps: FP32 ones there cost more steps
-      // than they save)
+      // one SCC iteration of every monomer at the globally mixed charges, then
+      // the mixing of the next ones, with the monomer-block Newton step
+      // (1 + M_I G_I)^-1 (q_out - q_in) as the residual; the host learns of
+      // the step's residual while the mixing runs (a converged step takes the
+      // charges that the SCC iteration gave instead).  FP64 products: FP32
+      // ones here cost more steps than they save.
+      hipLaunchKernelGGL(k_mono_begin, dim3(mb.nsys), dim3(64), 0, stream, mb.dev(), (const double*)d_q.p,
+                         (const double*)d_phi.p, refresh ? 1 : 0, step_max.p);
       run_scc(mb, all_mono, false, &it_mono, true, refresh);
+      res.solves_mono += mb.nsys;
+      next_history();
+      hipLaunchKernelGGL(k_mono_end, dim3(mb.nsys), dim3(64), 0, stream, mb.dev(), d_qnew.p, hX.p, hR.p,
+                         (long long)Nsh, sl, step_part.p, step_max.p);
+      step_send();
+      hipLaunchKernelGGL(k_hist_next, dim3(std::min(gN, 256u)), dim3(256), 0, stream, (const double*)hX.p,
+                         (const double*)hR.p, (long long)Nsh, sl, (const double*)step_part.p, mb.nsys, hG.p, fused_beta,
+                         d_q.p);
+      check(hipGetLastError(), "monomer step");
+      const bool ov = ov_batch(mb);
+      double mx[2];
+      step_wait(mx);
+      delta = mx[0];
+      if (ov) {
+        // a rotation leaves the orbitals up to a fifth of |X| behind
+        if (!(0.2 * mx[1] <= delta)) delta = 0.2 * mx[1];
+        if (mono_eig) {
+          std::vector<int> modes;
+          mb.mode.download(modes, stream);
+          sync();
+          mono_eig = std::any_of(modes.begin(), modes.end(), [](int m) { return m != 1; });
+        } else {
+          mono_eig = mx[1] > OV_XMAX;
+        }
+      }
       refresh = false;
-    } else {
+      if (verbose)
+        std::fprintf(stderr, "[fx] monomer step %d: max |dq_out - dq_in| = %.3e, %.1f ms\n", macro, delta,
+                     now_ms() - t1);
+      if (delta < opt.macro_tol) {
+        if (canonical_basis(mb)) {
+          check(hipMemcpyAsync(d_q.p, d_qnew.p, sizeof(double) * Nsh, hipMemcpyDeviceToDevice, stream), "copy");
+          break;
+        }
+        mono_eig = true;  // a gap closed on the way: on with the eigensolver
+      }
+      continue;
+    }
+    hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_phi.p, mb.phi.p);
+    {
       if (cold)
         hipLaunchKernelGGL(k_gather_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_q.p, mb.q_in.p);
       else
@@ -2337,29 +2410,17 @@ void Ctx::run(fx_result* out) {
     cold = false;
     res.solves_mono += mb.nsys;
     hipLaunchKernelGGL(k_scatter_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, mb.q_out.p, d_qnew.p);
-    max_absdiff(d_qnew.p, d_q.p, Nsh, d_scalar.p, mb.xn.p, mb.nsys);
-    std::vector<double> hs(2);
-    d_scalar.download(hs, stream, 2);
-    std::vector<int> modes;
-    const bool ov = ov_batch(mb) && fused_mode;
-    if (ov && mono_eig) mb.mode.download(modes, stream);
+    max_absdiff(d_qnew.p, d_q.p, Nsh, d_scalar.p);
+    std::vector<double> hs(1);
+    d_scalar.download(hs, stream, 1);
     sync();
     delta = hs[0];
-    if (ov) {
-      // a rotation leaves the orbitals up to a fifth of |X| behind
-      delta = std::max(delta, 0.2 * hs[1]);
-      if (mono_eig)
-        mono_eig = std::any_of(modes.begin(), modes.end(), [](int m) { return m != 1; });
-      else
-        mono_eig = hs[1] > OV_XMAX;
-    }
     if (verbose)
-      std::fprintf(stderr, "[fx] monomer %s %d: max |dq_out - dq_in| = %.3e, %.1f ms\n",
-                   fused_mode ? "step" : "sweep", macro, delta, now_ms() - t1);
-    if (delta < opt.macro_tol && !canonical_basis(mb)) {
-      mono_eig = true;  // a gap closed on the way: on with the eigensolver
-    } else if (delta < opt.macro_tol) {
+      std::fprintf(stderr, "[fx] monomer sweep %d: max |dq_out - dq_in| = %.3e, %.1f ms\n", macro, delta,
+                   now_ms() - t1);
+    if (delta < opt.macro_tol) {
       if (failed) all_conv = false;
+      (void)canonical_basis(mb);
       check(hipMemcpyAsync(d_q.p, d_qnew.p, sizeof(double) * Nsh, hipMemcpyDeviceToDevice, stream), "copy");
       break;
     }
@@ -2371,30 +2432,13 @@ void Ctx::run(fx_result* out) {
       next_slot = 0;
       continue;
     }
-    // history update and mixing; in the fused loop the residual is the
-    // monomer-block Newton step (1 + M_I G_I)^-1 (q_out - q_in)
-    const double* target = d_qnew.p;
-    if (fused_mode) {
-      hipLaunchKernelGGL(k_precond_step, dim3(mb.nsys), dim3(128), 0, stream, mb.dev(), d_tmp_local.p);
-      hipLaunchKernelGGL(k_scatter_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, d_tmp_local.p, mono_tmp.p);
-      target = mono_tmp.p;
-    }
-    int slot;
-    if ((int)slots.size() < HIST) {
-      slot = next_slot++;
-    } else {
-      slot = slots.front();
-      slots.erase(slots.begin());
-    }
-    slots.push_back(slot);
-    hipLaunchKernelGGL(k_hist_store, dim3(gN), dim3(256), 0, stream, d_q.p, target, (long long)Nsh, slot, hX.p,
+    // history update and mixing
+    const int slot = next_history();
+    hipLaunchKernelGGL(k_hist_store, dim3(gN), dim3(256), 0, stream, d_q.p, d_qnew.p, (long long)Nsh, slot, hX.p,
                        hR.p);
-    Slots sl;
-    sl.m = (int)slots.size();
-    for (int k = 0; k < sl.m; ++k) sl.id[k] = slots[k];
     hist_coef(hR.p, (long long)Nsh, sl, hC.p);
-    hipLaunchKernelGGL(k_hist_mix, dim3(gN), dim3(256), 0, stream, hX.p, hR.p, (long long)Nsh, sl, hC.p,
-                       fused_mode ? fused_beta : macro_beta, d_q.p);
+    hipLaunchKernelGGL(k_hist_mix, dim3(gN), dim3(256), 0, stream, hX.p, hR.p, (long long)Nsh, sl, hC.p, macro_beta,
+                       d_q.p);
     check(hipGetLastError(), "monomer mixing");
   }
   if (macro > opt.max_macro) {

@@ -213,6 +213,44 @@ __device__ inline double wave_sum_f64(double v) {
                           __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
+// LDS written by some lanes of a wave may be read by its other lanes (no
+// work-group barrier)
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Solution of the M x M system in B (LDS, M <= 63 rows of M + 1: matrix and
+// right-hand side; overwritten) by one wave: Gauss-Jordan elimination with row
+// pivoting, 64 elements at a time.  f: M doubles of LDS.  Lane k < M returns
+// unknown k.  (One thread eliminating the mixers' 9 x 9 system took 10 to
+// 25 us, this takes 3.)
+__device__ inline double wave_solve(double* B, double* f, int M) {
+  const int lane = threadIdx.x & 63, W = M + 1;
+  unsigned long long used = 0;
+  int row = 0;  // the lane's unknown: its pivot row
+  for (int c = 0; c < M; ++c) {
+    const double t = lane < M && !(used >> lane & 1ULL) ? fabs(B[lane * W + c]) : -1.0;
+    // (clamped: a column of NaN leaves no candidate)
+    const int piv = min(max(__ffsll((unsigned long long)__ballot(t == wave_max_f64(t))) - 1, 0), M - 1);
+    used |= 1ULL << piv;
+    if (lane == c) row = piv;
+    double dv = B[piv * W + c];
+    if (fabs(dv) < 1e-300) dv = 1e-300;
+    if (lane < M) f[lane] = lane != piv ? B[lane * W + c] / dv : 0.0;
+    wave_sync();
+    const int wc = W - c - 1;  // columns c + 1 ..
+    for (int e = lane; e < M * wc; e += 64) {
+      const int r = e / wc, k = c + 1 + e - r * wc;
+      if (r != piv) B[r * W + k] -= f[r] * B[piv * W + k];
+    }
+    if (lane == 0) B[piv * W + c] = dv;
+    wave_sync();
+  }
+  return lane < M ? B[row * W + M] / B[row * W + lane] : 0.0;
+}
+
 // List slot and tile of work-group L in a launch of xcd_grid(nl, tps)
 // work-groups over nl systems of tps tiles each.  The dispatcher deals
 // consecutive work-group ids to the 8 XCDs in turn; slot s runs on XCD s % 8

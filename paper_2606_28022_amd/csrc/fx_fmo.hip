@@ -278,6 +278,205 @@ __global__ void k_hist_store(const double* x, const double* y, long long n, int 
   R[(long long)slot * n + k] = y[k] - x[k];
 }
 
+// ---------------------------------------------------------------------------
+// The iterations over the whole charge vector (fused monomer steps, adjoint
+// response) as few launches: on small systems a step is launch latency, and a
+// step of separate gather, reset, scatter, difference, maximum, history and
+// Gram launches took 18 of them besides its field pass and its SCC iteration.
+
+// start of a fused monomer step, per monomer: charges and field of its shells,
+// iteration state cleared (as k_reset_state with the residual kept); refresh:
+// the eigensolver takes it.  The step's maxima are cleared too.
+__global__ void __launch_bounds__(64) k_mono_begin(DevBatch bt, const double* q, const double* phi, int refresh,
+                                                   unsigned long long* maxima) {
+  const int si = blockIdx.x;
+  const SysDesc d = bt.desc[si];
+  for (int s = threadIdx.x; s < d.nsh; s += 64) {
+    const int g = bt.sys_sh_global[d.sh_off + s];
+    bt.q_in[d.sh_off + s] = q[g];
+    bt.phi[d.sh_off + s] = phi[g];
+  }
+  if (threadIdx.x == 0) {
+    bt.status[si] = 0;
+    bt.niter[si] = 0;
+    bt.nhist[si] = 0;
+    bt.e_prev[si] = 0.0;
+    if (refresh) {
+      bt.mode[si] = 0;
+      bt.xn[si] = -1.0;
+    }
+    if (si == 0) maxima[0] = maxima[1] = 0ULL;
+  }
+}
+
+// history row of the system's shells: x and r into the newest slot, and the
+// products of r with the m residuals into part[HIST si + k] (k-th oldest)
+__device__ inline void hist_row(const DevBatch& bt, const SysDesc& d, int si, double* X, double* R, long long n,
+                                const Slots& sl, const double* x, const double* r, double* part) {
+  const int m = sl.m;
+  double acc[HIST];
+#pragma unroll
+  for (int k = 0; k < HIST; ++k) acc[k] = 0.0;
+  for (int s = threadIdx.x; s < d.nsh; s += 64) {
+    const int g = bt.sys_sh_global[d.sh_off + s];
+    X[(long long)sl.id[m - 1] * n + g] = x[s];
+    R[(long long)sl.id[m - 1] * n + g] = r[s];
+#pragma unroll
+    for (int k = 0; k < HIST; ++k)
+      if (k < m) acc[k] = fma(r[s], k == m - 1 ? r[s] : R[(long long)sl.id[k] * n + g], acc[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < HIST; ++k) {
+    const double v = wave_sum_f64(acc[k]);
+    if (threadIdx.x == 0) part[HIST * si + k] = v;
+  }
+}
+
+// maximum into a cleared slot: non-negative numbers order as their bits (a NaN
+// above all, so that it never passes for convergence)
+__device__ inline void max_into(unsigned long long* m, double v) {
+  atomicMax(m, (unsigned long long)__double_as_longlong(fabs(v)));
+}
+
+// end of a fused monomer step, per monomer (one wave): its charges into q_new,
+// max |q_out - q_in| and max |X| (DevBatch), and the history row of the
+// Newton step (1 + M G)^-1 (q_out - q_in) (bt.pre, stored transposed)
+__global__ void __launch_bounds__(64) k_mono_end(DevBatch bt, double* q_new, double* X, double* R, long long n, Slots sl,
+                                                 double* part, unsigned long long* maxima) {
+  const int si = blockIdx.x;
+  const SysDesc d = bt.desc[si];
+  const int ns = d.nsh, lane = threadIdx.x;
+  __shared__ double r[MAXN], v[MAXN];
+  const double* qi = bt.q_in + d.sh_off;
+  const double* qo = bt.q_out + d.sh_off;
+  double dm = 0.0;
+  bool nan = false;
+  for (int s = lane; s < ns; s += 64) {
+    const double t = qo[s] - qi[s];
+    r[s] = t;
+    nan = nan || t != t;
+    dm = fmax(dm, fabs(t));
+    q_new[bt.sys_sh_global[d.sh_off + s]] = qo[s];
+  }
+  dm = wave_max_f64(dm);
+  nan = __ballot(nan) != 0;
+  __syncthreads();
+  const float* Pr = bt.pre + d.gam_off;
+  for (int s = lane; s < ns; s += 64) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int u = 0; u < ns; ++u) t += (double)Pr[(long long)u * ns + s] * r[u];
+    v[s] = t;
+  }
+  __syncthreads();
+  hist_row(bt, d, si, X, R, n, sl, qi, v, part);
+  if (lane == 0) {
+    max_into(maxima, nan ? __longlong_as_double(0x7ff8000000000000LL) : dm);
+    max_into(maxima + 1, fmax(bt.xn[si], 0.0));
+  }
+}
+
+// one adjoint response sweep, per monomer: w = R y, u = -M w
+__global__ void __launch_bounds__(64) k_resp_sweep(DevBatch bt, const double* R, const double* M, const double* y,
+                                                   double* w, double* u, unsigned long long* maxima) {
+  const int si = blockIdx.x;
+  const SysDesc d = bt.desc[si];
+  const int ns = d.nsh;
+  __shared__ double ys[MAXN], ws[MAXN];
+  for (int s = threadIdx.x; s < ns; s += 64) ys[s] = y[bt.sys_sh_global[d.sh_off + s]];
+  __syncthreads();
+  for (int s = threadIdx.x; s < ns; s += 64) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int t = 0; t < ns; ++t) v += R[d.gam_off + (long long)s * ns + t] * ys[t];
+    ws[s] = v;
+    w[d.sh_off + s] = v;
+  }
+  __syncthreads();
+  for (int s = threadIdx.x; s < ns; s += 64) {
+    double v = 0.0;
+#pragma unroll 8
+    for (int t = 0; t < ns; ++t) v += M[d.gam_off + (long long)t * ns + s] * ws[t];  // (M is symmetric)
+    u[bt.sys_sh_global[d.sh_off + s]] = -v;
+  }
+  if (si == 0 && threadIdx.x == 0) maxima[0] = maxima[1] = 0ULL;
+}
+
+// its end, per monomer: y_new = v + field of u, max |y_new - y|, history row
+__global__ void __launch_bounds__(64) k_resp_end(DevBatch bt, const double* v, const double* fu, const double* y,
+                                                 double* y_new, double* X, double* R, long long n, Slots sl,
+                                                 double* part, unsigned long long* maxima) {
+  const int si = blockIdx.x;
+  const SysDesc d = bt.desc[si];
+  __shared__ double x[MAXN], r[MAXN];
+  double dm = 0.0;
+  bool nan = false;
+  for (int s = threadIdx.x; s < d.nsh; s += 64) {
+    const int g = bt.sys_sh_global[d.sh_off + s];
+    const double yn = v[g] + fu[g], yo = y[g], t = yn - yo;
+    y_new[g] = yn;
+    x[s] = yo;
+    r[s] = t;
+    nan = nan || t != t;
+    dm = fmax(dm, fabs(t));
+  }
+  dm = wave_max_f64(dm);
+  nan = __ballot(nan) != 0;
+  __syncthreads();
+  hist_row(bt, d, si, X, R, n, sl, x, r, part);
+  if (threadIdx.x == 0) max_into(maxima, nan ? __longlong_as_double(0x7ff8000000000000LL) : dm);
+}
+
+// Mixing of such a step: the newest residual's Gram row from the systems'
+// parts (fixed order), the other entries from gram[slot][slot] (where
+// work-group 0 also stores the new row), the coefficients by one wave of every
+// work-group, and the work-group's slice of q = sum_k c_k (x_k + beta r_k).
+__global__ void __launch_bounds__(256) k_hist_next(const double* X, const double* R, long long n, Slots sl,
+                                                   const double* part, int nparts, double* gram, double beta,
+                                                   double* q) {
+  const int m = sl.m, M = m + 1, W = M + 1, t = threadIdx.x;
+  __shared__ double sum[32][HIST], row[HIST], B[(HIST + 1) * (HIST + 2)], f[HIST + 1], coef[HIST];
+  {
+    const int k = t & (HIST - 1);
+    double v = 0.0;
+    for (int p = t / HIST; p < nparts; p += 32) v += part[HIST * p + k];
+    sum[t / HIST][k] = v;
+  }
+  __syncthreads();
+  if (t < HIST) {
+    double v = 0.0;
+    for (int p = 0; p < 32; ++p) v += sum[p][t];
+    row[t] = v;
+    if (blockIdx.x == 0 && t < m) {
+      gram[sl.id[m - 1] * HIST + sl.id[t]] = v;
+      if (t != m - 1) gram[sl.id[t] * HIST + sl.id[m - 1]] = v;
+    }
+  }
+  __syncthreads();
+  if (t < 64) {
+    auto entry = [&](int i, int j) {
+      return i == m - 1 ? row[j] : j == m - 1 ? row[i] : gram[sl.id[i] * HIST + sl.id[j]];
+    };
+    double tr = 0.0;
+    for (int i = 0; i < m; ++i) tr += entry(i, i);
+    for (int e = t; e < M * W; e += 64) {
+      const int i = e / W, j = e - i * W;
+      double v = j == M ? (i == m ? 1.0 : 0.0) : i == j ? 0.0 : 1.0;
+      if (i < m && j < m) v = entry(i, j) + (i == j ? 1e-14 * tr : 0.0);
+      B[e] = v;
+    }
+    wave_sync();
+    const double c = wave_solve(B, f, M);
+    if (t < m) coef[t] = c;
+  }
+  __syncthreads();
+  for (long long g = (long long)blockIdx.x * 256 + t; g < n; g += (long long)gridDim.x * 256) {
+    double v = 0.0;
+    for (int k = 0; k < m; ++k) v += coef[k] * (X[sl.id[k] * n + g] + beta * R[sl.id[k] * n + g]);
+    q[g] = v;
+  }
+}
+
 // Trimer corrections Delta E_IJK - Delta E_IJ - Delta E_IK - Delta E_JK
 // (eq. fmo3_energy; an ES-DIM sub-pair enters with its ES-DIM value): sub
 // holds, per trimer, the three sub-pairs as an index into dE_scc or nscc +

@@ -287,7 +287,7 @@ void Ctx::gradient() {
     d_nocc.upload(nocc);
     DevBuf<long long> d_qoff;
     d_qoff.upload(qoff);
-    DevBuf<double> Q, M, R, Wk, G1, G2, G3, w, y, yn, ul, gx;
+    DevBuf<double> Q, M, R, Wk, G1, G2, G3, w, gx;
     long long tot_gam = 0;
     for (auto& d : b.h_desc) tot_gam += (long long)d.nsh * d.nsh;
     if (!resp_ok) {
@@ -301,8 +301,6 @@ void Ctx::gradient() {
     G2.alloc(b.tot_mat);
     G3.alloc(b.tot_mat);
     w.alloc(b.tot_sh);
-    y.alloc(b.tot_sh);
-    ul.alloc(b.tot_sh);
     gx.alloc(b.tot_sh);
     std::vector<int> all(b.nsys);
     for (int k = 0; k < b.nsys; ++k) all[k] = k;
@@ -335,13 +333,13 @@ void Ctx::gradient() {
       hipLaunchKernelGGL(k_resp_R, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, p_M, Wk.p, R.p);
     check(hipGetLastError(), "response setup");
     // adjoint sweeps y = v + field_excl(u(y)), Anderson-accelerated
-    DevBuf<double> yg, yng, hX, hR, hC, fu;
+    DevBuf<double> yg, yng, hX, hR, hG, fu;
     yg.alloc(Nsh);
     yng.alloc(Nsh);
     fu.alloc(Nsh);
     hX.alloc((long long)HIST * Nsh);
     hR.alloc((long long)HIST * Nsh);
-    hC.alloc(HIST);
+    hG.alloc(HIST * HIST);
     check(hipMemcpyAsync(yg.p, v.p, sizeof(double) * Nsh, hipMemcpyDeviceToDevice, stream), "copy");
     std::vector<int> slots;
     int next_slot = 0;
@@ -357,16 +355,30 @@ void Ctx::gradient() {
     // the FP32 sweeps end after a quarter of the allowed sweeps at the latest
     const int max_fp32_sweeps = std::max(1, max_sweeps / 4);
     for (it = 1; it <= max_sweeps; ++it) {
-      hipLaunchKernelGGL(k_gather_shell, dim3(b.nsys), dim3(64), 0, stream, dmb, yg.p, y.p);
-      hipLaunchKernelGGL(k_resp_apply, dim3(b.nsys), dim3(256), 0, stream, dmb, R.p, p_M, y.p, w.p, ul.p);
-      hipLaunchKernelGGL(k_scatter_shell, dim3(b.nsys), dim3(64), 0, stream, dmb, ul.p, u.p);
+      hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M,
+                         (const double*)yg.p, w.p, u.p, step_max.p);
       field(u.p, fu.p, field32);
-      hipLaunchKernelGGL(k_axpy, dim3(gN), dim3(256), 0, stream, (long long)Nsh, v.p, 1.0, fu.p, yng.p);
-      max_absdiff(yng.p, yg.p, Nsh, d_scalar.p);
-      std::vector<double> hs(1);
-      d_scalar.download(hs, stream, 1);
-      sync();
-      delta = hs[0];
+      int slot;
+      if ((int)slots.size() < HIST) {
+        slot = next_slot++;
+      } else {
+        slot = slots.front();
+        slots.erase(slots.begin());
+      }
+      slots.push_back(slot);
+      Slots sl;
+      sl.m = (int)slots.size();
+      for (int k = 0; k < sl.m; ++k) sl.id[k] = slots[k];
+      hipLaunchKernelGGL(k_resp_end, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)v.p, (const double*)fu.p,
+                         (const double*)yg.p, yng.p, hX.p, hR.p, (long long)Nsh, sl, step_part.p, step_max.p);
+      step_send();
+      // (the mixing runs while the host learns of the sweep's change)
+      hipLaunchKernelGGL(k_hist_next, dim3(std::min(gN, 256u)), dim3(256), 0, stream, (const double*)hX.p,
+                         (const double*)hR.p, (long long)Nsh, sl, (const double*)step_part.p, b.nsys, hG.p, 1.0, yg.p);
+      check(hipGetLastError(), "response sweep");
+      double mx[2];
+      step_wait(mx);
+      delta = mx[0];
       if (verbose) std::fprintf(stderr, "[fx] response sweep %d: max |dy| = %.3e\n", it, delta);
       if (field32 && (delta < 1e-6 || it >= max_fp32_sweeps)) {
         field32 = false;
@@ -376,22 +388,6 @@ void Ctx::gradient() {
         resp_converged = true;
         break;
       }
-      int slot;
-      if ((int)slots.size() < HIST) {
-        slot = next_slot++;
-      } else {
-        slot = slots.front();
-        slots.erase(slots.begin());
-      }
-      slots.push_back(slot);
-      hipLaunchKernelGGL(k_hist_store, dim3(gN), dim3(256), 0, stream, yg.p, yng.p, (long long)Nsh, slot, hX.p, hR.p);
-      Slots sl;
-      sl.m = (int)slots.size();
-      for (int k = 0; k < sl.m; ++k) sl.id[k] = slots[k];
-      hist_coef(hR.p, (long long)Nsh, sl, hC.p);
-      hipLaunchKernelGGL(k_hist_mix, dim3(gN), dim3(256), 0, stream, hX.p, hR.p, (long long)Nsh, sl, hC.p, 1.0,
-                         yg.p);
-      check(hipGetLastError(), "response mixing");
     }
     response_sweeps = std::min(it, max_sweeps);
     if (!resp_converged) {
@@ -400,9 +396,8 @@ void Ctx::gradient() {
                                 max_sweeps, delta);
     }
     // final w, u from the converged y
-    hipLaunchKernelGGL(k_gather_shell, dim3(b.nsys), dim3(64), 0, stream, dmb, yng.p, y.p);
-    hipLaunchKernelGGL(k_resp_apply, dim3(b.nsys), dim3(256), 0, stream, dmb, R.p, p_M, y.p, w.p, ul.p);
-    hipLaunchKernelGGL(k_scatter_shell, dim3(b.nsys), dim3(64), 0, stream, dmb, ul.p, u.p);
+    hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M,
+                       (const double*)yng.p, w.p, u.p, step_max.p);
     // Z and its AO forms
     hipLaunchKernelGGL(k_resp_Z, dim3(b.nsys), dim3(256), 0, stream, dmb, p_order, d_nocc.p, d_qoff.p, p_Q, w.p,
                        G2.p, G3.p);

@@ -351,6 +351,8 @@ struct Ctx {
     for (hipEvent_t e : cnt_ev)
       if (e) (void)hipEventDestroy(e);
     if (cnt_host) (void)hipHostFree(cnt_host);
+    if (step_ev) (void)hipEventDestroy(step_ev);
+    if (step_host) (void)hipHostFree(step_host);
   }
   HostParams P;
   int device = 0;
@@ -442,7 +444,6 @@ struct Ctx {
   // per step with global (preconditioned) mixing of all monomer charges
   bool fused = !(std::getenv("FX_FUSED") && std::atoi(std::getenv("FX_FUSED")) == 0);
   double fused_beta = std::getenv("FX_FUSED_BETA") ? std::atof(std::getenv("FX_FUSED_BETA")) : 1.0;
-  DevBuf<double> mono_tmp;
   bool monomer_response_setup();
   // dynamic LDS of k_resp_M for a batch (throws when a system is too large)
   unsigned resp_M_lds(const Batch& b) const;
@@ -618,6 +619,14 @@ struct Ctx {
   std::vector<hipEvent_t> cnt_ev;
   DevBuf<int> cnt_dev;
   void count_ring_init();
+  // maxima of a step of the iterations over the whole charge vector
+  // (k_mono_end, k_resp_end): device pair, pinned copy, event
+  DevBuf<unsigned long long> step_max;
+  double* step_host = nullptr;
+  hipEvent_t step_ev = nullptr;
+  void step_send();                // queue the copy
+  void step_wait(double* maxima);  // wait for it
+  DevBuf<double> step_part;        // Gram row parts, HIST per monomer
   int run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single = false,
               bool refresh = false);
   // batches of systems of up to 32 AOs without projectors: one wave per system

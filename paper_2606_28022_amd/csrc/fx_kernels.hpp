@@ -34,7 +34,6 @@ __global__ void k_hist_reset(DevBatch bt, const int* list, int nl);
 // xcd_slot_tile: 8 ceil(nl / 8) tps
 inline long long xcd_grid(int nl, int tps) { return 8LL * ((nl + 7) / 8) * tps; }
 __global__ void k_compact_active(const int* status, const int* mode, const int* list, int nl, int* act, int* count);
-__global__ void k_precond_step(DevBatch bt, double* out);
 __global__ void k_cholinv(DevBatch bt, const int* list, const double* Apool, double* Lpool, double* Xpool);
 __global__ void k_cluster_init_ct(DevBatch bt, const int* list, DevBatch mono, const long long* warm_off);
 __global__ void k_warm_start(DevBatch bt, const long long* mat_off_old, const long long* sh_off_old,
@@ -199,6 +198,16 @@ __global__ void k_hist_gram_part(const double* R, long long n, Slots sl, double*
 __global__ void k_hist_solve(const double* part, int np, Slots sl, double* coef);
 __global__ void k_hist_mix(const double* X, const double* R, long long n, Slots sl, const double* coef, double beta,
                            double* q);
+// the iterations over the whole charge vector in few launches
+__global__ void k_mono_begin(DevBatch bt, const double* q, const double* phi, int refresh, unsigned long long* maxima);
+__global__ void k_mono_end(DevBatch bt, double* q_new, double* X, double* R, long long n, Slots sl, double* part,
+                           unsigned long long* maxima);
+__global__ void k_resp_sweep(DevBatch bt, const double* R, const double* M, const double* y, double* w, double* u,
+                             unsigned long long* maxima);
+__global__ void k_resp_end(DevBatch bt, const double* v, const double* fu, const double* y, double* y_new, double* X,
+                           double* R, long long n, Slots sl, double* part, unsigned long long* maxima);
+__global__ void k_hist_next(const double* X, const double* R, long long n, Slots sl, const double* part, int nparts,
+                            double* gram, double beta, double* q);
 __global__ void k_hist_store(const double* x, const double* y, long long n, int slot, double* X, double* R);
 
 // response and gradient kernels
@@ -219,7 +228,6 @@ __global__ void k_resp_R(DevSystem sys, DevBatch bt, const double* M, double* Wk
 // k_resp_R_lds: systems of at most MAXN_RESP_LDS shells (the matrix in LDS)
 constexpr int MAXN_RESP_LDS = 96, RR_THREADS = 512;
 __global__ void k_resp_R_lds(DevSystem sys, DevBatch bt, const double* M, double* R);
-__global__ void k_resp_apply(DevBatch bt, const double* R, const double* M, const double* y, double* w, double* u);
 __global__ void k_resp_Z(DevBatch bt, const int* order, const int* nocc, const long long* qoff, const double* Q,
                          const double* w, double* Zm, double* Ze);
 __global__ void k_rowscale(DevBatch bt, const double* wsh, const double* P, double* out);

@@ -548,26 +548,6 @@ __global__ void __launch_bounds__(RR_THREADS) k_resp_R_lds(DevSystem sys, DevBat
   }
 }
 
-// w = R y,  u = -M w   (local shell vectors)
-__global__ void k_resp_apply(DevBatch bt, const double* R, const double* M, const double* y, double* w, double* u) {
-  const int si = blockIdx.x;
-  const SysDesc d = bt.desc[si];
-  const int ns = d.nsh;
-  __shared__ double ws[MAXN];
-  for (int s = threadIdx.x; s < ns; s += blockDim.x) {
-    double v = 0.0;
-    for (int t = 0; t < ns; ++t) v += R[d.gam_off + (long long)s * ns + t] * y[d.sh_off + t];
-    ws[s] = v;
-    w[d.sh_off + s] = v;
-  }
-  __syncthreads();
-  for (int s = threadIdx.x; s < ns; s += blockDim.x) {
-    double v = 0.0;
-    for (int t = 0; t < ns; ++t) v += M[d.gam_off + (long long)s * ns + t] * ws[t];
-    u[d.sh_off + s] = -v;
-  }
-}
-
 // Z in the MO basis: Zm[a][i] = -2 (w . Q_ai) / (eps_a - eps_i) and
 // Ze[a][i] = Zm[a][i] eps_i (zero elsewhere)
 __global__ void k_resp_Z(DevBatch bt, const int* order, const int* nocc, const long long* qoff, const double* Q,

@@ -143,26 +143,6 @@ __global__ void __launch_bounds__(1024) k_compact_active(const int* status, cons
   }
 }
 
-// Preconditioned monomer step of the fused embedding loop, per system:
-// out = q_in + (1 + M G)^-1 (q_out - q_in) (local shell vectors)
-__global__ void k_precond_step(DevBatch bt, double* out) {
-  const int si = blockIdx.x;
-  const SysDesc d = bt.desc[si];
-  const int ns = d.nsh;
-  __shared__ double r[MAXN];
-  const double* qi = bt.q_in + d.sh_off;
-  const double* qo = bt.q_out + d.sh_off;
-  for (int s = threadIdx.x; s < ns; s += blockDim.x) r[s] = qo[s] - qi[s];
-  __syncthreads();
-  const float* Pr = bt.pre + d.gam_off;
-  for (int s = threadIdx.x; s < ns; s += blockDim.x) {
-    double v = 0.0;
-#pragma unroll 8
-    for (int t = 0; t < ns; ++t) v += (double)Pr[(long long)t * ns + s] * r[t];  // stored transposed
-    out[d.sh_off + s] = qi[s] + v;
-  }
-}
-
 // initial basis of a cluster from its monomers' eigenvectors: block-diagonal
 // rows of the monomer C^T (fragment order), later S-orthonormalised.
 __global__ void k_cluster_init_ct(DevBatch bt, const int* list, DevBatch mono, const long long* warm_off) {
@@ -1332,38 +1312,6 @@ __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate)
 
 // ---------------------------------------------------------------------------
 // Mulliken charges of P, energy, convergence test and Anderson mixing.
-__device__ void solve_small(double* M, double* rhs, int m) {
-  // Gaussian elimination with partial pivoting on an (m x m) system, in place
-  for (int c = 0; c < m; ++c) {
-    int piv = c;
-    for (int r = c + 1; r < m; ++r)
-      if (fabs(M[r * m + c]) > fabs(M[piv * m + c])) piv = r;
-    if (piv != c) {
-      for (int k = 0; k < m; ++k) {
-        double t = M[c * m + k];
-        M[c * m + k] = M[piv * m + k];
-        M[piv * m + k] = t;
-      }
-      double t = rhs[c];
-      rhs[c] = rhs[piv];
-      rhs[piv] = t;
-    }
-    double dv = M[c * m + c];
-    if (fabs(dv) < 1e-300) dv = 1e-300;
-    for (int r = c + 1; r < m; ++r) {
-      double f = M[r * m + c] / dv;
-      for (int k = c; k < m; ++k) M[r * m + k] -= f * M[c * m + k];
-      rhs[r] -= f * rhs[c];
-    }
-  }
-  for (int c = m - 1; c >= 0; --c) {
-    double v = rhs[c];
-    for (int k = c + 1; k < m; ++k) v -= M[c * m + k] * rhs[k];
-    double dv = M[c * m + c];
-    rhs[c] = v / (fabs(dv) < 1e-300 ? 1e-300 : dv);
-  }
-}
-
 // eig 0: this iteration launched no eigensolver; the systems that need one wait.
 // parts: the populations' and Tr(P H0)'s sums over the density's tiles
 // (k_gemm_mfma<2, 2>, pstride doubles per system), or null: from P itself
@@ -1554,7 +1502,7 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int e
     // B_ij = r_i . r_j (slots ordered oldest..newest): every thread
     // accumulates its part of all m (m + 1) / 2 products in one pass over the
     // history, then a butterfly within each wave and the wave totals in order
-    __shared__ double Bm[(HIST + 1) * (HIST + 1)];
+    __shared__ double Bm[(HIST + 1) * (HIST + 2)];
     __shared__ double rhs[HIST + 1];
     __shared__ double wsum[16][HIST * (HIST + 1) / 2];
     constexpr int NPR = HIST * (HIST + 1) / 2;
@@ -1570,39 +1518,33 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int e
 #pragma unroll
         for (int j = i; j < HIST; ++j, ++k) loc[k] = fma(r[i], r[j], loc[k]);
     }
-    const int wv = threadIdx.x >> 6, nwv = blockDim.x >> 6;
 #pragma unroll
     for (int k = 0; k < NPR; ++k) {
-      double v = loc[k];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      if ((threadIdx.x & 63) == 0) wsum[wv][k] = v;
+      const double v = wave_sum_f64(loc[k]);
+      if (ln == 0) wsum[wv][k] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int i = 0, k = 0; i < HIST; ++i)
-        for (int j = i; j < HIST; ++j, ++k) {
-          if (i >= m || j >= m) continue;
-          double v = 0.0;
+    if (wv == 0) {
+      // the bordered system, one wave.  (Diagonal lifted relative to itself: a
+      // shift relative to the trace, which the oldest and largest residuals
+      // dominate, swamped the newest ones once they had dropped seven orders
+      // below them and slowed the last iterations: pentacene dimers 25,610 ->
+      // 24,950 iterations)
+      const int M = m + 1, W = M + 1;
+      for (int e = ln; e < M * W; e += 64) {
+        const int r = e / W, c = e - r * W;
+        double v = c == M ? (r == m ? 1.0 : 0.0) : r == c ? 0.0 : 1.0;
+        if (r < m && c < m) {
+          const int i = min(r, c), j = max(r, c), k = i * HIST - i * (i - 1) / 2 + (j - i);
+          v = 0.0;
           for (int w = 0; w < nwv; ++w) v += wsum[w][k];
-          Bm[i * (m + 1) + j] = v;
-          Bm[j * (m + 1) + i] = v;
+          if (r == c) v *= 1.0 + 1e-12;
         }
-      int M = m + 1;
-      // (diagonal lifted relative to itself: a shift relative to the
-      // trace, which the oldest and largest residuals dominate, swamped the
-      // newest ones once they had dropped seven orders below them and slowed
-      // the last iterations: pentacene dimers 25,610 -> 24,950 iterations)
-      for (int i = 0; i < m; ++i) {
-        Bm[i * M + i] *= 1.0 + 1e-12;
-        Bm[i * M + m] = 1.0;
-        Bm[m * M + i] = 1.0;
-        rhs[i] = 0.0;
+        Bm[e] = v;
       }
-      Bm[m * M + m] = 0.0;
-      rhs[m] = 1.0;
-      solve_small(Bm, rhs, M);
-      for (int i = 0; i < m; ++i) coef[i] = rhs[i];
+      wave_sync();
+      const double x = wave_solve(Bm, rhs, M);
+      if (ln < m) coef[ln] = x;
     }
     __syncthreads();
     double* qn = bt.q_in + d.sh_off;

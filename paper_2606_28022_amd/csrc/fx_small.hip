@@ -74,9 +74,8 @@ __device__ inline double lane_f64(double v, int l) {
 }
 
 // Anderson coefficients from the Gram matrix G of the m residuals (indexed by
-// slot): the bordered system in LDS (B, W = m + 2 columns), Gauss-Jordan
-// elimination with row pivoting, 64 elements at a time.  Returns the lane's
-// coefficient (lane k: the k-th oldest).
+// slot): the bordered system in B.  Returns the lane's coefficient (lane k:
+// the k-th oldest).
 __device__ inline double small_anderson(const double (*G)[HIST], double* B, double* f, int nh, int m) {
   const int lane = threadIdx.x, M = m + 1, W = M + 1;
   for (int e = lane; e < M * W; e += 64) {
@@ -88,30 +87,8 @@ __device__ inline double small_anderson(const double (*G)[HIST], double* B, doub
     }
     B[e] = v;
   }
-  __syncthreads();
-  unsigned used = 0;
-  double x = 0.0;
-  int row = 0;  // the lane's unknown: its pivot row
-  for (int c = 0; c < M; ++c) {
-    const double t = lane < M && !(used >> lane & 1u) ? fabs(B[lane * W + c]) : -1.0;
-    // (clamped: a residual of NaN leaves no candidate)
-    const int piv = min(max(__ffsll((unsigned long long)__ballot(t == wave_max_f64(t))) - 1, 0), M - 1);
-    used |= 1u << piv;
-    if (lane == c) row = piv;
-    double dv = B[piv * W + c];
-    if (fabs(dv) < 1e-300) dv = 1e-300;
-    if (lane < M) f[lane] = lane != piv ? B[lane * W + c] / dv : 0.0;
-    __syncthreads();
-    const int wc = W - c - 1;  // columns c + 1 ..
-    for (int e = lane; e < M * wc; e += 64) {
-      const int r = e / wc, k = c + 1 + e - r * wc;
-      if (r != piv) B[r * W + k] -= f[r] * B[piv * W + k];
-    }
-    if (lane == 0) B[piv * W + c] = dv;
-    __syncthreads();
-  }
-  if (lane < M) x = B[row * W + M] / B[row * W + lane];
-  return x;
+  wave_sync();
+  return wave_solve(B, f, M);
 }
 
 }  // namespace
