@@ -497,8 +497,6 @@ void Ctx::init_device() {
                             lds_max);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_resp_M), hipFuncAttributeMaxDynamicSharedMemorySize,
                             lds_max);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_resp_M_mfma), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            lds_max);
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_resp_R_lds), hipFuncAttributeMaxDynamicSharedMemorySize,
                             lds_max - 24576);
   for (const void* k : {reinterpret_cast<const void*>(k_precond_build<PRE_ROWS_SMALL>),
@@ -595,10 +593,7 @@ void Ctx::launch_resp_M(const Batch& b, const DevBatch& db, const int* order, co
                         const double* Q, double* M) {
   int nsh = 0;
   for (const auto& d : b.h_desc) nsh = std::max(nsh, d.nsh);
-  const size_t bm = resp_M_mfma_lds_bytes(nsh);
-  if (nsh <= 16 * RMM_MAXB && (long long)bm <= (long long)lds_max)
-    hipLaunchKernelGGL(k_resp_M_mfma, dim3(b.nsys), dim3(256), (unsigned)bm, stream, db, order, nocc, qoff, Q, M);
-  else
+  if (!launch_resp_M_mfma(b.nsys, n_cu, lds_max, stream, db, nsh, order, nocc, qoff, Q, M))
     hipLaunchKernelGGL(k_resp_M, dim3(b.nsys), dim3(256), resp_M_lds(b), stream, db, order, nocc, qoff, Q, M);
 }
 
@@ -636,7 +631,7 @@ bool Ctx::monomer_response_setup() {
   hipLaunchKernelGGL(k_mo_order, dim3(b.nsys), dim3(256), 0, stream, dmb, resp_nocc.p, resp_order.p);
   // (S C)^T = Ct S into the GEMM scratch
   gemm_batch(b, dmb, b.nsys, b.d_list.p, 0, b.Ct.p, b.S.p, b.Tm.p, (const double*)nullptr, b.gemm_gflop_all());
-  hipLaunchKernelGGL(k_resp_Q, dim3(b.nsys), dim3(256), (unsigned)resp_Q_lds_bytes(b.max_nao), stream, dev_system(),
+  hipLaunchKernelGGL(k_resp_Q, dim3(b.nsys, slices(b, b.nsys)), dim3(256), (unsigned)resp_Q_lds_bytes(b.max_nao), stream, dev_system(),
                      dmb, b.Tm.p, resp_order.p,
                      resp_nocc.p, resp_qoff.p, resp_Q.p);
   launch_resp_M(b, dmb, resp_order.p, resp_nocc.p, resp_qoff.p, resp_Q.p, resp_M.p);
@@ -935,7 +930,13 @@ void Ctx::build_matrices(Batch& b, bool from_mono) {
   // clusters of a system without cut bonds copy their monomers' blocks (the
   // monomer batch holds this geometry's matrices)
   const int copy = from_mono && bonds.empty() && b.h_nfrag > 1 ? 1 : 0;
-  hipLaunchKernelGGL(k_build_system, dim3(b.nsys), dim3(256), 0, stream, dev_system(), db, nullptr, mb.dev(), copy);
+  const int sl = slices(b, b.nsys);
+  if (sl > 1) erep_part.alloc((long long)b.nsys * sl);
+  hipLaunchKernelGGL(k_build_system, dim3(b.nsys, sl), dim3(256), 0, stream, dev_system(), db, nullptr, mb.dev(),
+                     copy, erep_part.p);
+  if (sl > 1)
+    hipLaunchKernelGGL(k_erep_sum, dim3((b.nsys + 255) / 256), dim3(256), 0, stream, db, b.nsys, sl,
+                       (const double*)erep_part.p);
   if (b.has_hop) hipLaunchKernelGGL(k_vhop, dim3(b.nsys), dim3(256), 0, stream, db, P.g.VHOP);
   check(hipGetLastError(), "k_build_system");
   // mixed precision: FP32 copies of H0 and S for the FP32 Fock builds
@@ -1642,9 +1643,7 @@ void Ctx::launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na) {
 // Fock matrices of the na systems listed in dl: up to eight work-groups per
 // system while that leaves at most two per CU
 void Ctx::launch_fock(const Batch& b, const DevSystem& ds, const DevBatch& db, const int* dl, int na) {
-  int slices = 1;
-  while (slices < 8 && 2LL * slices * na <= 2LL * n_cu && b.max_nao > 32 * slices) slices *= 2;
-  hipLaunchKernelGGL(k_fock, dim3(na, slices), dim3(256), 0, stream, ds, db, dl);
+  hipLaunchKernelGGL(k_fock, dim3(na, slices(b, na)), dim3(256), 0, stream, ds, db, dl);
 }
 
 void Ctx::density_sums(const Batch& b, const DevBatch& db, int nl, const int* dl, double gflop) {
@@ -1973,8 +1972,12 @@ void Ctx::build_lists_impl() {
       if (!(P.elems[elem[a]].rvdw > 0.0))
         throw FxError(FX_E_UNSUPPORTED, "van der Waals radius missing from the parameters");
   if (F > 1) {
-    hipLaunchKernelGGL(k_pair_contacts, dim3(F), dim3(256), 0, stream, dev_system(), d_frag_atoms_real.p,
-                       d_frag_off_real.p, vdw ? 1 : 0, opt.cutoff_bohr * opt.cutoff_bohr, opt.vdw_dimer,
+    // a group of lanes per pair, as many as an average fragment has atoms
+    int lanes = 1;
+    while (lanes < 64 && lanes * (long long)F < N) lanes *= 2;
+    const int jy = std::max(1, std::min(8, F * lanes / 512));
+    hipLaunchKernelGGL(k_pair_contacts, dim3(F, jy), dim3(256), 0, stream, dev_system(), d_frag_atoms_real.p,
+                       d_frag_off_real.p, lanes, vdw ? 1 : 0, opt.cutoff_bohr * opt.cutoff_bohr, opt.vdw_dimer,
                        opt.vdw_trimer, flag.p);
     check(hipGetLastError(), "k_pair_contacts");
   }

@@ -58,7 +58,8 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
                1, true);
   c.gemm_batch(b, db, nr, b.d_list.p + ne, 0, b.Pm.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(rot));
   c.gemm_batch(b, db, nr, b.d_list.p + ne, 1, b.Tm.p, b.Pm.p, b.Fm.p, nullptr, b.gemm_gflop_sym(rot), 0, 1);
-  hipLaunchKernelGGL(k_make_DS, dim3(b.nsys), dim3(256), 0, c.stream, db, b.Pm.p, b.Tm.p, b.Fm.p, nr > 0 ? 1 : 0);
+  const int sl = c.slices(b, b.nsys);
+  hipLaunchKernelGGL(k_make_DS, dim3(b.nsys, sl), dim3(256), 0, c.stream, db, b.Pm.p, b.Tm.p, b.Fm.p, nr > 0 ? 1 : 0);
   if (b.has_hop)
     hipLaunchKernelGGL(k_hop_grad, dim3(b.nsys), dim3(256), 0, c.stream, ds, db, (const double*)b.Pm.p, b.Fm.p, wsys,
                        (const int*)c.d_bonds.p, c.P.g.VHOP, slot_base, hop_f);
@@ -66,8 +67,10 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
   for (auto& d : b.h_desc) natot += d.nat;
   g_sys.alloc(3LL * natot);
   F_sys.alloc(natot);
-  hipLaunchKernelGGL(k_grad_contract, dim3(b.nsys), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, b.Fm.p,
-                     b.q_out.p, b.q_out.p, wsys, 1, 0, g_sys.p, F_sys.p, b.Tm.p);
+  hipLaunchKernelGGL(k_grad_pairs, dim3(b.nsys, sl), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, b.Fm.p,
+                     b.q_out.p, b.q_out.p, 1, b.Tm.p);
+  hipLaunchKernelGGL(k_grad_gather, dim3(b.nsys), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, wsys, 0, g_sys.p,
+                     F_sys.p, (const double*)b.Tm.p);
   Ctx::check(hipGetLastError(), "explicit gradient terms");
 }
 
@@ -143,14 +146,14 @@ void Ctx::gradient() {
   if (nscc > 0) {
     explicit_terms(*this, db_, d_sw.p, gd, Fd, hop_f.p, n_hop_m);
     DevBatch ddb = db_.dev();
-    hipLaunchKernelGGL(k_grad_pair_corr, dim3(db_.nsys), dim3(128), 0, stream, ds, ddb, d_q.p, ddq_scc.p, d_sw.p,
+    hipLaunchKernelGGL(k_grad_pair_corr, dim3(db_.nsys), dim3(256), 0, stream, ds, ddb, d_q.p, ddq_scc.p, d_sw.p,
                        (const int*)nullptr, gd.p, ghost_f.p);
     check(hipGetLastError(), "k_grad_pair_corr");
   }
   if (ntri > 0) {
     explicit_terms(*this, tb_, nullptr, gt, Ft, nullptr, 0);
     DevBatch dtb = tb_.dev();
-    hipLaunchKernelGGL(k_grad_pair_corr, dim3(tb_.nsys), dim3(128), 0, stream, ds, dtb, d_q.p, ddq_tri.p,
+    hipLaunchKernelGGL(k_grad_pair_corr, dim3(tb_.nsys), dim3(256), 0, stream, ds, dtb, d_q.p, ddq_tri.p,
                        (const double*)nullptr, d_tmask.p, gt.p, ghost_f.p);
     check(hipGetLastError(), "k_grad_pair_corr (trimers)");
   }
@@ -320,7 +323,7 @@ void Ctx::gradient() {
       // (SC)^T = Ct S into G1
       gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 0, b.Ct.p, b.S.p, G1.p, (const double*)nullptr,
                  b.gemm_gflop_all());
-      hipLaunchKernelGGL(k_resp_Q, dim3(b.nsys), dim3(256), (unsigned)resp_Q_lds_bytes(b.max_nao), stream, ds, dmb,
+      hipLaunchKernelGGL(k_resp_Q, dim3(b.nsys, slices(b, b.nsys)), dim3(256), (unsigned)resp_Q_lds_bytes(b.max_nao), stream, ds, dmb,
                          G1.p, order.p, d_nocc.p, d_qoff.p, Q.p);
       launch_resp_M(b, dmb, order.p, d_nocc.p, d_qoff.p, Q.p, M.p);
     }
@@ -399,7 +402,8 @@ void Ctx::gradient() {
     hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M,
                        (const double*)yng.p, w.p, u.p, step_max.p);
     // Z and its AO forms
-    hipLaunchKernelGGL(k_resp_Z, dim3(b.nsys), dim3(256), 0, stream, dmb, p_order, d_nocc.p, d_qoff.p, p_Q, w.p,
+    const int sl = slices(b, b.nsys);
+    hipLaunchKernelGGL(k_resp_Z, dim3(b.nsys, sl), dim3(256), 0, stream, dmb, p_order, d_nocc.p, d_qoff.p, p_Q, w.p,
                        G2.p, G3.p);
     // Zt = Ct^T (Zm Ct) -> G1 ; WZ = Ct^T (Ze Ct) -> G2
     gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 0, G2.p, b.Ct.p, b.Tm.p, (const double*)nullptr, b.gemm_gflop_all());
@@ -407,17 +411,19 @@ void Ctx::gradient() {
     gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 0, G3.p, b.Ct.p, b.Tm.p, (const double*)nullptr, b.gemm_gflop_all());
     gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 2, b.Ct.p, b.Tm.p, G2.p, (const double*)nullptr, b.gemm_gflop_all());
     // X2 = P S (D_w P) -> G3
-    hipLaunchKernelGGL(k_rowscale, dim3(b.nsys), dim3(256), 0, stream, dmb, w.p, b.Pm.p, b.Fm.p);
+    hipLaunchKernelGGL(k_rowscale, dim3(b.nsys, sl), dim3(256), 0, stream, dmb, w.p, b.Pm.p, b.Fm.p);
     gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 0, b.S.p, b.Fm.p, b.Tm.p, (const double*)nullptr, b.gemm_gflop_all());
     gemm_batch(b, dmb, (int)b.nsys, b.d_list.p, 0, b.Pm.p, b.Tm.p, G3.p, (const double*)nullptr, b.gemm_gflop_all());
-    hipLaunchKernelGGL(k_sym_inplace, dim3(b.nsys), dim3(256), 0, stream, dmb, G1.p);
-    hipLaunchKernelGGL(k_resp_DS, dim3(b.nsys), dim3(256), 0, stream, dmb, G1.p, G2.p, G3.p, w.p, b.Fm.p, gx.p);
+    hipLaunchKernelGGL(k_sym_inplace, dim3(b.nsys, sl), dim3(256), 0, stream, dmb, G1.p);
+    hipLaunchKernelGGL(k_resp_DS, dim3(b.nsys, sl), dim3(256), 0, stream, ds, dmb, G1.p, G2.p, G3.p, w.p, b.Fm.p, gx.p);
     // the projector derivative with the Z-vector density (eq. hop_resp)
     if (b.has_hop)
       hipLaunchKernelGGL(k_hop_grad, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, (const double*)G1.p, b.Fm.p,
                          (const double*)nullptr, (const int*)d_bonds.p, P.g.VHOP, n_hop_m + n_hop_d, hop_f.p);
-    hipLaunchKernelGGL(k_grad_contract, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p, b.Fm.p, gx.p,
-                       b.q_out.p, (const double*)nullptr, 0, 1, gm.p, Fm_.p, b.Tm.p);
+    hipLaunchKernelGGL(k_grad_pairs, dim3(b.nsys, sl), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p, b.Fm.p, gx.p,
+                       b.q_out.p, 0, b.Tm.p);
+    hipLaunchKernelGGL(k_grad_gather, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p,
+                       (const double*)nullptr, 1, gm.p, Fm_.p, (const double*)b.Tm.p);
     check(hipGetLastError(), "response gradient terms");
     build_force_map();  // host work while the queued kernels run
     sync();

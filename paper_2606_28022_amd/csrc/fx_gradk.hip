@@ -12,7 +12,7 @@
 //  * per fragment system: the single-system gradient of eq. xtb_grad with the
 //    W matrix of eq. W_matrix (sigma containing the embedding potential), the
 //    H0 derivative split of eq. H0_deriv and the CN sensitivity of
-//    eq. cn_factor (k_grad_contract);
+//    eq. cn_factor (k_grad_pairs);
 //  * inter-fragment kernel derivatives: ES-DIM (eq. esd_grad), charge-transfer
 //    embedding (eq. ctij) and the response charges (eq. ZxG_inter) in one
 //    N-body force pass over all cross-fragment shell pairs (k_force_inter)
@@ -173,10 +173,13 @@ __device__ void atom_pair_overlap_contract(const DevElem& ea, const DevElem& eb,
 // at fixed CN, for every atom a of the system, and the CN sensitivity
 // F_a = d/dCN_a of the D_H term.  Results are multiplied by the system weight
 // and written (or added) to the per-system atom arrays.
+// Two kernels: the pairs, bound by the latency of their overlap and gamma
+// chains (spread over gridDim.y work-groups where the batch is small: 28
+// pentacene pairs 352 -> 137 us), then the sums per atom, whose order does
+// not depend on that split.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-    k_grad_contract(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
-                                const double* gx, const double* gy, const double* wsys, int with_rep, int accumulate,
-                                double* g_out, double* F_out, double* scratch) {
+    k_grad_pairs(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
+                 const double* gx, const double* gy, int with_rep, double* scratch) {
   const int si = list[blockIdx.x];
   const SysDesc d = bt.desc[si];
   const int n = d.nao, nat = d.nat;
@@ -185,14 +188,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
   const int* atoms = bt.sys_atoms + d.atom_off;
   const int* aao = bt.sys_atom_ao0 + d.atom_off;
   const int* ash = bt.sys_atom_sh0 + d.atom_off;
-  const double cw = wsys ? wsys[si] : 1.0;
   // every pair term is a function of R_a - R_b: each unordered pair (a < b)
   // is evaluated once, its gradient enters a with + and b with -, plus the
   // CN sensitivities of both atoms; 5 values per pair in the scratch block
-  // (5 nat (nat - 1) / 2 <= n^2 doubles), then gathered per atom in order
+  // (5 nat (nat - 1) / 2 <= n^2 doubles)
   double* pb = scratch + d.mat_off;
   const int np = nat * (nat - 1) / 2;
-  for (int p = threadIdx.x; p < np; p += blockDim.x) {
+  for (int p = blockIdx.y * blockDim.x + threadIdx.x; p < np; p += gridDim.y * blockDim.x) {
     int a = 0, rem = p;
     while (rem >= nat - 1 - a) {
       rem -= nat - 1 - a;
@@ -296,39 +298,42 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
     o[3] = Fa;
     o[4] = Fb;
   }
-  __syncthreads();
-  for (int a = threadIdx.x; a < nat; a += blockDim.x) {
-    const int A = atoms[a];
-    const DevElem& ea = sys.elems[sys.elem[A]];
-    const int oa = aao[a];
-    double t[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int s = 0; s < ea.nsh; ++s)
-      for (int u = 0; u < ea.nao_sh[s]; ++u) {
-        int mu = oa + ea.ao0[s] + u;
-        t[3] += DH[(long long)mu * n + mu] * ea.level[s] * ea.kcn[s];
-      }
-    for (int b = 0; b < nat; ++b) {
-      if (b == a) continue;
-      if (b > a) {
-        const double* q = pb + 5LL * (a * (2 * nat - a - 1) / 2 + (b - a - 1));
-        t[0] += q[0];
-        t[1] += q[1];
-        t[2] += q[2];
-        t[3] += q[3];
-      } else {
-        const double* q = pb + 5LL * (b * (2 * nat - b - 1) / 2 + (a - b - 1));
-        t[0] -= q[0];
-        t[1] -= q[1];
-        t[2] -= q[2];
-        t[3] += q[4];
-      }
+}
+
+// The pair values of k_grad_pairs and the one-centre CN terms, summed per
+// atom in the order of the other atoms: four neighbouring threads take the
+// three components and the sensitivity of one atom.
+__global__ void __launch_bounds__(256) k_grad_gather(DevSystem sys, DevBatch bt, const int* list, const double* DHp,
+                                                     const double* wsys, int accumulate, double* g_out,
+                                                     double* F_out, const double* scratch) {
+  const int si = list[blockIdx.x];
+  const SysDesc d = bt.desc[si];
+  const int n = d.nao, nat = d.nat;
+  const double* DH = DHp + d.mat_off;
+  const double* pb = scratch + d.mat_off;
+  const double cw = wsys ? wsys[si] : 1.0;
+  for (int e = blockIdx.y * blockDim.x + threadIdx.x; e < 4 * nat; e += gridDim.y * blockDim.x) {
+    const int a = e >> 2, c = e & 3;
+    double t = 0.0;
+    if (c == 3) {
+      const DevElem& ea = sys.elems[sys.elem[bt.sys_atoms[d.atom_off + a]]];
+      const int oa = bt.sys_atom_ao0[d.atom_off + a];
+      for (int s = 0; s < ea.nsh; ++s)
+        for (int u = 0; u < ea.nao_sh[s]; ++u) {
+          const int mu = oa + ea.ao0[s] + u;
+          t += DH[(long long)mu * n + mu] * ea.level[s] * ea.kcn[s];
+        }
     }
-    long long o = (long long)d.atom_off + a;
-    for (int k = 0; k < 3; ++k) {
-      double v = cw * t[k];
-      g_out[3 * o + k] = accumulate ? g_out[3 * o + k] + v : v;
-    }
-    F_out[o] = accumulate ? F_out[o] + cw * t[3] : cw * t[3];
+    // pairs (b, a), b < a: minus the gradient, the second sensitivity
+    const double sg = c == 3 ? 1.0 : -1.0;
+    const int cl = c == 3 ? 4 : c;
+    for (int b = 0; b < a; ++b) t += sg * pb[5LL * (b * (2 * nat - b - 1) / 2 + (a - b - 1)) + cl];
+    const double* q = pb + 5LL * (a * (2 * nat - a - 1) / 2) + c;
+    for (int b = a + 1; b < nat; ++b, q += 5) t += *q;
+    const double v = cw * t;
+    const long long o = (long long)d.atom_off + a;
+    double* out = c == 3 ? F_out + o : g_out + 3 * o + c;
+    *out = accumulate ? *out + v : v;
   }
 }
 
@@ -356,13 +361,19 @@ __global__ void k_grad_pair_corr(DevSystem sys, DevBatch bt, const double* qmono
   // their monomer charges are cross-fragment charges of the all-pairs pass
   // and their charge transfer is -q (eq. ctij_ghost)
   const int h0 = bt.healed_off ? bt.healed_off[si] : 0, h1 = bt.healed_off ? bt.healed_off[si + 1] : 0;
-  for (int a = threadIdx.x; a < nat; a += blockDim.x) {
+  // eight neighbouring lanes share an atom (its partners, then its healed
+  // ghosts, dealt in turn; the partial sums added pairwise): a lane per atom
+  // was one chain of nat partners for at most two waves of the chip's work
+  constexpr int PL = 8;
+  const int al = threadIdx.x % PL;
+  for (int a0 = 0; a0 < nat; a0 += blockDim.x / PL) {  // (whole waves: the sums below are over lanes)
+    const int aa = a0 + threadIdx.x / PL, a = min(aa, nat - 1);
     const int A = atoms[a];
     const DevElem& ea = sys.elems[sys.elem[A]];
     const int fa = sys.frag[A];
     const int pa = fa == d.frag[0] ? 0 : (fa == d.frag[1] ? 1 : 2);
     double g[3] = {0.0, 0.0, 0.0};
-    for (int b = 0; b < nat; ++b) {
+    for (int b = al; b < nat; b += PL) {
       const int B = atoms[b];
       const int fb = sys.frag[B];
       if (fb == fa) continue;
@@ -383,7 +394,7 @@ __global__ void k_grad_pair_corr(DevSystem sys, DevBatch bt, const double* qmono
           for (int k = 0; k < 3; ++k) g[k] -= c * dg * Rv[k] / R;
         }
     }
-    for (int e = h0; e < h1; ++e) {
+    for (int e = h0 + al; e < h1; e += PL) {
       const int t = bt.healed_sh[e], G = sys.sh_atom[t];
       if (sys.frag[G] == fa) continue;
       double Rv[3] = {sys.xyz[3 * A] - sys.xyz[3 * G], sys.xyz[3 * A + 1] - sys.xyz[3 * G + 1],
@@ -399,8 +410,11 @@ __global__ void k_grad_pair_corr(DevSystem sys, DevBatch bt, const double* qmono
         for (int k = 0; k < 3; ++k) g[k] -= c * dg * Rv[k] / R;
       }
     }
+    for (int k = 0; k < 3; ++k)
+      for (int o = PL / 2; o > 0; o >>= 1) g[k] += __shfl_xor(g[k], o, 64);
     long long o = (long long)d.atom_off + a;
-    for (int k = 0; k < 3; ++k) g_out[3 * o + k] += g[k];
+    if (al == 0 && aa < nat)
+      for (int k = 0; k < 3; ++k) g_out[3 * o + k] += g[k];
   }
   // the opposite forces on the healed ghosts (one entry per healed shell)
   for (int e = h0 + threadIdx.x; e < h1; e += blockDim.x) {
@@ -431,7 +445,7 @@ __global__ void k_grad_pair_corr(DevSystem sys, DevBatch bt, const double* qmono
 // every system of a batch, V^HOP = S D S (eq. vhop), D = V h h^T on a
 // detached atom and V (1_sp - h h^T) on a ghost, h = 1/2 s + sqrt(3)/2 b.p:
 //  * overlap part (eq. hopsder): Dm S D + D S Dm is added to the system's
-//    D_S matrix, which k_grad_contract contracts with the overlap derivative;
+//    D_S matrix, which k_grad_pairs contracts with the overlap derivative;
 //  * hybrid-coefficient part (eq. hopcoder): with db/dR_attached =
 //    (1 - b b^T) / |R_attached - R_detached|, the force on the attached atom
 //    is +-2 V sqrt(3)/2 (1 - b b^T) w_p / |R| with w = (S Dm S) h on the
@@ -765,8 +779,8 @@ __global__ void k_make_DS(DevBatch bt, const double* P, const double* W, double*
   const int n = d.nao;
   const int* aosh = bt.sys_ao_sh + d.ao_off;
   const double* sg = bt.sig + d.sh_off;
-  for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
-    int i = (int)(idx / n), j = (int)(idx % n);
+  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.y * blockDim.x) {
+    const int i = idx / n, j = idx - i * n;
     const double w = half ? 0.5 * out[d.mat_off + idx] : W[d.mat_off + idx];
     out[d.mat_off + idx] = 0.5 * (sg[aosh[i]] + sg[aosh[j]]) * P[d.mat_off + idx] - w;
   }

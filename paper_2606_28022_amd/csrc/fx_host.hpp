@@ -587,6 +587,19 @@ struct Ctx {
   // densities themselves from the last orbitals and occupations
   void density_sums(const Batch& b, const DevBatch& db, int nl, const int* dl, double gflop);
   void ensure_density(Batch& b);
+  // Work-groups per system for kernels whose loops over a system's elements
+  // or atom pairs can be cut anywhere: one where the batch alone covers the
+  // chip (the loop's setup is then paid once), up to eight where it does not,
+  // as long as every slice keeps 32 rows (FX_SLICES: at most that many).
+  // 8 pentacenes and 28 pairs, one or up to eight: build 307 -> 69 / 84 us,
+  // gradient pairs 352 -> 68 / 137 us, transition charges 270 -> 105 us.
+  int max_slices = std::getenv("FX_SLICES") ? std::atoi(std::getenv("FX_SLICES")) : 8;
+  int slices(const Batch& b, int nsys) const {
+    int s = 1;
+    while (s < max_slices && 2LL * s * nsys <= 2LL * n_cu && b.max_nao > 32 * s) s *= 2;
+    return s;
+  }
+  DevBuf<double> erep_part;
   void launch_fock(const Batch& b, const DevSystem& ds, const DevBatch& db, const int* dl, int na);
   // eigenvectors and eigenvalues of the systems of b whose last iteration was
   // a rotation; false when one of them has no gap any more (it is then left to

@@ -74,42 +74,65 @@ __global__ void k_cn(DevSystem sys, int nchunk, double* part) {
 //           radii r; bit 0 with lam = lam2, bit 1 with lam = lam3.
 // d2 = (dx*dx + dy*dy) + dz*dz and the threshold lam * (r_a + r_b), squared,
 // with every operation rounded separately (no contraction).
-__global__ void k_pair_contacts(DevSystem sys, const int* frag_atoms, const int* frag_off, int rule, double cut2,
-                                double lam2, double lam3, int8_t* flag) {
+// A group of `lanes` neighbouring lanes (a power of two, near the size of a
+// fragment) shares a pair: the group's lanes take the atoms of J, which stay
+// in their registers' reach for all of I's atoms (staged in LDS), and the
+// minimum or the bits are combined over the group.  Both are exact, so the
+// result does not depend on the split.  One lane per pair left most of the
+// chip idle on a chain of 36 x 36 dependent loads: 2.9 ms for 660
+// pentacenes, now 0.25 ms.
+__global__ void __launch_bounds__(256) k_pair_contacts(DevSystem sys, const int* frag_atoms, const int* frag_off,
+                                                       int lanes, int rule, double cut2, double lam2, double lam3,
+                                                       int8_t* flag) {
 #pragma clang fp contract(off)
+  __shared__ double sx[64], sy[64], sz[64], sr[64];
   int I = blockIdx.x;
   int F = sys.nfrag;
   int a0 = frag_off[I], a1 = frag_off[I + 1];
   long long base = (long long)I * F - (long long)I * (I + 1) / 2;  // index of (I, I+1)
-  for (int J = I + 1 + threadIdx.x; J < F; J += blockDim.x) {
-    int b0 = frag_off[J], b1 = frag_off[J + 1];
+  const int ngrp = blockDim.x / lanes, grp = threadIdx.x / lanes, gl = threadIdx.x - grp * lanes;
+  for (int J0 = I + 1 + blockIdx.y * ngrp; J0 < F; J0 += gridDim.y * ngrp) {
+    const int J = J0 + grp;
+    const int b0 = J < F ? frag_off[J] : 0, b1 = J < F ? frag_off[J + 1] : 0;
     double best = 1e300;
     int bits = 0;
-    for (int ia = a0; ia < a1; ++ia) {
-      int a = frag_atoms[ia];
-      double xa = sys.xyz[3 * a], ya = sys.xyz[3 * a + 1], za = sys.xyz[3 * a + 2];
-      const double ra = sys.elems[sys.elem[a]].rvdw;
-      for (int ib = b0; ib < b1; ++ib) {
-        int b = frag_atoms[ib];
-        double dx = xa - sys.xyz[3 * b];
-        double dy = ya - sys.xyz[3 * b + 1];
-        double dz = za - sys.xyz[3 * b + 2];
-        double xx = __dmul_rn(dx, dx);
-        double yy = __dmul_rn(dy, dy);
-        double zz = __dmul_rn(dz, dz);
-        double d2 = __dadd_rn(__dadd_rn(xx, yy), zz);
-        if (rule == 0) {
-          best = d2 < best ? d2 : best;
-        } else {
-          const double rs = __dadd_rn(ra, sys.elems[sys.elem[b]].rvdw);
-          const double t2 = __dmul_rn(lam2, rs), t3 = __dmul_rn(lam3, rs);
-          if (d2 < __dmul_rn(t2, t2)) bits |= 1;
-          if (d2 < __dmul_rn(t3, t3)) bits |= 2;
+    for (int c0 = a0; c0 < a1; c0 += 64) {  // I's atoms, 64 at a time
+      const int nc = min(64, a1 - c0);
+      __syncthreads();  // the previous atoms are consumed
+      if ((int)threadIdx.x < nc) {
+        const int a = frag_atoms[c0 + threadIdx.x];
+        sx[threadIdx.x] = sys.xyz[3 * a];
+        sy[threadIdx.x] = sys.xyz[3 * a + 1];
+        sz[threadIdx.x] = sys.xyz[3 * a + 2];
+        sr[threadIdx.x] = sys.elems[sys.elem[a]].rvdw;
+      }
+      __syncthreads();
+      for (int ib = b0 + gl; ib < b1; ib += lanes) {
+        const int b = frag_atoms[ib];
+        const double xb = sys.xyz[3 * b], yb = sys.xyz[3 * b + 1], zb = sys.xyz[3 * b + 2];
+        const double rb = rule == 0 ? 0.0 : sys.elems[sys.elem[b]].rvdw;
+        for (int ia = 0; ia < nc; ++ia) {
+          double dx = sx[ia] - xb;
+          double dy = sy[ia] - yb;
+          double dz = sz[ia] - zb;
+          double xx = __dmul_rn(dx, dx);
+          double yy = __dmul_rn(dy, dy);
+          double zz = __dmul_rn(dz, dz);
+          double d2 = __dadd_rn(__dadd_rn(xx, yy), zz);
+          if (rule == 0) {
+            best = d2 < best ? d2 : best;
+          } else {
+            const double rs = __dadd_rn(sr[ia], rb);
+            const double t2 = __dmul_rn(lam2, rs), t3 = __dmul_rn(lam3, rs);
+            if (d2 < __dmul_rn(t2, t2)) bits |= 1;
+            if (d2 < __dmul_rn(t3, t3)) bits |= 2;
+          }
         }
       }
     }
     if (rule == 0) bits = best < cut2 ? 3 : 0;
-    flag[base + (J - I - 1)] = (int8_t)bits;
+    for (int o = 1; o < lanes; o <<= 1) bits |= __shfl_xor(bits, o, 64);
+    if (gl == 0 && J < F) flag[base + (J - I - 1)] = (int8_t)bits;
   }
 }
 
@@ -238,11 +261,16 @@ __device__ inline double pair_block(const DevSystem& sys, const DevBatch& bt, co
 // component equals the monomer's (the same atom pairs, CN and shells), so it
 // is copied from the monomer batch, and only the pairs between components
 // are evaluated; the repulsion adds the monomers' own.
+// gridDim.y work-groups share a system (every element has one writer; only
+// the repulsion energy is a sum over them, completed by k_erep_sum): 28
+// pentacene pairs took 307 us on 28 CUs, 84 us on 224.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-    k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono) {
+    k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono,
+                   double* erep_part) {
   int si = list ? list[blockIdx.x] : blockIdx.x;
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
+  const int tid = blockIdx.y * blockDim.x + threadIdx.x, nth = gridDim.y * blockDim.x;
   double* S = bt.S + d.mat_off;
   double* H = bt.H0 + d.mat_off;
   const int* atoms = bt.sys_atoms + d.atom_off;
@@ -283,7 +311,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
       const int m = md->nao, msh = md->nsh;
       const double* mS = mono.S + md->mat_off;
       const double* mH = mono.H0 + md->mat_off;
-      for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
+      for (int e = tid; e < m * m; e += nth) {
         const int i = e / m, j = e - i * m;
         const long long o = (long long)(co[c] + i) * n + co[c] + j;
         S[o] = mS[e];
@@ -292,14 +320,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
       const double* mG = mono.gam + md->gam_off;
       double* G = bt.gam + d.gam_off;
       const int s0 = csh[c];
-      for (int e = threadIdx.x; e < msh * msh; e += blockDim.x) {
+      for (int e = tid; e < msh * msh; e += nth) {
         const int i = e / msh, j = e - i * msh;
         G[(long long)(s0 + i) * d.nsh + s0 + j] = mG[e];
       }
     }
   } else {
     // diagonal atom blocks
-    for (int a = threadIdx.x; a < d.nat; a += blockDim.x) {
+    for (int a = tid; a < d.nat; a += nth) {
       int A = atoms[a];
       const DevElem& e = sys.elems[sys.elem[A]];
       int o = aao[a];
@@ -318,7 +346,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   // pairs off(a) = a nat - a (a + 1) / 2 .. off(a + 1) - 1; with copied
   // components, the pairs between components only
   const int nat = d.nat, np = copy ? roff[nrect] : nat * (nat - 1) / 2;
-  for (int idx = threadIdx.x; idx < np; idx += blockDim.x) {
+  for (int idx = tid; idx < np; idx += nth) {
     int a, b;
     if (copy) {
       int k = 0;
@@ -339,7 +367,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   // gamma of the system's shells (with copied components: between them)
   double* G = bt.gam + d.gam_off;
   const int* shg = bt.sys_sh_global + d.sh_off;
-  for (int idx = threadIdx.x; idx < d.nsh * d.nsh; idx += blockDim.x) {
+  for (int idx = tid; idx < d.nsh * d.nsh; idx += nth) {
     int s = idx / d.nsh, t = idx - s * d.nsh;
     if (copy) {
       int cs = 0, ct = 0;
@@ -366,10 +394,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   }
   if (threadIdx.x == 0) {
     double e = red[0];
-    if (copy)
+    if (copy && blockIdx.y == 0)
       for (int c = 0; c < nc; ++c) e += mono.erep[cfrag[c]];
-    bt.erep[si] = e;
+    if (gridDim.y == 1)
+      bt.erep[si] = e;
+    else
+      erep_part[(long long)si * gridDim.y + blockIdx.y] = e;
   }
+}
+
+// repulsion energies of systems that k_build_system built in slices: their
+// parts in slice order
+__global__ void k_erep_sum(DevBatch bt, int nsys, int slices, const double* erep_part) {
+  const int si = blockIdx.x * blockDim.x + threadIdx.x;
+  if (si >= nsys) return;
+  double e = 0.0;
+  for (int y = 0; y < slices; ++y) e += erep_part[(long long)si * slices + y];
+  bt.erep[si] = e;
 }
 
 // ---------------------------------------------------------------------------

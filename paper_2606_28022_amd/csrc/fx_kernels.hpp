@@ -9,9 +9,11 @@ namespace fx {
 
 // integrals / lists / fields (fx_integrals.hip)
 __global__ void k_cn(DevSystem sys, int nchunk, double* part);
-__global__ void k_pair_contacts(DevSystem sys, const int* frag_atoms, const int* frag_off, int rule, double cut2,
+__global__ void k_pair_contacts(DevSystem sys, const int* frag_atoms, const int* frag_off, int lanes, int rule, double cut2,
                                 double lam2, double lam3, int8_t* flag);
-__global__ void k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono);
+__global__ void k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono,
+                               double* erep_part);
+__global__ void k_erep_sum(DevBatch bt, int nsys, int slices, const double* erep_part);
 __global__ void k_field_partial(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_partial_f32(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_wave(DevSystem sys, const double* q, double* phi);
@@ -219,9 +221,8 @@ __global__ void k_resp_M(DevBatch bt, const int* order, const int* nocc, const l
 size_t resp_M_lds_bytes(int nsh);
 // k_resp_M_mfma: systems of at most 16 RMM_MAXB shells
 constexpr int RMM_MAXB = 8;
-__global__ void k_resp_M_mfma(DevBatch bt, const int* order, const int* nocc, const long long* qoff, const double* Q,
-                              double* M);
-size_t resp_M_mfma_lds_bytes(int nsh);
+bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, hipStream_t stream, const DevBatch& bt, int nsh,
+                        const int* order, const int* nocc, const long long* qoff, const double* Q, double* M);
 constexpr int RQ_CH = 16;        // AOs per staged run of k_resp_Q
 size_t resp_Q_lds_bytes(int n);  // dynamic LDS of k_resp_Q for systems of up to n AOs
 __global__ void k_resp_R(DevSystem sys, DevBatch bt, const double* M, double* Wk, double* R);
@@ -232,7 +233,7 @@ __global__ void k_resp_Z(DevBatch bt, const int* order, const int* nocc, const l
                          const double* w, double* Zm, double* Ze);
 __global__ void k_rowscale(DevBatch bt, const double* wsh, const double* P, double* out);
 __global__ void k_sym_inplace(DevBatch bt, double* A);
-__global__ void k_resp_DS(DevBatch bt, const double* Zb, const double* WZ, const double* X2, const double* wsh,
+__global__ void k_resp_DS(DevSystem sys, DevBatch bt, const double* Zb, const double* WZ, const double* X2, const double* wsh,
                           double* DS, double* gx);
 __global__ void k_trimer_corr(long long ntri, const double* dEIJK, const double* dE_scc, long long nscc,
                               const double* dE_esd, const long long* sub, double* out);
@@ -242,9 +243,10 @@ __global__ void k_sub_healed(DevBatch bt, const double* vgh, double* v);
 __global__ void k_gather_csr(int n, const int* rowptr, const int* ent, const double* src, const double* base,
                              double sign, double* dst);
 __global__ void k_axpy(long long n, const double* x, double a, const double* y, double* out);
-__global__ void k_grad_contract(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
-                                const double* gx, const double* gy, const double* wsys, int with_rep, int accumulate,
-                                double* g_out, double* F_out, double* scratch);
+__global__ void k_grad_pairs(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
+                             const double* gx, const double* gy, int with_rep, double* scratch);
+__global__ void k_grad_gather(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* wsys,
+                              int accumulate, double* g_out, double* F_out, const double* scratch);
 __global__ void k_grad_pair_corr(DevSystem sys, DevBatch bt, const double* qmono, const double* ddq,
                                  const double* wct, const int* qqmask, double* g_out, double* ghost_out);
 __global__ void k_hop_grad(DevSystem sys, DevBatch bt, const double* Dmp, double* DSp, const double* wsys,

@@ -65,6 +65,7 @@ __global__ void __launch_bounds__(256) k_resp_Q(DevSystem sys, DevBatch bt, cons
   for (int k = threadIdx.x; k < n; k += blockDim.x) ord[k] = order[d.ao_off + k];
   const int K = nv * no;
   double* Qs = Q + qoff[si];
+  int run = 0;
   for (int s = 0; s < ns;) {
     int mua, na;
     shell_aos(sys, bt, d, s, mua, na);
@@ -75,6 +76,11 @@ __global__ void __launch_bounds__(256) k_resp_Q(DevSystem sys, DevBatch bt, cons
       if (m1 + n1 - mua > RQ_CH) break;
       mub = m1 + n1;
       ++s1;
+    }
+    // the runs are dealt to the system's work-groups
+    if (run++ % (int)gridDim.y != (int)blockIdx.y) {
+      s = s1;
+      continue;
     }
     const int w = mub - mua;
     __syncthreads();  // the previous run is consumed (and ord written)
@@ -191,79 +197,90 @@ __global__ void __launch_bounds__(256) k_resp_M(DevBatch bt, const int* order, c
 }
 
 // The same M on the FP64 matrix cores for systems of up to 16 RMM_MAXB
-// shells: the upper 16 x 16 blocks of M = (Q diag(w)) Q^T, dealt to the four
-// waves in turn, each accumulated with v_mfma_f64_16x16x4 over the staged
-// (a, i) chunks (rows padded to whole blocks with zeros, the chunk's tail
-// steps with zero weights), then written with their mirrors (on the
-// diagonal blocks the upper entries, so that M is exactly symmetric).
+// shells: the upper 16 x 16 blocks of M = (Q diag(w)) Q^T, dealt to the waves
+// of the system's gridDim.y work-groups in turn, QB to each (a wave past the
+// last block repeats the first and stores nothing), accumulated with
+// v_mfma_f64_16x16x4 over (a, i) chunks staged in LDS, then written with
+// their mirrors (on the diagonal blocks the upper entries, so that M is
+// exactly symmetric).  No branch and no select in the loop: rows past ns and
+// columns past K repeat the last one, with zero weights and unstored sums.
+// Latency-bound for small batches: one work-group per system that loaded a
+// chunk, waited and multiplied, its waves' blocks under conditions (whose
+// register moves outweighed the products), took 516 us for 8 pentacenes
+// (72 shells, 3315 pairs) and 0.96 ms for 660.  With the next chunk in
+// flight during the products and the blocks spread over work-groups:
+// 105 us and 0.66 ms.
+// MB: 16-row blocks of the system; RMM_LD = 4 mod 32 doubles spreads a wave's
+// operand reads (16 rows by 4 columns) evenly over the banks.
 typedef double rm_v4d __attribute__((ext_vector_type(4)));
-__global__ void __launch_bounds__(256) k_resp_M_mfma(DevBatch bt, const int* order, const int* nocc,
-                                                     const long long* qoff, const double* Q, double* M) {
+constexpr int RMM_LD = RM_KC + 4;
+template <int MB, int QB>
+__global__ void __launch_bounds__(256, 2) k_resp_M_mfma(DevBatch bt, const int* order, const int* nocc,
+                                                        const long long* qoff, const double* Q, double* M) {
   const int si = blockIdx.x;
   const SysDesc d = bt.desc[si];
   const int n = d.nao, no = nocc[si], nv = n - no, ns = d.nsh;
-  const int* ord = order + d.ao_off;
-  const double* e = bt.eps + d.ao_off;
-  const long long K = (long long)nv * no;
+  const int K = nv * no;
   const double* Qs = Q + qoff[si];
-  extern __shared__ double rm_lds[];
-  const int nb = (ns + 15) / 16, nrow = 16 * nb;
-  double* qt = rm_lds;                  // [nrow][RM_LD] (rows past ns zero)
-  double* idn = rm_lds + nrow * RM_LD;  // [RM_KC]
+  __shared__ double qt[16 * MB * RMM_LD], idn[RM_KC], eo[MAXN];
+  for (int r = threadIdx.x; r < n; r += blockDim.x) eo[r] = bt.eps[d.ao_off + order[d.ao_off + r]];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nblk = nb * (nb + 1) / 2;
-  constexpr int QB = (RMM_MAXB * (RMM_MAXB + 1) / 2 + 3) / 4;  // blocks per wave, at most
+  const int nb = (ns + 15) / 16, nblk = nb * (nb + 1) / 2;
   int bsr[QB], bbr[QB];
   rm_v4d acc[QB];
-  int nmine = 0;
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
     acc[q] = (rm_v4d){0.0, 0.0, 0.0, 0.0};
-    const int blk = wave + 4 * q;
+    const int blk = wave + 4 * ((int)blockIdx.y + (int)gridDim.y * q);
     int bs = 0, rem = blk < nblk ? blk : 0;
     while (rem >= nb - bs) {
       rem -= nb - bs;
       ++bs;
     }
-    bsr[q] = bs;
+    bsr[q] = blk < nblk ? bs : -1 - bs;
     bbr[q] = bs + rem;
-    nmine += blk < nblk;
   }
   const int i16 = lane & 15, kq = lane >> 4;
-  for (long long k0 = 0; k0 < K; k0 += RM_KC) {
-    const int kn = (int)((K - k0) < RM_KC ? (K - k0) : RM_KC);
+  // a chunk is loaded while the products of the one before run: the waves
+  // take its rows in turn, a row's 64 columns to the lanes
+  static_assert(RM_KC == 64, "a wave loads a row's chunk");
+  constexpr int NL = 4 * MB;
+  double st[NL];
+  auto load = [&](int k0) {
+    const double* c = Qs + min(k0 + lane, K - 1);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) st[q] = c[(long long)min(wave + 4 * q, ns - 1) * K];
+  };
+  if (K > 0) load(0);
+  __syncthreads();
+  for (int k0 = 0; k0 < K; k0 += RM_KC) {
+    const int kn = min(K - k0, RM_KC);
     __syncthreads();
-    for (int x = threadIdx.x; x < nrow * RM_KC; x += blockDim.x) {
-      const int sh = x / RM_KC, k = x - sh * RM_KC;
-      qt[sh * RM_LD + k] = (k < kn && sh < ns) ? Qs[(long long)sh * K + k0 + k] : 0.0;
-    }
-    for (int k = threadIdx.x; k < RM_KC; k += blockDim.x) {
-      double v = 0.0;
-      if (k < kn) {
-        const long long kk = k0 + k;
-        const int ap = (int)(kk / no), ip = (int)(kk - (long long)ap * no);
-        v = 1.0 / (e[ord[no + ap]] - e[ord[ip]]);
-      }
-      idn[k] = v;
+#pragma unroll
+    for (int q = 0; q < NL; ++q) qt[(wave + 4 * q) * RMM_LD + lane] = st[q];
+    if (wave == 0) {
+      const int k = min(k0 + lane, K - 1), ap = k / no, ip = k - ap * no;
+      idn[lane] = lane < kn ? 1.0 / (eo[no + ap] - eo[ip]) : 0.0;
     }
     __syncthreads();
-    for (int kk = 0; kk < kn; kk += 4) {
+    load(min(k0 + RM_KC, K - 1));
+#pragma unroll 4
+    for (int kk = 0; kk < RM_KC; kk += 4) {
       const int k = kk + kq;
       const double w = idn[k];
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        if (q < nmine) {
-          const double a = qt[(16 * bsr[q] + i16) * RM_LD + k] * w;
-          const double b = qt[(16 * bbr[q] + i16) * RM_LD + k];
-          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[q], 0, 0, 0);
-        }
+        const int bs = bsr[q] < 0 ? -1 - bsr[q] : bsr[q];
+        const double a = qt[(16 * bs + i16) * RMM_LD + k] * w;
+        const double b = qt[(16 * bbr[q] + i16) * RMM_LD + k];
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[q], 0, 0, 0);
       }
     }
   }
   double* Mo = M + d.gam_off;
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
-    if (q >= nmine) continue;
+    if (bsr[q] < 0) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int s = 16 * bsr[q] + kq + 4 * r, t = 16 * bbr[q] + i16;
@@ -274,8 +291,26 @@ __global__ void __launch_bounds__(256) k_resp_M_mfma(DevBatch bt, const int* ord
   }
 }
 
-size_t resp_M_mfma_lds_bytes(int nsh) {
-  return ((size_t)(16 * ((nsh + 15) / 16)) * RM_LD + RM_KC) * sizeof(double);
+// A block per wave where that fits the idle CUs (two work-groups each), else
+// a quarter of the blocks per wave.
+bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, hipStream_t stream, const DevBatch& bt, int nsh,
+                        const int* order, const int* nocc, const long long* qoff, const double* Q, double* M) {
+  const int nb = (nsh + 15) / 16, wg = (nb * (nb + 1) / 2 + 3) / 4;
+  if (nb > RMM_MAXB || (16 * nb * RMM_LD + RM_KC + MAXN) * (int)sizeof(double) > lds_max) return false;
+  const bool split = (long long)wg * nsys <= 2LL * n_cu;
+  auto go = [&](auto* whole, auto* one) {
+    hipLaunchKernelGGL(split ? one : whole, dim3(nsys, split ? wg : 1), dim3(256), 0, stream, bt, order, nocc, qoff, Q,
+                       M);
+  };
+  switch (nb) {
+    case 0: case 1: case 2: go(k_resp_M_mfma<2, 1>, k_resp_M_mfma<2, 1>); break;
+    case 3: go(k_resp_M_mfma<3, 2>, k_resp_M_mfma<3, 1>); break;
+    case 4: go(k_resp_M_mfma<4, 3>, k_resp_M_mfma<4, 1>); break;
+    case 5: go(k_resp_M_mfma<5, 4>, k_resp_M_mfma<5, 1>); break;
+    case 6: go(k_resp_M_mfma<6, 6>, k_resp_M_mfma<6, 1>); break;
+    default: go(k_resp_M_mfma<8, 9>, k_resp_M_mfma<8, 1>); break;
+  }
+  return true;
 }
 
 // dynamic LDS of k_resp_M for systems of up to nsh shells
@@ -557,17 +592,26 @@ __global__ void k_resp_Z(DevBatch bt, const int* order, const int* nocc, const l
   const int n = d.nao, no = nocc[si], nv = n - no, ns = d.nsh;
   const int* ord = order + d.ao_off;
   const double* e = bt.eps + d.ao_off;
-  const long long K = (long long)nv * no;
-  for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
+  const int K = nv * no;
+  const int tid = blockIdx.y * blockDim.x + threadIdx.x, nth = gridDim.y * blockDim.x;
+  // zeros everywhere but at (virtual, occupied), which the loop below writes
+  __shared__ unsigned char virt[MAXN];
+  for (int r = threadIdx.x; r < n; r += blockDim.x) virt[ord[r]] = r >= no;
+  __syncthreads();
+  for (int idx = tid; idx < n * n; idx += nth) {
+    const int a = idx / n, i = idx - a * n;
+    if (virt[a] && !virt[i]) continue;
     Zm[d.mat_off + idx] = 0.0;
     Ze[d.mat_off + idx] = 0.0;
   }
-  __syncthreads();
-  for (long long k = threadIdx.x; k < K; k += blockDim.x) {
-    int ap = (int)(k / no), ip = (int)(k % no);
-    int a = ord[no + ap], i = ord[ip];
+  const double* ws = w + d.sh_off;
+  for (int k = tid; k < K; k += nth) {
+    const int ap = k / no, ip = k - ap * no;
+    const int a = ord[no + ap], i = ord[ip];
+    const double* q = Q + qoff[si] + k;
     double v = 0.0;
-    for (int s = 0; s < ns; ++s) v += w[d.sh_off + s] * Q[qoff[si] + (long long)s * K + k];
+#pragma unroll 8
+    for (int s = 0; s < ns; ++s) v += ws[s] * q[(long long)s * K];
     double z = -2.0 * v / (e[a] - e[i]);
     Zm[d.mat_off + (long long)a * n + i] = z;
     Ze[d.mat_off + (long long)a * n + i] = z * e[i];
@@ -580,8 +624,8 @@ __global__ void k_rowscale(DevBatch bt, const double* wsh, const double* P, doub
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
   const int* aosh = bt.sys_ao_sh + d.ao_off;
-  for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
-    int i = (int)(idx / n);
+  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.y * blockDim.x) {
+    int i = idx / n;
     out[d.mat_off + idx] = wsh[d.sh_off + aosh[i]] * P[d.mat_off + idx];
   }
 }
@@ -591,8 +635,8 @@ __global__ void k_sym_inplace(DevBatch bt, double* A) {
   const int si = blockIdx.x;
   const SysDesc d = bt.desc[si];
   const int n = d.nao;
-  for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
-    int i = (int)(idx / n), j = (int)(idx % n);
+  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.y * blockDim.x) {
+    int i = idx / n, j = idx - i * n;
     if (j <= i) continue;
     double a = A[d.mat_off + (long long)i * n + j], b = A[d.mat_off + (long long)j * n + i];
     double m = 0.5 * (a + b);
@@ -603,7 +647,7 @@ __global__ void k_sym_inplace(DevBatch bt, double* A) {
 
 // D_S of the response: 1/2 (sig_i + sig_j) Zb - sym(WZ) + 1/2 (w_i + w_j) P - 1/4 (X2 + X2^T)
 // and gx = 2 Q^Z with Q^Z_s = sum_{mu in s} sum_nu Zb_mu,nu S_mu,nu
-__global__ void k_resp_DS(DevBatch bt, const double* Zb, const double* WZ, const double* X2, const double* wsh,
+__global__ void k_resp_DS(DevSystem sys, DevBatch bt, const double* Zb, const double* WZ, const double* X2, const double* wsh,
                           double* DS, double* gx) {
   const int si = blockIdx.x;
   const SysDesc d = bt.desc[si];
@@ -614,25 +658,24 @@ __global__ void k_resp_DS(DevBatch bt, const double* Zb, const double* WZ, const
   const double* P = bt.P + d.mat_off;
   const double* S = bt.S + d.mat_off;
   const long long o = d.mat_off;
-  for (long long idx = threadIdx.x; idx < (long long)n * n; idx += blockDim.x) {
-    int i = (int)(idx / n), j = (int)(idx % n);
+  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.y * blockDim.x) {
+    int i = idx / n, j = idx - i * n;
     long long ij = o + idx, ji = o + (long long)j * n + i;
     int si_ = aosh[i], sj_ = aosh[j];
     DS[ij] = 0.5 * (sg[si_] + sg[sj_]) * Zb[ij] - 0.5 * (WZ[ij] + WZ[ji]) + 0.5 * (w[si_] + w[sj_]) * P[idx] -
              0.25 * (X2[ij] + X2[ji]);
   }
-  __shared__ double pop[MAXN];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+  // gx_s = 2 sum_{mu in s} sum_j Z_mu,j S_mu,j: a wave per shell, its lanes
+  // along the rows
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  for (int s = blockIdx.y * nw + (threadIdx.x >> 6); s < d.nsh; s += gridDim.y * nw) {
+    int mu0, nu;
+    shell_aos(sys, bt, d, s, mu0, nu);
     double v = 0.0;
-    for (int j = 0; j < n; ++j) v += Zb[o + (long long)i * n + j] * S[(long long)i * n + j];
-    pop[i] = v;
-  }
-  __syncthreads();
-  for (int s = threadIdx.x; s < d.nsh; s += blockDim.x) {
-    double v = 0.0;
-    for (int i = 0; i < n; ++i)
-      if (aosh[i] == s) v += pop[i];
-    gx[d.sh_off + s] = 2.0 * v;
+    for (int i = mu0; i < mu0 + nu; ++i)
+      for (int j = lane; j < n; j += 64) v += Zb[o + (long long)i * n + j] * S[(long long)i * n + j];
+    v = wave_sum_f64(v);
+    if (lane == 0) gx[d.sh_off + s] = 2.0 * v;
   }
 }
 
