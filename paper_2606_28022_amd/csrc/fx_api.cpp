@@ -201,7 +201,9 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
         const double r = std::sqrt(r2);
         for (int c = 0; c < 3; ++c) hb[3 * e + c] = v[c] / r;
       }
-      b.hop_b.upload(hb);
+      Transfer up(*this, false);
+      up.put(b.hop_b, hb);
+      up.flush();
     }
     b.has_pre = false;
     check(hipMemsetAsync(b.phi.p, 0, sizeof(double) * std::max(1, b.tot_sh), stream), "memset");
@@ -336,7 +338,8 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
     gam += (long long)nsh * nsh;
     b.max_nao = std::max(b.max_nao, nao);
   }
-  b.sh_mono.upload(sh_mono);
+  Transfer up(*this, false);
+  up.put(b.sh_mono, sh_mono);
   b.h_hop_off = hop_off;
   b.h_hop_bond = hop_bond;
   b.h_healed_off = healed_off;
@@ -345,15 +348,15 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
   b.n_hop = (int)hop_atom.size();
   b.has_healed = !healed_sh.empty();
   if (b.has_hop || b.has_healed) {
-    b.sh_q0.upload(sh_q0);
-    b.atom_zs.upload(atom_zs);
-    b.hop_off.upload(hop_off);
-    b.hop_atom.upload(hop_atom.empty() ? std::vector<int>{0} : hop_atom);
-    b.hop_kind.upload(hop_kind.empty() ? std::vector<int>{0} : hop_kind);
-    b.hop_bond.upload(hop_bond.empty() ? std::vector<int>{0} : hop_bond);
-    b.hop_b.upload(hop_b.empty() ? std::vector<double>{0.0} : hop_b);
-    b.healed_off.upload(healed_off);
-    b.healed_sh.upload(healed_sh.empty() ? std::vector<int>{0} : healed_sh);
+    up.put(b.sh_q0, sh_q0);
+    up.put(b.atom_zs, atom_zs);
+    up.put(b.hop_off, hop_off);
+    up.put(b.hop_atom, hop_atom.empty() ? std::vector<int>{0} : hop_atom);
+    up.put(b.hop_kind, hop_kind.empty() ? std::vector<int>{0} : hop_kind);
+    up.put(b.hop_bond, hop_bond.empty() ? std::vector<int>{0} : hop_bond);
+    up.put(b.hop_b, hop_b.empty() ? std::vector<double>{0.0} : hop_b);
+    up.put(b.healed_off, healed_off);
+    up.put(b.healed_sh, healed_sh.empty() ? std::vector<int>{0} : healed_sh);
   }
   b.h_desc = desc;
   b.tot_sh = sh_off;
@@ -361,15 +364,15 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
   b.tot_mat = mat;
   b.tot_gam = gam;
   b.has_pre = false;
-  b.d_desc.upload(desc);
-  b.d_atoms.upload(atoms);
+  up.put(b.d_desc, desc);
+  up.put(b.d_atoms, atoms);
   b.h_atoms = atoms;
-  b.d_atom_ao0.upload(atom_ao0);
-  b.d_atom_sh0.upload(atom_sh0);
-  b.d_sh_global.upload(sh_global);
+  up.put(b.d_atom_ao0, atom_ao0);
+  up.put(b.d_atom_sh0, atom_sh0);
+  up.put(b.d_sh_global, sh_global);
   b.h_sh_global = sh_global;
-  b.d_sh_atom.upload(sh_atom);
-  b.d_ao_sh.upload(ao_sh);
+  up.put(b.d_sh_atom, sh_atom);
+  up.put(b.d_ao_sh, ao_sh);
   b.S.alloc(mat);
   b.H0.alloc(mat);
   b.Fm.alloc(mat);
@@ -415,7 +418,8 @@ void Ctx::build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters,
   b.sweeps.alloc(ns);
   std::vector<int> all(ns);
   for (int k = 0; k < ns; ++k) all[k] = k;
-  b.d_all.upload(all);
+  up.put(b.d_all, all);
+  up.flush();
   check(hipMemsetAsync(b.phi.p, 0, sizeof(double) * std::max(1, sh_off), stream), "memset");
   b.h_system_gen = system_gen;
 }
@@ -620,14 +624,16 @@ bool Ctx::monomer_response_setup() {
     if ((long long)resp_Q_lds_bytes(b.max_nao) > (long long)lds_max) return false;
   }
   DevBatch dmb = b.dev();
-  resp_nocc.upload(nocc);
-  resp_qoff.upload(qoff);
+  Transfer up(*this, false);
+  up.put(resp_nocc, nocc);
+  up.put(resp_qoff, qoff);
   resp_order.alloc(b.tot_ao);
   resp_Q.alloc(std::max(1LL, qoff[b.nsys]));
   resp_M.alloc(std::max(1LL, b.tot_gam));
   std::vector<int> all(b.nsys);
   for (int k = 0; k < b.nsys; ++k) all[k] = k;
-  b.d_list.upload(all);
+  up.put(b.d_list, all);
+  up.flush();
   hipLaunchKernelGGL(k_mo_order, dim3(b.nsys), dim3(256), 0, stream, dmb, resp_nocc.p, resp_order.p);
   // (S C)^T = Ct S into the GEMM scratch
   gemm_batch(b, dmb, b.nsys, b.d_list.p, 0, b.Ct.p, b.S.p, b.Tm.p, (const double*)nullptr, b.gemm_gflop_all());
@@ -663,12 +669,13 @@ void Ctx::build_precond(Batch& b) {
     hipLaunchKernelGGL(k_precond_build<PRE_ROWS>, dim3(b.nsys), dim3(PRE_THREADS), bytes, stream, dev_system(), db,
                        b.d_all.p, mb.dev(), (const double*)resp_M.p, b.pre.p, ok.p);
   check(hipGetLastError(), "k_precond_build");
-  std::vector<int> h;
-  ok.download(h, stream);
-  sync();
-  int bad = 0;
-  for (int v : h) bad += v == 0;
-  if (verbose) std::fprintf(stderr, "[fx] mixing preconditioner for %d systems (%d singular)\n", b.nsys, bad);
+  if (verbose) {
+    std::vector<int> h;
+    fetch(ok, h);
+    int bad = 0;
+    for (int v : h) bad += v == 0;
+    std::fprintf(stderr, "[fx] mixing preconditioner for %d systems (%d singular)\n", b.nsys, bad);
+  }
   b.has_pre = true;
 }
 
@@ -722,8 +729,7 @@ double Ctx::mlp_grad_impl(const float* d_x, const float* d_y, long long n) {
                      1.0 / (2.0 * (double)n), mlp_loss.p);
   check(hipGetLastError(), "mlp gradient");
   std::vector<double> h;
-  mlp_loss.download(h, stream, 1);
-  sync();
+  fetch(mlp_loss, h, 1);
   return h[0];
 }
 
@@ -970,7 +976,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   const int nl = (int)list.size();
   // reset per-system iteration state on the device (the whole batch has its
   // list there already)
-  if (nl != b.nsys) b.d_list.upload(list);
+  if (nl != b.nsys) put(b.d_list, list);
   const int* lst = nl == b.nsys ? b.d_all.p : b.d_list.p;
   // (a fused monomer step: k_mono_begin has done it)
   if (!single) {
@@ -1273,8 +1279,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       check(hipGraphLaunch(gexec, gstream), "hipGraphLaunch");
       timers.end(gstream, ev, kt("scc iteration (graph)"), 0.0);
       check(hipStreamSynchronize(gstream), "hipStreamSynchronize");
-      b.status.download(status, stream);
-      sync();
+      fetch(b.status, status);
       timers.resolve();
       std::vector<int> next;
       for (int s : active)
@@ -1289,8 +1294,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         // median first-iteration residual over the batch (all listed systems
         // took part in iteration 0)
         std::vector<double> e;
-        b.err.download(e, stream);
-        sync();
+        fetch(b.err, e);
         std::vector<double> v;
         for (int s : list) v.push_back(e[s]);
         std::nth_element(v.begin(), v.begin() + v.size() / 2, v.end());
@@ -1304,10 +1308,8 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       }
       const int slot = it % CNT_RING;
       hipLaunchKernelGGL(k_compact_active, dim3(1), dim3(1024), 0, stream, (const int*)b.status.p,
-                         (const int*)b.mode.p, (const int*)lst, nl, d_act.p, cnt_dev.p + 2 * slot);
+                         (const int*)b.mode.p, (const int*)lst, nl, d_act.p, cnt_host + 2 * slot);
       check(hipGetLastError(), "k_compact_active");
-      check(hipMemcpyAsync(cnt_host + 2 * slot, cnt_dev.p + 2 * slot, 2 * sizeof(int), hipMemcpyDeviceToHost, stream),
-            "count copy");
       check(hipEventRecord(cnt_ev[slot], stream), "hipEventRecord");
       pending.push_back(slot);
       // take the counts that have arrived; block only when async_lag
@@ -1341,7 +1343,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         if (!is32[s]) ordered.push_back(s);
       active.swap(ordered);
     }
-    d_act.upload(active);
+    put(d_act, active);
     const int na = (int)active.size();
     if (!switched.empty()) {
       d_switched.upload(switched);
@@ -1356,8 +1358,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     if (first_solve && it == 0) {
       // median first-iteration residual over the batch
       std::vector<double> e;
-      b.err.download(e, stream);
-      sync();
+      fetch(b.err, e);
       std::vector<double> v;
       for (int s : active) v.push_back(e[s]);
       if (!v.empty()) {
@@ -1371,10 +1372,11 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
                          opt.guess_tau, fallback_flag.p);
       check(hipGetLastError(), "k_guess_fallback");
     }
-    b.status.download(status, stream);
     std::vector<double> errs;
-    if ((n32 > 0 && prod_mode == 1) || verbose) b.err.download(errs, stream);
-    sync();
+    Transfer get(*this, true);
+    get.get(b.status, status);
+    if ((n32 > 0 && prod_mode == 1) || verbose) get.get(b.err, errs);
+    get.wait();
     timers.resolve();
     // algorithmic work of the eigensolve of one SCC iteration, as budgeted
     // for a dense symmetric eigensolver: 3.3 n^3 (reduction about 1.3 n^3,
@@ -1425,15 +1427,20 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   DevBuf<int> d_open;
   std::vector<int> open(1, 0), modes;
   if (ov && !single) {
-    d_open.upload(open);
+    put(d_open, open);
     hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(256), 0, stream, db, (const int*)lst, P.g.kT, d_open.p);
     check(hipGetLastError(), "k_ov_gap");
-    d_open.download(open, stream);
-    b.mode.download(modes, stream);
   }
-  b.status.download(status, stream);
-  b.niter.download(niter, stream);
-  sync();
+  {
+    Transfer get(*this, true);
+    if (ov && !single) {
+      get.get(d_open, open);
+      get.get(b.mode, modes);
+    }
+    get.get(b.status, status);
+    get.get(b.niter, niter);
+    get.wait();
+  }
   if (async) {
     timers.resolve();
     // algorithmic work from the per-system iteration counts (the launches
@@ -1528,8 +1535,7 @@ int Ctx::run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::
     launch(1);
     --left;
     std::vector<double> e;
-    b.err.download(e, stream);
-    sync();
+    fetch(b.err, e);
     std::vector<double> v;
     for (int s : list) v.push_back(e[s]);
     std::nth_element(v.begin(), v.begin() + v.size() / 2, v.end());
@@ -1551,9 +1557,10 @@ int Ctx::run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::
   }
   if (left > 0) launch(left);
   std::vector<int> status, niter;
-  b.status.download(status, stream);
-  b.niter.download(niter, stream);
-  sync();
+  Transfer get(*this, true);
+  get.get(b.status, status);
+  get.get(b.niter, niter);
+  get.wait();
   timers.resolve();
   kt("fx::k_scc_small")->gflop += small_gflop(b, list, niter);
   int failed = 0;
@@ -1595,7 +1602,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
   for (int pass = 0; pass < max_pass && !todo.empty(); ++pass) {
     const int nt = (int)todo.size();
     if (pass > 0) {
-      pass_list.upload(todo);
+      put(pass_list, todo);
       dt = pass_list.p;
       launch_fock(b, ds, db, dt, nt);
       gemm_batch(b, db, nt, dt, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, 0.0, 1);
@@ -1607,8 +1614,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
     ev = timed ? timers.begin(stream) : -1;
     launch_apply(b, db, dt, nt, stride);
     if (timed) timers.end(stream, ev, kt_app, 0.0);
-    b.nlog.download(nlog, stream);
-    sync();
+    fetch(b.nlog, nlog);
     std::vector<int> next;
     for (int s : todo)
       if (nlog[s] >= cold_log()) next.push_back(s);
@@ -1669,8 +1675,7 @@ void Ctx::ensure_density(Batch& b) {
 bool Ctx::canonical_basis(Batch& b) {
   if (!ov_batch(b) || b.nsys == 0) return true;
   std::vector<double> xn;
-  b.xn.download(xn, stream);
-  sync();
+  fetch(b.xn, xn);
   std::vector<int> l;
   for (int s = 0; s < b.nsys; ++s)
     if (xn[s] >= 0.0) l.push_back(s);
@@ -1679,7 +1684,7 @@ bool Ctx::canonical_basis(Batch& b) {
   DevBatch db = b.dev();
   DevSystem ds = dev_system();
   ensure_density(b);  // (of the orbitals that gave the charges)
-  b.d_list.upload(l);
+  put(b.d_list, l);
   hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl, 1, 0);
   JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);
   auto itp = tuned.find(jp_key(b.max_nao, jp.elt));
@@ -1695,8 +1700,7 @@ bool Ctx::canonical_basis(Batch& b) {
   hipLaunchKernelGGL(k_fermi, dim3(nl), dim3(256), 0, stream, ds, db, b.d_list.p, 1);
   check(hipGetLastError(), "canonical basis");
   std::vector<int> mode;
-  b.mode.download(mode, stream);
-  sync();
+  fetch(b.mode, mode);
   bool gapped = true;
   for (int s : l)
     if (mode[s] != 1) {
@@ -1806,14 +1810,13 @@ Ctx::RotShape Ctx::rot_shape(Batch& b, const DevBatch& db, const int* dl, int na
   return best;
 }
 
-void Ctx::step_send() {
-  if (!step_host) {
-    check(hipEventCreateWithFlags(&step_ev, hipEventDisableTiming), "hipEventCreate");
-    check(hipHostMalloc((void**)&step_host, 2 * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
-  }
-  check(hipMemcpyAsync(step_host, step_max.p, 2 * sizeof(double), hipMemcpyDeviceToHost, stream), "maxima copy");
-  check(hipEventRecord(step_ev, stream), "hipEventRecord");
+double* Ctx::step_target() {
+  if (!step_host) check(hipHostMalloc((void**)&step_host, 2 * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+  if (!step_ev) check(hipEventCreateWithFlags(&step_ev, hipEventDisableTiming), "hipEventCreate");
+  return step_host;
 }
+
+void Ctx::step_mark() { check(hipEventRecord(step_ev, stream), "hipEventRecord"); }
 
 void Ctx::step_wait(double* maxima) {
   check(hipEventSynchronize(step_ev), "hipEventSynchronize");
@@ -1821,9 +1824,75 @@ void Ctx::step_wait(double* maxima) {
   maxima[1] = step_host[1];
 }
 
+// ---------------------------------------------------------------------------
+// host tables to the device and results back (k_transfer)
+
+char* Ctx::Transfer::reserve(size_t bytes, long long* off) {
+  bytes = (bytes + 15) & ~(size_t)15;
+  Pinned& p = c.pinned;
+  if (p.used + bytes > p.cap) {
+    if (to_host)
+      wait();
+    else
+      flush();
+    c.sync();  // every earlier transfer has read its part
+    p.used = 0;
+    if (bytes > p.cap) {
+      if (p.mem) (void)hipHostFree(p.mem);
+      p.mem = nullptr;
+      p.cap = 0;
+      const size_t cap = std::max<size_t>(bytes, 1u << 20);
+      check(hipHostMalloc((void**)&p.mem, cap, hipHostMallocDefault), "hipHostMalloc");
+      p.cap = cap;
+    }
+  }
+  *off = (long long)p.used;
+  p.used += bytes;
+  return p.mem + *off;
+}
+
+void Ctx::Transfer::add(void* dev, const void* src, void* dst, size_t bytes) {
+  if (bytes > (1u << 22)) {  // large tables: a copy each
+    if (src)
+      check(hipMemcpyAsync(dev, src, bytes, hipMemcpyHostToDevice, c.stream), "copy to the device");
+    else
+      check(hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, c.stream), "copy to the host");
+    if (src) c.sync();  // (the caller's vector may go)
+    return;
+  }
+  if (n == TRANSFER_MAX) {
+    if (src)
+      flush();
+    else
+      wait();
+  }
+  long long off;
+  char* h = reserve(bytes, &off);
+  if (src) std::memcpy(h, src, bytes);
+  list.item[n] = {dev, off, (long long)bytes};
+  host[n] = dst;
+  ++n;
+}
+
+void Ctx::Transfer::flush() {
+  if (n == 0) return;
+  long long most = 0;
+  for (int k = 0; k < n; ++k) most = std::max(most, list.item[k].bytes);
+  const unsigned gx = (unsigned)std::min<long long>(64, (most + 16383) / 16384);
+  hipLaunchKernelGGL(k_transfer, dim3(gx, n), dim3(256), 0, c.stream, list, c.pinned.mem, to_host ? 1 : 0);
+  check(hipGetLastError(), "k_transfer");
+  if (!to_host) n = 0;
+}
+
+void Ctx::Transfer::wait() {
+  flush();
+  c.sync();
+  for (int k = 0; k < n; ++k) std::memcpy(host[k], c.pinned.mem + list.item[k].off, (size_t)list.item[k].bytes);
+  n = 0;
+}
+
 void Ctx::count_ring_init() {
   if (cnt_host) return;
-  if (cnt_dev.n < 2 * CNT_RING) cnt_dev.alloc(2 * CNT_RING);
   cnt_ev.assign(CNT_RING, nullptr);
   for (auto& e : cnt_ev) check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
   check(hipHostMalloc((void**)&cnt_host, sizeof(int) * 2 * CNT_RING, hipHostMallocDefault), "hipHostMalloc");
@@ -1838,8 +1907,7 @@ void Ctx::count_ring_init() {
 int Ctx::retry_failed(Batch& b, long long* iters_out) {
   auto unconverged = [&]() {
     std::vector<int> st, l;
-    b.status.download(st, stream);
-    sync();
+    fetch(b.status, st);
     for (int s = 0; s < b.nsys; ++s)
       if (st[s] != 1) l.push_back(s);
     return l;
@@ -1911,7 +1979,7 @@ void Ctx::sum_arrays(const SumArrays& a, double* out) {
 
 void Ctx::field(const double* d_q, double* d_phi, bool fp32) {
   const DevSystem ds = dev_system();
-  if (!fp32 && ds.g.kg == 2.0 && Ne <= field_wave_max) {
+  if (!fp32 && field_is_wave()) {
     const int ev = timers.begin(stream);
     hipLaunchKernelGGL(k_field_wave, dim3((Ne + 3) / 4), dim3(256), 0, stream, ds, d_q, d_phi);
     timers.end(stream, ev, kt("fx::k_field_wave"), 8e-9 * field_pairs);
@@ -1982,8 +2050,7 @@ void Ctx::build_lists_impl() {
     check(hipGetLastError(), "k_pair_contacts");
   }
   std::vector<int8_t> h(npair);
-  if (npair) flag.download(h, stream);
-  sync();
+  if (npair) fetch(flag, h);
   scc_pairs.clear();
   esd_pairs.clear();
   trimers.clear();
@@ -2038,6 +2105,42 @@ void Ctx::build_lists_impl() {
   lists_built = true;
 }
 
+// No two atoms closer than 0.3 bohr: cells of 2 bohr in a hash table of
+// chains; an atom is compared with the chains of every cell that its
+// neighbourhood touches (two cells on average, not all 27 around it).
+void Ctx::check_contacts(const double* xyz) const {
+  const double cs = 2.0, reach = 0.3001;
+  size_t size = 64;
+  while (size < 2 * (size_t)N) size *= 2;
+  std::vector<int> head(size, -1), next(N);
+  auto bucket = [&](long long i, long long j, long long k) {
+    unsigned long long h = (unsigned long long)i * 0x9E3779B97F4A7C15ull;
+    h = (h ^ (h >> 29)) + (unsigned long long)j * 0xBF58476D1CE4E5B9ull;
+    h = (h ^ (h >> 31)) + (unsigned long long)k * 0x94D049BB133111EBull;
+    return (size_t)((h ^ (h >> 32)) & (size - 1));
+  };
+  auto cell = [&](double v) { return (long long)std::floor(v / cs); };
+  for (int A = 0; A < N; ++A) {
+    const double* x = xyz + 3 * (size_t)A;
+    long long lo[3], hi[3];
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = cell(x[k] - reach);
+      hi[k] = cell(x[k] + reach);
+    }
+    for (long long i = lo[0]; i <= hi[0]; ++i)
+      for (long long j = lo[1]; j <= hi[1]; ++j)
+        for (long long k = lo[2]; k <= hi[2]; ++k)
+          for (int B = head[bucket(i, j, k)]; B >= 0; B = next[B]) {
+            double r2 = 0.0;
+            for (int c = 0; c < 3; ++c) r2 += (x[c] - xyz[3 * (size_t)B + c]) * (x[c] - xyz[3 * (size_t)B + c]);
+            if (r2 < 0.09) throw FxError(FX_E_INVALID, "atoms closer than 0.3 bohr");
+          }
+    const size_t h = bucket(cell(x[0]), cell(x[1]), cell(x[2]));
+    next[A] = head[h];
+    head[h] = A;
+  }
+}
+
 void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32_t n_frag, const int32_t* atom_frag,
                      const int32_t* fchg, int32_t n_bonds, const int32_t* bonds_in) {
   if (n_atoms <= 0 || n_frag <= 0 || !Z || !xyz || !atom_frag || !fchg) throw FxError(FX_E_INVALID, "bad system");
@@ -2058,27 +2161,7 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
     for (int k = 0; k < 3; ++k)
       if (!std::isfinite(xyz[3 * A + k])) throw FxError(FX_E_INVALID, "non-finite coordinate");
   }
-  // atoms closer than 0.3 bohr (cell grid)
-  {
-    const double cs = 2.0;
-    std::map<std::array<long long, 3>, std::vector<int>> grid;
-    for (int A = 0; A < N; ++A) {
-      std::array<long long, 3> key = {(long long)std::floor(xyz[3 * A] / cs), (long long)std::floor(xyz[3 * A + 1] / cs),
-                                      (long long)std::floor(xyz[3 * A + 2] / cs)};
-      for (int dx = -1; dx <= 1; ++dx)
-        for (int dy = -1; dy <= 1; ++dy)
-          for (int dz = -1; dz <= 1; ++dz) {
-            auto it = grid.find({key[0] + dx, key[1] + dy, key[2] + dz});
-            if (it == grid.end()) continue;
-            for (int B : it->second) {
-              double r2 = 0.0;
-              for (int k = 0; k < 3; ++k) r2 += (xyz[3 * A + k] - xyz[3 * B + k]) * (xyz[3 * A + k] - xyz[3 * B + k]);
-              if (r2 < 0.09) throw FxError(FX_E_INVALID, "atoms closer than 0.3 bohr");
-            }
-          }
-      grid[key].push_back(A);
-    }
-  }
+  check_contacts(xyz);
   // covalent boundaries: detached atom (stays in its fragment) and attached
   // atom; one ghost atom per bond joins the attached atom's fragment
   NB = n_bonds;
@@ -2144,21 +2227,23 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
     field_pairs = (double)Nsh * Nsh;
     for (double v : nsh_f) field_pairs -= v * v;
   }
-  d_xyz.upload(xyz_h);
-  d_elem.upload(elem);
-  d_frag.upload(frag);
-  d_atom_sh0.upload(atom_sh0_g);
-  d_sh_atom.upload(sh_atom);
-  d_sh_frag.upload(sh_frag);
-  d_sh_eta.upload(sh_eta);
+  Transfer up(*this, false);
+  up.put(d_xyz, xyz_h);
+  up.put(d_elem, elem);
+  up.put(d_frag, frag);
+  up.put(d_atom_sh0, atom_sh0_g);
+  up.put(d_sh_atom, sh_atom);
+  up.put(d_sh_frag, sh_frag);
+  up.put(d_sh_eta, sh_eta);
   std::vector<double> sh_ieta(sh_eta.size());
   for (size_t k = 0; k < sh_eta.size(); ++k) sh_ieta[k] = 0.5 / sh_eta[k];
-  d_sh_ieta.upload(sh_ieta);
-  d_frag_atoms.upload(frag_atoms);
-  d_frag_off.upload(frag_off);
-  d_frag_atoms_real.upload(frag_atoms_real);
-  d_frag_off_real.upload(frag_off_real);
-  d_bonds.upload(bonds.empty() ? std::vector<int>{0, 0} : bonds);
+  up.put(d_sh_ieta, sh_ieta);
+  up.put(d_frag_atoms, frag_atoms);
+  up.put(d_frag_off, frag_off);
+  up.put(d_frag_atoms_real, frag_atoms_real);
+  up.put(d_frag_off_real, frag_off_real);
+  up.put(d_bonds, bonds.empty() ? std::vector<int>{0, 0} : bonds);
+  up.flush();
   d_cn.alloc(Ne);
   d_q.alloc(Nsh);
   d_qnew.alloc(Nsh);
@@ -2178,15 +2263,22 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
 void Ctx::set_coordinates(const double* xyz) {
   if (!has_system) throw FxError(FX_E_STATE, "no system set");
   if (!xyz) throw FxError(FX_E_INVALID, "null coordinates");
-  std::vector<int32_t> Z(N), fr(frag.begin(), frag.begin() + N), ch(frag_charge.begin(), frag_charge.end());
-  for (int A = 0; A < N; ++A) Z[A] = P.elems[elem[A]].Z;
-  std::vector<int32_t> bd(bonds.begin(), bonds.end());
-  const int nb = NB;
-  std::vector<double> g = guess;
-  const bool wv = warm_valid;
-  set_system(N, Z.data(), xyz, F, fr.data(), ch.data(), nb, nb ? bd.data() : nullptr);
-  guess = g;
-  warm_valid = wv;  // same fragments: the last run's clusters remain valid starts
+  // the same atoms, fragments and bonds: every table but the coordinates
+  // stands, and so do the batches' own and the last run's clusters as starts
+  has_system = false;  // (refused coordinates leave no system)
+  for (long long k = 0; k < 3LL * N; ++k)
+    if (!std::isfinite(xyz[k])) throw FxError(FX_E_INVALID, "non-finite coordinate");
+  check_contacts(xyz);
+  xyz_h.assign(xyz, xyz + 3 * (size_t)N);
+  for (int k = 0; k < NB; ++k)
+    for (int c = 0; c < 3; ++c) xyz_h.push_back(xyz[3 * (size_t)bonds[2 * k] + c]);
+  Transfer up(*this, false);
+  up.put(d_xyz, xyz_h);
+  up.flush();
+  has_system = true;
+  lists_built = false;
+  has_result = false;
+  has_grad = false;
 }
 
 // Velocity Verlet (atomic units: bohr, electron masses, hbar/Eh):
@@ -2227,10 +2319,11 @@ void Ctx::md_verlet(int n_steps, double dt, const double* mass, double* xyz, dou
     run(&r);
     if (!res.converged) throw FxError(FX_E_NOCONV, "molecular dynamics step " + std::to_string(step) +
                                                        ": a fragment SCC or the monomer loop did not converge");
-    d_grad.download_raw(gn.data(), n3, stream);
     guess.resize(Nsh);
-    d_q.download_raw(guess.data(), Nsh, stream);
-    sync();
+    Transfer get(*this, true);
+    get.raw(d_grad, gn.data(), n3);
+    get.raw(d_q, guess.data(), Nsh);
+    get.wait();
     return r.e_total;
   };
   double E = energy_gradient(0);
@@ -2310,14 +2403,15 @@ void Ctx::run(fx_result* out) {
   mono_eig = true;
   // mixed precision: FP32 field passes until the monomer charges move by
   // less than 1e-6, FP64 from then on (the fixed point is the FP64 one)
-  bool field32 = mixed;
+  bool field32 = mixed, field_queued = false;
   for (macro = 1; macro <= opt.max_macro; ++macro) {
     if (field32 && delta < 1e-6) {
       field32 = false;
       slots.clear();
       next_slot = 0;
     }
-    field(d_q.p, d_phi.p, field32);
+    if (!field_queued) field(d_q.p, d_phi.p, field32);
+    field_queued = false;
     int failed = 0;
     Slots sl;
     auto next_history = [&]() {
@@ -2347,11 +2441,16 @@ void Ctx::run(fx_result* out) {
       next_history();
       hipLaunchKernelGGL(k_mono_end, dim3(mb.nsys), dim3(64), 0, stream, mb.dev(), d_qnew.p, hX.p, hR.p,
                          (long long)Nsh, sl, step_part.p, step_max.p);
-      step_send();
       hipLaunchKernelGGL(k_hist_next, dim3(std::min(gN, 256u)), dim3(256), 0, stream, (const double*)hX.p,
                          (const double*)hR.p, (long long)Nsh, sl, (const double*)step_part.p, mb.nsys, hG.p, fused_beta,
-                         d_q.p);
+                         d_q.p, (const double*)step_max.p, step_target());
       check(hipGetLastError(), "monomer step");
+      step_mark();
+      // (the next step's field runs while the host wakes, where it costs less
+      // than that, 4 against 25 us at 264 atoms; after the last step the pass
+      // over the converged charges replaces it)
+      field_queued = !field32 && field_is_wave();
+      if (field_queued) field(d_q.p, d_phi.p);
       const bool ov = ov_batch(mb);
       double mx[2];
       step_wait(mx);
@@ -2361,8 +2460,7 @@ void Ctx::run(fx_result* out) {
         if (!(0.2 * mx[1] <= delta)) delta = 0.2 * mx[1];
         if (mono_eig) {
           std::vector<int> modes;
-          mb.mode.download(modes, stream);
-          sync();
+          fetch(mb.mode, modes);
           mono_eig = std::any_of(modes.begin(), modes.end(), [](int m) { return m != 1; });
         } else {
           mono_eig = mx[1] > OV_XMAX;
@@ -2402,8 +2500,7 @@ void Ctx::run(fx_result* out) {
       first_solve = false;
       if (cold) {
         std::vector<int> fl;
-        fallback_flag.download(fl, stream);
-        sync();
+        fetch(fallback_flag, fl);
         for (int v : fl) res.guess_fallbacks += v;
       }
       scc_tol_cur = etol_cur = -1.0;
@@ -2415,8 +2512,7 @@ void Ctx::run(fx_result* out) {
     hipLaunchKernelGGL(k_scatter_shell, dim3(mb.nsys), dim3(64), 0, stream, dmb, mb.q_out.p, d_qnew.p);
     max_absdiff(d_qnew.p, d_q.p, Nsh, d_scalar.p);
     std::vector<double> hs(1);
-    d_scalar.download(hs, stream, 1);
-    sync();
+    fetch(d_scalar, hs, 1);
     delta = hs[0];
     if (verbose)
       std::fprintf(stderr, "[fx] monomer sweep %d: max |dq_out - dq_in| = %.3e, %.1f ms\n", macro, delta,
@@ -2491,8 +2587,10 @@ void Ctx::run(fx_result* out) {
         ++nwarm;
       }
       if (nwarm > 0) {
-        db_.warm_off.upload(mo);
-        warm_so.upload(so);
+        Transfer up(*this, false);
+        up.put(db_.warm_off, mo);
+        up.put(warm_so, so);
+        up.flush();
         hipLaunchKernelGGL(k_warm_start, dim3(db_.nsys), dim3(256), 0, stream, ddb, db_.warm_off.p, warm_so.p,
                            warm_C.p, warm_q.p);
         check(hipGetLastError(), "k_warm_start");
@@ -2579,7 +2677,7 @@ void Ctx::run(fx_result* out) {
   dE_esd.alloc(std::max(1LL, nesd));
   if (nesd > 0) {
     DevBuf<int> dp;
-    dp.upload(esd_pairs);
+    put(dp, esd_pairs);
     if (nesd > 0x7fffffffLL) throw FxError(FX_E_INVALID, "too many ES-DIM pairs");
     hipLaunchKernelGGL(k_esd_pairs, dim3((unsigned)nesd), dim3(64), 0, stream, dev_system(), dp.p,
                        nesd, d_frag_atoms.p, d_frag_off.p, d_q.p, dE_esd.p);
@@ -2589,8 +2687,7 @@ void Ctx::run(fx_result* out) {
   {
     sum_arrays({3, {e_mono.p, dE_scc.p, dE_esd.p}, {F, nscc, nesd}}, d_scalar.p);
     std::vector<double> hs(1);
-    d_scalar.download(hs, stream, 1);
-    sync();
+    fetch(d_scalar, hs, 1);
     res.e_fmo2 = hs[0];
     res.e_total = hs[0];
   }
@@ -2610,7 +2707,7 @@ void Ctx::run(fx_result* out) {
       sub_idx[3 * k + 2] = where.at((long long)J * F + K);
     }
     DevBuf<long long> d_sub;
-    d_sub.upload(sub_idx);
+    put(d_sub, sub_idx);
     hipLaunchKernelGGL(k_trimer_corr, dim3((unsigned)((ntri + 255) / 256)), dim3(256), 0, stream, ntri,
                        (const double*)d_dEIJK.p, (const double*)dE_scc.p, nscc, (const double*)dE_esd.p,
                        (const long long*)d_sub.p, dE_tri.p);
@@ -2619,8 +2716,7 @@ void Ctx::run(fx_result* out) {
     outv.alloc(1);
     sum_arrays({2, {d_scalar.p, dE_tri.p, nullptr}, {1, ntri, 0}}, outv.p);
     std::vector<double> hs(1);
-    outv.download(hs, stream, 1);
-    sync();
+    fetch(outv, hs, 1);
     res.e_total = hs[0];
   }
   double t5 = now_ms();
@@ -2908,11 +3004,12 @@ int fx_get_energies(fx_ctx* ctx, double* E_mono, double* dE_scc, double* dE_esd,
     if (!c.has_result) throw fx::FxError(FX_E_STATE, "no result");
     const long long nscc = (long long)c.scc_pairs.size() / 2, nesd = (long long)c.esd_pairs.size() / 2,
                     ntri = (long long)c.trimers.size() / 3;
-    if (E_mono) c.e_mono.download_raw(E_mono, c.F, c.stream);
-    if (dE_scc && nscc) c.dE_scc.download_raw(dE_scc, nscc, c.stream);
-    if (dE_esd && nesd) c.dE_esd.download_raw(dE_esd, nesd, c.stream);
-    if (dE_tri && ntri && c.opt.order >= 3) c.dE_tri.download_raw(dE_tri, ntri, c.stream);
-    c.sync();
+    fx::Ctx::Transfer get(c, true);
+    if (E_mono) get.raw(c.e_mono, E_mono, c.F);
+    if (dE_scc && nscc) get.raw(c.dE_scc, dE_scc, nscc);
+    if (dE_esd && nesd) get.raw(c.dE_esd, dE_esd, nesd);
+    if (dE_tri && ntri && c.opt.order >= 3) get.raw(c.dE_tri, dE_tri, ntri);
+    get.wait();
   });
 }
 
@@ -2920,8 +3017,9 @@ int fx_get_charges(fx_ctx* ctx, double* dq) {
   if (!ctx || !dq) return FX_E_INVALID;
   FX_GUARD(ctx, {
     if (!ctx->c.has_result) throw fx::FxError(FX_E_STATE, "no result");
-    ctx->c.d_q.download_raw(dq, ctx->c.Nsh, ctx->c.stream);
-    ctx->c.sync();
+    fx::Ctx::Transfer get(ctx->c, true);
+    get.raw(ctx->c.d_q, dq, ctx->c.Nsh);
+    get.wait();
   });
 }
 
@@ -2929,8 +3027,9 @@ int fx_get_gradient(fx_ctx* ctx, double* grad) {
   if (!ctx || !grad) return FX_E_INVALID;
   FX_GUARD(ctx, {
     if (!ctx->c.has_grad) throw fx::FxError(FX_E_STATE, "no gradient computed");
-    ctx->c.d_grad.download_raw(grad, 3LL * ctx->c.N, ctx->c.stream);
-    ctx->c.sync();
+    fx::Ctx::Transfer get(ctx->c, true);
+    get.raw(ctx->c.d_grad, grad, 3LL * ctx->c.N);
+    get.wait();
   });
 }
 

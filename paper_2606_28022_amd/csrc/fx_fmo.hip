@@ -433,8 +433,9 @@ __global__ void __launch_bounds__(64) k_resp_end(DevBatch bt, const double* v, c
 // work-group, and the work-group's slice of q = sum_k c_k (x_k + beta r_k).
 __global__ void __launch_bounds__(256) k_hist_next(const double* X, const double* R, long long n, Slots sl,
                                                    const double* part, int nparts, double* gram, double beta,
-                                                   double* q) {
+                                                   double* q, const double* maxima, double* host_maxima) {
   const int m = sl.m, M = m + 1, W = M + 1, t = threadIdx.x;
+  if (blockIdx.x == 0 && t < 2) host_maxima[t] = maxima[t];  // (pinned: the step's residual for the host)
   __shared__ double sum[32][HIST], row[HIST], B[(HIST + 1) * (HIST + 2)], f[HIST + 1], coef[HIST];
   {
     const int k = t & (HIST - 1);
@@ -475,6 +476,25 @@ __global__ void __launch_bounds__(256) k_hist_next(const double* X, const double
     for (int k = 0; k < m; ++k) v += coef[k] * (X[sl.id[k] * n + g] + beta * R[sl.id[k] * n + g]);
     q[g] = v;
   }
+}
+
+// Several host tables to their device buffers (or back) in one launch:
+// blockIdx.y's piece lies at its offset of the pinned block `host`, which the
+// kernel reads or writes over the bus.  A blocking copy each cost 25 to 35 us,
+// about 60 of them per run; offsets are multiples of 16 bytes, device
+// addresses those of whole buffers.
+__global__ void __launch_bounds__(256) k_transfer(TransferList l, char* host, int to_host) {
+  const TransferItem it = l.item[blockIdx.y];
+  char* const h = host + it.off;
+  char* const d = static_cast<char*>(it.dev);
+  const char* const src = to_host ? d : h;
+  char* const dst = to_host ? h : d;
+  const long long tid = (long long)blockIdx.x * 256 + threadIdx.x, nth = (long long)gridDim.x * 256;
+  const bool wide = (reinterpret_cast<unsigned long long>(d) & 15) == 0;
+  const long long n16 = wide ? it.bytes / 16 : 0;
+  for (long long k = tid; k < n16; k += nth)
+    reinterpret_cast<float4*>(dst)[k] = reinterpret_cast<const float4*>(src)[k];
+  for (long long k = 16 * n16 + tid; k < it.bytes; k += nth) dst[k] = src[k];
 }
 
 // Trimer corrections Delta E_IJK - Delta E_IJ - Delta E_IK - Delta E_JK

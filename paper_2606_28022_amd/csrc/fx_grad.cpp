@@ -32,7 +32,7 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
   const int nt = (b.max_nao + 31) / 32;
   std::vector<int> all(b.nsys);
   for (int k = 0; k < b.nsys; ++k) all[k] = k;
-  b.d_list.upload(all);
+  c.put(b.d_list, all);
   // W = C diag(n eps) C^T into T (symmetric; over the orbitals of the last
   // occupation list, whose weights n eps vanish with n), D_S into F
   std::vector<int> all_sys(b.nsys);
@@ -42,15 +42,14 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
   std::vector<int> rot;
   if (c.ov_batch(b)) {
     std::vector<double> xn;
-    b.xn.download(xn, c.stream);
-    c.sync();
+    c.fetch(b.xn, xn);
     std::vector<int> eig;
     for (int k = 0; k < b.nsys; ++k) (xn[k] >= 0.0 ? rot : eig).push_back(k);
     if (!rot.empty()) {
       all_sys = eig;
       all = eig;
       all.insert(all.end(), rot.begin(), rot.end());
-      b.d_list.upload(all);
+      c.put(b.d_list, all);
     }
   }
   const int ne = (int)all_sys.size(), nr = (int)rot.size();
@@ -83,8 +82,10 @@ void cluster_csr(Ctx& c, Batch& b, DevBuf<int>& ptr, DevBuf<int>& ent) {
   for (int s = 0; s < c.Nsh; ++s) cnt[s + 1] += cnt[s];
   std::vector<int> pos(cnt.begin(), cnt.end() - 1);
   for (int k = 0; k < (int)shg.size(); ++k) e[pos[shg[k]]++] = k;
-  ptr.upload(cnt);
-  ent.upload(e);
+  Ctx::Transfer up(c, false);
+  up.put(ptr, cnt);
+  up.put(ent, e);
+  up.flush();
 }
 
 }  // namespace
@@ -127,9 +128,13 @@ void Ctx::gradient() {
   }
   DevBuf<double> d_cw, d_sw;
   DevBuf<int> d_tmask;
-  d_cw.upload(cw);
-  d_sw.upload(sw);
-  d_tmask.upload(tmask);
+  {
+    Transfer up(*this, false);
+    up.put(d_cw, cw);
+    up.put(d_sw, sw);
+    up.put(d_tmask, tmask);
+    up.flush();
+  }
 
   // ---- explicit fragment terms and the per-cluster corrections of the
   //      all-pairs force pass; projector forces of boundary entries in
@@ -287,9 +292,10 @@ void Ctx::gradient() {
       qoff[k + 1] = qoff[k] + (long long)d.nsh * nocc[k] * (d.nao - nocc[k]);
     }
     DevBuf<int> d_nocc, order;
-    d_nocc.upload(nocc);
+    Transfer up(*this, false);
+    up.put(d_nocc, nocc);
     DevBuf<long long> d_qoff;
-    d_qoff.upload(qoff);
+    up.put(d_qoff, qoff);
     DevBuf<double> Q, M, R, Wk, G1, G2, G3, w, gx;
     long long tot_gam = 0;
     for (auto& d : b.h_desc) tot_gam += (long long)d.nsh * d.nsh;
@@ -307,7 +313,8 @@ void Ctx::gradient() {
     gx.alloc(b.tot_sh);
     std::vector<int> all(b.nsys);
     for (int k = 0; k < b.nsys; ++k) all[k] = k;
-    b.d_list.upload(all);
+    up.put(b.d_list, all);
+    up.flush();
     const int nt = (b.max_nao + 31) / 32;
     // the susceptibility blocks of the converged monomer orbitals are kept
     // from the monomer loop when available
@@ -357,9 +364,12 @@ void Ctx::gradient() {
     const int max_sweeps = opt.max_response;
     // the FP32 sweeps end after a quarter of the allowed sweeps at the latest
     const int max_fp32_sweeps = std::max(1, max_sweeps / 4);
+    auto sweep = [&](const double* y) {
+      hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M, y, w.p, u.p,
+                         step_max.p);
+    };
+    sweep(yg.p);
     for (it = 1; it <= max_sweeps; ++it) {
-      hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M,
-                         (const double*)yg.p, w.p, u.p, step_max.p);
       field(u.p, fu.p, field32);
       int slot;
       if ((int)slots.size() < HIST) {
@@ -374,11 +384,12 @@ void Ctx::gradient() {
       for (int k = 0; k < sl.m; ++k) sl.id[k] = slots[k];
       hipLaunchKernelGGL(k_resp_end, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)v.p, (const double*)fu.p,
                          (const double*)yg.p, yng.p, hX.p, hR.p, (long long)Nsh, sl, step_part.p, step_max.p);
-      step_send();
       // (the mixing runs while the host learns of the sweep's change)
       hipLaunchKernelGGL(k_hist_next, dim3(std::min(gN, 256u)), dim3(256), 0, stream, (const double*)hX.p,
-                         (const double*)hR.p, (long long)Nsh, sl, (const double*)step_part.p, b.nsys, hG.p, 1.0, yg.p);
+                         (const double*)hR.p, (long long)Nsh, sl, (const double*)step_part.p, b.nsys, hG.p, 1.0, yg.p, (const double*)step_max.p, step_target());
       check(hipGetLastError(), "response sweep");
+      step_mark();
+      sweep(yg.p);  // the next one's, while the host wakes
       double mx[2];
       step_wait(mx);
       delta = mx[0];
@@ -399,8 +410,7 @@ void Ctx::gradient() {
                                 max_sweeps, delta);
     }
     // final w, u from the converged y
-    hipLaunchKernelGGL(k_resp_sweep, dim3(b.nsys), dim3(64), 0, stream, dmb, (const double*)R.p, p_M,
-                       (const double*)yng.p, w.p, u.p, step_max.p);
+    sweep(yng.p);
     // Z and its AO forms
     const int sl = slices(b, b.nsys);
     hipLaunchKernelGGL(k_resp_Z, dim3(b.nsys, sl), dim3(256), 0, stream, dmb, p_order, d_nocc.p, d_qoff.p, p_Q, w.p,
@@ -434,9 +444,10 @@ void Ctx::gradient() {
   if (!force_map_built) build_force_map();
   DevBuf<int> d_rp, d_eb;
   DevBuf<long long> d_eo;
-  d_rp.upload(rowptr);
-  d_eb.upload(ent_b);
-  d_eo.upload(ent_o);
+  Transfer up(*this, false);
+  up.put(d_rp, rowptr);
+  up.put(d_eb, ent_b);
+  up.put(d_eo, ent_o);
   // batches 3 and 4 carry forces only: their CN sensitivities read zeros
   zero_f.alloc(std::max(1LL, std::max(n_healed, 2 * n_slots)));
   check(hipMemsetAsync(zero_f.p, 0, sizeof(double) * std::max(1LL, std::max(n_healed, 2 * n_slots)), stream),
@@ -444,8 +455,9 @@ void Ctx::gradient() {
   std::vector<const double*> gb = {gm.p, nscc > 0 ? gd.p : gm.p, ntri > 0 ? gt.p : gm.p, ghost_f.p, hop_f.p};
   std::vector<const double*> fb = {Fm_.p, nscc > 0 ? Fd.p : Fm_.p, ntri > 0 ? Ft.p : Fm_.p, zero_f.p, zero_f.p};
   DevBuf<const double*> d_gb, d_fb;
-  d_gb.upload(gb);
-  d_fb.upload(fb);
+  up.put(d_gb, gb);
+  up.put(d_fb, fb);
+  up.flush();
   DevBuf<double> Ftot;
   Ftot.alloc(N);
   d_grad.alloc(3LL * N);

@@ -353,6 +353,55 @@ struct Ctx {
     if (cnt_host) (void)hipHostFree(cnt_host);
     if (step_ev) (void)hipEventDestroy(step_ev);
     if (step_host) (void)hipHostFree(step_host);
+    if (pinned.mem) (void)hipHostFree(pinned.mem);
+  }
+  // Host tables to device buffers, or results back, as one launch for all of
+  // them (k_transfer) through a pinned block: put ... flush, or get ... wait.
+  // put copies the vector at once; a flushed block is not written again
+  // before the stream has passed it.  One Transfer at a time may hold
+  // unflushed pieces; what is not flushed is dropped (an exception on the
+  // way).
+  struct Pinned {
+    char* mem = nullptr;
+    size_t cap = 0, used = 0;
+  } pinned;
+  struct Transfer {
+    Ctx& c;
+    const bool to_host;
+    int n = 0;
+    TransferList list;
+    void* host[TRANSFER_MAX];
+    Transfer(Ctx& c_, bool to_host_) : c(c_), to_host(to_host_) {}
+    char* reserve(size_t bytes, long long* off);
+    void add(void* dev, const void* src, void* dst, size_t bytes);
+    void flush();
+    void wait();
+    template <class T>
+    void put(DevBuf<T>& b, const std::vector<T>& v) {
+      b.alloc((long long)v.size());
+      if (!v.empty()) add(b.p, v.data(), nullptr, sizeof(T) * v.size());
+    }
+    template <class T>
+    void raw(const DevBuf<T>& b, T* dst, long long count) {
+      if (count > 0) add(b.p, nullptr, dst, sizeof(T) * (size_t)count);
+    }
+    template <class T>
+    void get(const DevBuf<T>& b, std::vector<T>& v, long long count = -1) {
+      v.resize((size_t)(count < 0 ? b.n : count));
+      raw(b, v.data(), (long long)v.size());
+    }
+  };
+  template <class T>
+  void put(DevBuf<T>& b, const std::vector<T>& v) {
+    Transfer t(*this, false);
+    t.put(b, v);
+    t.flush();
+  }
+  template <class T>
+  void fetch(const DevBuf<T>& b, std::vector<T>& v, long long count = -1) {
+    Transfer t(*this, true);
+    t.get(b, v, count);
+    t.wait();
   }
   HostParams P;
   int device = 0;
@@ -630,15 +679,17 @@ struct Ctx {
   int async_lag = 2;
   int* cnt_host = nullptr;  // [CNT_RING][2], pinned
   std::vector<hipEvent_t> cnt_ev;
-  DevBuf<int> cnt_dev;
   void count_ring_init();
   // maxima of a step of the iterations over the whole charge vector
-  // (k_mono_end, k_resp_end): device pair, pinned copy, event
+  // (k_mono_end, k_resp_end): device pair, pinned copy (written by
+  // k_hist_next)
   DevBuf<unsigned long long> step_max;
   double* step_host = nullptr;
   hipEvent_t step_ev = nullptr;
-  void step_send();                // queue the copy
+  double* step_target();
+  void step_mark();                // behind k_hist_next
   void step_wait(double* maxima);  // wait for it
+  bool field_is_wave() const { return P.g.kg == 2.0 && Ne <= field_wave_max; }
   DevBuf<double> step_part;        // Gram row parts, HIST per monomer
   int run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* iters_out, bool single = false,
               bool refresh = false);
@@ -655,6 +706,7 @@ struct Ctx {
   // FX_RETRY_DAMPED_ITERS lets a test force the second stage
   int retry_damped_iters = std::getenv("FX_RETRY_DAMPED_ITERS") ? std::atoi(std::getenv("FX_RETRY_DAMPED_ITERS")) : 0;
   void run(fx_result* out);
+  void check_contacts(const double* xyz) const;
   void set_coordinates(const double* xyz);
   void md_verlet(int n_steps, double dt, const double* mass, double* xyz, double* vel, double* e_pot,
                  double* e_kin);

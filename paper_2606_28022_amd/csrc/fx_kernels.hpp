@@ -208,8 +208,18 @@ __global__ void k_resp_sweep(DevBatch bt, const double* R, const double* M, cons
                              unsigned long long* maxima);
 __global__ void k_resp_end(DevBatch bt, const double* v, const double* fu, const double* y, double* y_new, double* X,
                            double* R, long long n, Slots sl, double* part, unsigned long long* maxima);
+struct TransferItem {
+  void* dev;
+  long long off, bytes;
+};
+constexpr int TRANSFER_MAX = 24;
+struct TransferList {
+  TransferItem item[TRANSFER_MAX];
+};
+__global__ void k_transfer(TransferList l, char* host, int to_host);
 __global__ void k_hist_next(const double* X, const double* R, long long n, Slots sl, const double* part, int nparts,
-                            double* gram, double beta, double* q);
+                            double* gram, double beta, double* q,
+                            const double* maxima, double* host_maxima);
 __global__ void k_hist_store(const double* x, const double* y, long long n, int slot, double* X, double* R);
 
 // response and gradient kernels

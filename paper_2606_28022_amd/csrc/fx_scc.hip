@@ -99,7 +99,8 @@ __global__ void k_hist_reset(DevBatch bt, const int* list, int nl) {
 // Stable partition of the list by status, on the device: the systems still
 // iterating (status 0) first, in list order, then the others, in list order;
 // count[0] = the number of the former, count[1] = how many of these the
-// eigensolver (not an orbital rotation) takes next.  One work-group of 1024 threads: each
+// eigensolver (not an orbital rotation) takes next (count is pinned host
+// memory).  One work-group of 1024 threads: each
 // thread takes a contiguous chunk of the list, and a scan over the chunk
 // counts places it.  Every list entry is written, so a kernel launched over
 // more slots than *count finds converged systems there and returns.
