@@ -656,7 +656,7 @@ struct Ctx {
   bool canonical_basis(Batch& b);
   // passes of logged sweeps to convergence (cold solves by the split form)
   void rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
-                  const RotShape& rs, long long stride, bool timed);
+                  const RotShape& rs, long long stride, bool timed, const double* F = nullptr);
   void launch_apply(const Batch& b, const DevBatch& db, const int* dl, int na, long long log_stride);
   RotShape rot_shape(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
                      long long log_stride, bool may_tune);

@@ -241,6 +241,7 @@ constexpr int MAXN_RESP_LDS = 96, RR_THREADS = 512;
 __global__ void k_resp_R_lds(DevSystem sys, DevBatch bt, const double* M, double* R);
 __global__ void k_resp_Z(DevBatch bt, const int* order, const int* nocc, const long long* qoff, const double* Q,
                          const double* w, double* Zm, double* Ze);
+__global__ void k_identity(DevBatch bt, double* A);
 __global__ void k_rowscale(DevBatch bt, const double* wsh, const double* P, double* out);
 __global__ void k_sym_inplace(DevBatch bt, double* A);
 __global__ void k_resp_DS(DevSystem sys, DevBatch bt, const double* Zb, const double* WZ, const double* X2, const double* wsh,

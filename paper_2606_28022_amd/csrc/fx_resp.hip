@@ -630,6 +630,14 @@ __global__ void k_rowscale(DevBatch bt, const double* wsh, const double* P, doub
   }
 }
 
+// unit matrices
+__global__ void k_identity(DevBatch bt, double* A) {
+  const SysDesc d = bt.desc[blockIdx.x];
+  const int n = d.nao;
+  for (int idx = blockIdx.y * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.y * blockDim.x)
+    A[d.mat_off + idx] = idx % (n + 1) == 0 ? 1.0 : 0.0;
+}
+
 // symmetrise a matrix pool in place: A <- (A + A^T) / 2
 __global__ void k_sym_inplace(DevBatch bt, double* A) {
   const int si = blockIdx.x;
