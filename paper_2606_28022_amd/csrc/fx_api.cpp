@@ -1107,11 +1107,12 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   const bool split_ok = jacobi_split && jp.elt != 0 && (long long)apply_rot_lds_bytes(b.max_nao) <= lds_max &&
                         (int)jacobi_rot_layout(b.max_nao, jp.elt).total <= lds_max &&
                         8 * m4 <= 2 * 64 * apply_rot_waves(b.max_nao);
-  // cold solve by the split form (not in the mixed-precision form, whose
-  // cold iteration builds only the FP32 Fock matrix)
+  // cold solve by the split form (in the mixed-precision form too: the first
+  // pass takes the FP32 products' A, the rebuilds are FP64; 48 pentacenes by
+  // the LDS-resident kernel: 4.1 ms, by passes: 1.75)
   // warm iterations of gapped systems by occupied-virtual rotations
   const bool ov = ov_batch(b) && split_ok;
-  const bool cold_split = split_ok && jacobi_cold_log > 0 && cold && !b.init_from_mono && !(b.has_f32 && prod_mode != 0);
+  const bool cold_split = split_ok && jacobi_cold_log > 0 && cold && !b.init_from_mono;
   const long long cold_stride = (long long)jacobi_cold_log * jacobi_rot_log_entries(b.max_nao);
   if (split_ok) {
     b.rotlog.alloc((long long)b.nsys * (cold_split ? std::max(log_stride, cold_stride) : log_stride));
@@ -2415,8 +2416,11 @@ void Ctx::run(fx_result* out) {
   bool refresh = true;
   mono_eig = true;
   // mixed precision: FP32 field passes until the monomer charges move by
-  // less than 1e-6, FP64 from then on (the fixed point is the FP64 one)
-  bool field32 = mixed, field_queued = false;
+  // less than 1e-6, FP64 from then on (the fixed point is the FP64 one);
+  // FP64 throughout where that is one launch of the wave form (1728 atoms:
+  // 15 us against 17 for the FP32 pass's reduction alone; and no new history:
+  // 18 steps against 20)
+  bool field32 = mixed && !field_is_wave(), field_queued = false;
   for (macro = 1; macro <= opt.max_macro; ++macro) {
     if (field32 && delta < 1e-6) {
       field32 = false;

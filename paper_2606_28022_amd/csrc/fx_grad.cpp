@@ -359,7 +359,8 @@ void Ctx::gradient() {
     // mixed precision: FP32 field passes while the sweeps still change y by
     // more than 1e-6, FP64 from then on (the fixed point is the FP64 one; the
     // tolerance is only tested on FP64 sweeps)
-    bool field32 = opt.precision == FX_MIXED;
+    // (not where the FP64 pass is the wave form's one launch)
+    bool field32 = opt.precision == FX_MIXED && !field_is_wave();
     bool resp_converged = false;
     const int max_sweeps = opt.max_response;
     // the FP32 sweeps end after a quarter of the allowed sweeps at the latest
