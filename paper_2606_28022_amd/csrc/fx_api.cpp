@@ -177,6 +177,9 @@ DevSystem Ctx::dev_system() const {
   s.sh_eta = d_sh_eta.p;
   s.sh_ieta = d_sh_ieta.p;
   s.elems = d_elems.p;
+  s.prim_row = d_prim_row.p;
+  s.prim_rows = prim_rows;
+  s.prim = d_prim.p;
   s.g = P.g;
   return s;
 }
@@ -946,9 +949,10 @@ void Ctx::build_matrices(Batch& b, bool from_mono) {
   // clusters of a system without cut bonds copy their monomers' blocks (the
   // monomer batch holds this geometry's matrices)
   const int copy = from_mono && bonds.empty() && b.h_nfrag > 1 ? 1 : 0;
-  const int sl = slices(b, b.nsys);
+  const PairShape ps = pair_shape(b);
+  const int sl = ps.slices;
   if (sl > 1) erep_part.alloc((long long)b.nsys * sl);
-  hipLaunchKernelGGL(k_build_system, dim3(b.nsys, sl), dim3(256), 0, stream, dev_system(), db, nullptr, mb.dev(),
+  hipLaunchKernelGGL(ps.split ? k_build_system<4> : k_build_system<1>, dim3(b.nsys, sl), dim3(256), 0, stream, dev_system(), db, nullptr, mb.dev(),
                      copy, erep_part.p);
   if (sl > 1)
     hipLaunchKernelGGL(k_erep_sum, dim3((b.nsys + 255) / 256), dim3(256), 0, stream, db, b.nsys, sl,
@@ -1439,7 +1443,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   std::vector<int> open(1, 0), modes;
   if (ov && !single) {
     put(d_open, open);
-    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(256), 0, stream, db, (const int*)lst, P.g.kT, d_open.p);
+    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(1024), 0, stream, db, (const int*)lst, P.g.kT, d_open.p);
     check(hipGetLastError(), "k_ov_gap");
   }
   {
@@ -2119,6 +2123,27 @@ void Ctx::build_lists_impl() {
   lists_built = true;
 }
 
+// The primitive-pair table of the elements that the system has
+void Ctx::build_prim_table() {
+  std::vector<int> row(P.elems.size(), -1), present;
+  for (int e : elem)
+    if (row[e] < 0) {
+      row[e] = (int)present.size();
+      present.push_back(e);
+    }
+  prim_rows = (int)present.size();
+  for (int& r : row) r = std::max(r, 0);
+  DevBuf<int> d_present;
+  Transfer up(*this, false);
+  up.put(d_prim_row, row);
+  up.put(d_present, present);
+  up.flush();
+  d_prim.alloc((long long)prim_rows * prim_rows * PRIM_PAIRS);
+  hipLaunchKernelGGL(k_prim_table, dim3(prim_rows * prim_rows), dim3(192), 0, stream, d_elems.p, d_present.p, prim_rows,
+                     d_prim.p);
+  check(hipGetLastError(), "k_prim_table");
+}
+
 // No two atoms closer than 0.3 bohr: cells of 2 bohr in a hash table of
 // chains; an atom is compared with the chains of every cell that its
 // neighbourhood touches (two cells on average, not all 27 around it).
@@ -2258,6 +2283,7 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
   up.put(d_frag_off_real, frag_off_real);
   up.put(d_bonds, bonds.empty() ? std::vector<int>{0, 0} : bonds);
   up.flush();
+  build_prim_table();
   d_cn.alloc(Ne);
   d_q.alloc(Nsh);
   d_qnew.alloc(Nsh);

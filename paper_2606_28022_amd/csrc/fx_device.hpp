@@ -12,6 +12,7 @@ namespace fx {
 
 constexpr int MAXSH_EL = 2;   // shells per element (minimal s/p basis)
 constexpr int NPRIM = 6;      // STO-6G
+constexpr int PRIM_PAIRS = MAXSH_EL * MAXSH_EL * NPRIM * NPRIM;
 constexpr int MAXAO_EL = 4;   // AOs per element
 constexpr int HIST = 8;       // Anderson mixing memory
 constexpr int MAXN = 512;     // largest system (AOs) handled by the SCC kernels
@@ -64,8 +65,23 @@ struct DevSystem {
   const double* sh_eta;   // [Nsh] (1 + kappa) eta_A
   const double* sh_ieta;  // [Nsh] 1 / (2 (1 + kappa) eta_A): 1/eta_st = ieta_s + ieta_t
   const DevElem* elems;
+  // primitive pairs of the elements present (k_prim_table): row of each
+  // element, number of rows, PRIM_PAIRS entries per (row, row)
+  const int* prim_row;
+  int prim_rows;
+  const double4* prim;
   DevGlobals g;
 };
+__device__ inline const double4* prim_pairs(const DevSystem& sys, int el_a, int el_b) {
+  return sys.prim + (long long)(sys.prim_row[el_a] * sys.prim_rows + sys.prim_row[el_b]) * PRIM_PAIRS;
+}
+// sum over a group of L neighbouring lanes, in every lane of it
+template <int L>
+__device__ inline double lanes_sum(double v) {
+#pragma unroll
+  for (int o = 1; o < L; o <<= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
 
 // Per-batch tables and pools.
 struct DevBatch {

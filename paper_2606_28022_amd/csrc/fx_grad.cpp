@@ -66,7 +66,8 @@ void explicit_terms(Ctx& c, Batch& b, const double* wsys, DevBuf<double>& g_sys,
   for (auto& d : b.h_desc) natot += d.nat;
   g_sys.alloc(3LL * natot);
   F_sys.alloc(natot);
-  hipLaunchKernelGGL(k_grad_pairs, dim3(b.nsys, sl), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, b.Fm.p,
+  const Ctx::PairShape ps = c.pair_shape(b);
+  hipLaunchKernelGGL(ps.split ? k_grad_pairs<4> : k_grad_pairs<1>, dim3(b.nsys, ps.slices), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, b.Fm.p,
                      b.q_out.p, b.q_out.p, 1, b.Tm.p);
   hipLaunchKernelGGL(k_grad_gather, dim3(b.nsys), dim3(256), 0, c.stream, ds, db, b.d_list.p, b.Pm.p, wsys, 0, g_sys.p,
                      F_sys.p, (const double*)b.Tm.p);
@@ -431,7 +432,8 @@ void Ctx::gradient() {
     if (b.has_hop)
       hipLaunchKernelGGL(k_hop_grad, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, (const double*)G1.p, b.Fm.p,
                          (const double*)nullptr, (const int*)d_bonds.p, P.g.VHOP, n_hop_m + n_hop_d, hop_f.p);
-    hipLaunchKernelGGL(k_grad_pairs, dim3(b.nsys, sl), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p, b.Fm.p, gx.p,
+    const PairShape ps = pair_shape(b);
+    hipLaunchKernelGGL(ps.split ? k_grad_pairs<4> : k_grad_pairs<1>, dim3(b.nsys, ps.slices), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p, b.Fm.p, gx.p,
                        b.q_out.p, 0, b.Tm.p);
     hipLaunchKernelGGL(k_grad_gather, dim3(b.nsys), dim3(256), 0, stream, ds, dmb, b.d_list.p, G1.p,
                        (const double*)nullptr, 1, gm.p, Fm_.p, (const double*)b.Tm.p);

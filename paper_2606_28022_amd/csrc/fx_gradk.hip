@@ -63,10 +63,11 @@ __device__ inline double gamma_and_deriv(const DevGlobals& g, double R, double e
 //   p p:  S_uv = R_u R_v sum(fa fb s00) + delta_uv sum(h s00);
 //         g_k += ((W R)_k + (W^T R)_k) sum(fa fb s00)
 //                + R_k (R.W.R sum(-2 mu fa fb s00) + tr W sum(-2 mu h s00))
-__device__ void atom_pair_overlap_contract(const DevElem& ea, const DevElem& eb, const double Rv[3],
-                                           double (&W)[MAXAO_EL][MAXAO_EL], double S[MAXAO_EL][MAXAO_EL],
-                                           double g[3]) {
-  const double PI = 3.14159265358979323846;
+// (primitive pairs from the table of k_prim_table, shared by L lanes)
+template <int L>
+__device__ void atom_pair_overlap_contract(const DevElem& ea, const DevElem& eb, const double4* prim, int l,
+                                           const double Rv[3], double (&W)[MAXAO_EL][MAXAO_EL],
+                                           double S[MAXAO_EL][MAXAO_EL], double g[3]) {
   const double R2 = Rv[0] * Rv[0] + Rv[1] * Rv[1] + Rv[2] * Rv[2];
   if (ea.orth) {
 #pragma unroll
@@ -95,34 +96,20 @@ __device__ void atom_pair_overlap_contract(const DevElem& ea, const DevElem& eb,
       const int kind = 2 * la + lb;  // 0 s s, 1 s p, 2 p s, 3 p p
       // shell-pair sums over the primitives
       double t0 = 0.0, t1 = 0.0, t2 = 0.0, t3 = 0.0;
-#pragma unroll 1
-      for (int i = 0; i < NPRIM; ++i) {
-        const double a = ea.alpha[sa][i];
-        for (int j = 0; j < NPRIM; ++j) {
-          const double b = eb.alpha[sb][j];
-          const double ip = 1.0 / (a + b);
-          const double mu = a * b * ip;
-          const double s00 = ea.coef[sa][i] * eb.coef[sb][j] * PI * ip * sqrt(PI * ip) * exp(-mu * R2);
-          const double d00 = -2.0 * mu * s00;
-          const double fa = -b * ip, fb = a * ip;
-          if (kind == 0) {
-            t0 += s00;
-            t1 += d00;
-          } else if (kind == 2) {
-            t0 += fa * s00;
-            t1 += fa * d00;
-          } else if (kind == 1) {
-            t0 += fb * s00;
-            t1 += fb * d00;
-          } else {
-            const double ff = fa * fb, h = 0.5 * ip;
-            t0 += ff * s00;
-            t1 += ff * d00;
-            t2 += h * s00;
-            t3 += h * d00;
-          }
-        }
+      const double4* pr = prim + (sa * MAXSH_EL + sb) * NPRIM * NPRIM;
+#pragma unroll 3
+      for (int p = l; p < NPRIM * NPRIM; p += L) {
+        const double4 q = pr[p];
+        const double e = exp(-q.x * R2), m = q.x * e;
+        t0 += q.y * e;
+        t1 += q.y * m;
+        t2 += q.z * e;
+        t3 += q.z * m;
       }
+      t0 = lanes_sum<L>(t0);
+      t1 = -2.0 * lanes_sum<L>(t1);
+      t2 = lanes_sum<L>(t2);
+      t3 = -2.0 * lanes_sum<L>(t3);
       const int oa = sa, ob = sb;
       if (kind == 0) {
         S[oa][ob] = t0;
@@ -173,10 +160,13 @@ __device__ void atom_pair_overlap_contract(const DevElem& ea, const DevElem& eb,
 // at fixed CN, for every atom a of the system, and the CN sensitivity
 // F_a = d/dCN_a of the D_H term.  Results are multiplied by the system weight
 // and written (or added) to the per-system atom arrays.
-// Two kernels: the pairs, bound by the latency of their overlap and gamma
-// chains (spread over gridDim.y work-groups where the batch is small: 28
-// pentacene pairs 352 -> 137 us), then the sums per atom, whose order does
-// not depend on that split.
+// Two kernels: the pairs, then the sums per atom, whose order does not depend
+// on how the pairs were split.  The pairs are bound by FP64 arithmetic, most
+// of it exponentials (3425 pentacene pairs 5.7 ms with the primitive pairs'
+// factors formed in the loop, 3.4 from the table), in small batches by the
+// latency of one pair, which four lanes then share, with up to four
+// work-groups per CU: 13 pentacene pairs 352 -> 44 us, 8 waters 73 -> 23.
+template <int L>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
     k_grad_pairs(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
                  const double* gx, const double* gy, int with_rep, double* scratch) {
@@ -194,7 +184,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
   // (5 nat (nat - 1) / 2 <= n^2 doubles)
   double* pb = scratch + d.mat_off;
   const int np = nat * (nat - 1) / 2;
-  for (int p = blockIdx.y * blockDim.x + threadIdx.x; p < np; p += gridDim.y * blockDim.x) {
+  for (int x0 = blockIdx.y * blockDim.x + threadIdx.x; x0 < np * L; x0 += gridDim.y * blockDim.x) {
+    const int p = x0 / L, l = x0 % L;
     int a = 0, rem = p;
     while (rem >= nat - 1 - a) {
       rem -= nat - 1 - a;
@@ -245,7 +236,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
         const long long mn = (long long)(oa + i) * n + ob + j;
         W[i][j] = 2.0 * (fac[sa][sb] * DH[mn] + DS[mn]);
       }
-    atom_pair_overlap_contract(ea, eb, Rv, W, S, g);
+    atom_pair_overlap_contract<L>(ea, eb, prim_pairs(sys, sys.elem[A], sys.elem[B]), l, Rv, W, S, g);
 #pragma unroll
     for (int i = 0; i < MAXAO_EL; ++i)
 #pragma unroll
@@ -273,22 +264,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
         Fb += 2.0 * sumDHS[sa][sb] * base * Pi * 0.5 * eb.level[sb] * eb.kcn[sb];
       }
     if (gx) {
-      int s0 = ash[a], t0 = ash[b];
-      for (int sa = 0; sa < ea.nsh; ++sa)
-        for (int sb = 0; sb < eb.nsh; ++sb) {
-          double dg;
-          gamma_and_deriv(sys.g, R, ea.eta[sa], eb.eta[sb], &dg);
-          double c = 0.5 * (gx[d.sh_off + s0 + sa] * gy[d.sh_off + t0 + sb] +
-                            gy[d.sh_off + s0 + sa] * gx[d.sh_off + t0 + sb]);
-          for (int k = 0; k < 3; ++k) g[k] += c * dg * uR[k];
-        }
+      // (the shell pairs shared by the lanes)
+      const double* gxs = gx + d.sh_off;
+      const double* gys = gy + d.sh_off;
+      double t = 0.0;
+      for (int e = l; e < ea.nsh * eb.nsh; e += L) {
+        const int sa = e / eb.nsh, sb = e - sa * eb.nsh, ls = ash[a] + sa, lt = ash[b] + sb;
+        double dg;
+        gamma_and_deriv(sys.g, R, ea.eta[sa], eb.eta[sb], &dg);
+        t += 0.5 * (gxs[ls] * gys[lt] + gys[ls] * gxs[lt]) * dg;
+      }
+      t = lanes_sum<L>(t);
+      for (int k = 0; k < 3; ++k) g[k] += t * uR[k];
     }
+    if (l != 0) continue;
     if (with_rep) {
       double al = sqrt(ea.arep * eb.arep);
       // repulsion charges of boundary atoms are scaled (detached atom, ghost)
       const double zs = bt.atom_zs ? bt.atom_zs[d.atom_off + a] * bt.atom_zs[d.atom_off + b] : 1.0;
-      double e = zs * ea.zeff * eb.zeff / R * exp(-al * pow(R, sys.g.kf));
-      double de = e * (-1.0 / R - al * sys.g.kf * pow(R, sys.g.kf - 1.0));
+      const double rk = pow(R, sys.g.kf);
+      double e = zs * ea.zeff * eb.zeff / R * exp(-al * rk);
+      double de = e * (-1.0 - al * sys.g.kf * rk) / R;
       for (int k = 0; k < 3; ++k) g[k] += de * uR[k];
     }
     double* o = pb + 5LL * p;
@@ -299,6 +295,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
     o[4] = Fb;
   }
 }
+
+template __global__ void k_grad_pairs<1>(DevSystem, DevBatch, const int*, const double*, const double*, const double*,
+                                         const double*, int, double*);
+template __global__ void k_grad_pairs<4>(DevSystem, DevBatch, const int*, const double*, const double*, const double*,
+                                         const double*, int, double*);
 
 // The pair values of k_grad_pairs and the one-centre CN terms, summed per
 // atom in the order of the other atoms: four neighbouring threads take the

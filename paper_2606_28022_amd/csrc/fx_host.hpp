@@ -640,8 +640,7 @@ struct Ctx {
   // or atom pairs can be cut anywhere: one where the batch alone covers the
   // chip (the loop's setup is then paid once), up to eight where it does not,
   // as long as every slice keeps 32 rows (FX_SLICES: at most that many).
-  // 8 pentacenes and 28 pairs, one or up to eight: build 307 -> 69 / 84 us,
-  // gradient pairs 352 -> 68 / 137 us, transition charges 270 -> 105 us.
+  // 8 pentacenes, one or four: transition charges 270 -> 105 us.
   int max_slices = std::getenv("FX_SLICES") ? std::atoi(std::getenv("FX_SLICES")) : 8;
   int slices(const Batch& b, int nsys) const {
     int s = 1;
@@ -649,6 +648,32 @@ struct Ctx {
     return s;
   }
   DevBuf<double> erep_part;
+  // Lanes per atom pair (k_build_system, k_grad_pairs): four where that still
+  // is one pass of a work-group, or where the batch's pairs leave two thirds
+  // of the chip's lanes idle, else one.
+  // Work-groups per system: up to four per CU, while each has a full pass.
+  // 13 pentacene pairs, one lane and eight work-groups: 137 us in
+  // k_grad_pairs; four lanes: 126; four lanes and 32 work-groups: 44.
+  struct PairShape {
+    bool split;
+    int slices;
+  };
+  PairShape pair_shape(const Batch& b) const {
+    long long most = 0, all = 0;
+    for (const SysDesc& d : b.h_desc) {
+      const long long p = (long long)d.nat * (d.nat - 1) / 2;
+      most = std::max(most, p);
+      all += p;
+    }
+    PairShape s{most <= 64 || all <= 256LL * n_cu, 1};
+    while (max_slices > 1 && 2LL * s.slices * b.nsys <= 4LL * n_cu && 256LL * s.slices < (s.split ? 4 : 1) * most)
+      s.slices *= 2;
+    return s;
+  }
+  DevBuf<int> d_prim_row;
+  DevBuf<double4> d_prim;
+  int prim_rows = 0;
+  void build_prim_table();
   void launch_fock(const Batch& b, const DevSystem& ds, const DevBatch& db, const int* dl, int na);
   // eigenvectors and eigenvalues of the systems of b whose last iteration was
   // a rotation; false when one of them has no gap any more (it is then left to

@@ -139,14 +139,42 @@ __global__ void __launch_bounds__(256) k_pair_contacts(DevSystem sys, const int*
 // ---------------------------------------------------------------------------
 // overlap block between two atoms (raw contracted shells, then the on-site
 // orthogonalisation), R = A - B.  out is nao_a x nao_b, row-major, ld = 4.
-// Every primitive term of a shell pair is s00 times a polynomial in R whose
-// coefficients depend on the primitive pair only through fa = -b / (a + b),
+// Every primitive term of a shell pair is exp(-mu R^2) times a polynomial in R
+// whose coefficients depend on the primitive pair only, with fa = -b / (a + b),
 // fb = a / (a + b) and h = 1 / (2 (a + b)): s s sum s00; p s R_u sum(fa s00);
 // s p R_v sum(fb s00); p p R_u R_v sum(fa fb s00) + delta_uv sum(h s00).  So
-// the primitive loop accumulates at most two scalars per shell pair.
-__device__ void atom_pair_overlap(const DevElem& ea, const DevElem& eb, double Rx, double Ry,
-                                  double Rz, double out[MAXAO_EL][MAXAO_EL]) {
+// the loop over primitive pairs accumulates at most two scalars per shell pair
+// from the table of k_prim_table (a division, a square root and their products
+// per term otherwise, as long as the exponential).  L neighbouring lanes share
+// the terms of a pair and hold the same block in the end.
+
+// mu, coefficient of the s00 sum and (p p) of the h s00 sum for every
+// primitive pair of every two elements present
+__global__ void k_prim_table(const DevElem* elems, const int* present, int rows, double4* out) {
   const double PI = 3.14159265358979323846;
+  const DevElem& ea = elems[present[blockIdx.x / rows]];
+  const DevElem& eb = elems[present[blockIdx.x % rows]];
+  for (int e = threadIdx.x; e < PRIM_PAIRS; e += blockDim.x) {
+    const int sh = e / (NPRIM * NPRIM), p = e - sh * NPRIM * NPRIM;
+    const int sa = sh / MAXSH_EL, sb = sh - sa * MAXSH_EL, i = p / NPRIM, j = p - i * NPRIM;
+    double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (sa < ea.nsh && sb < eb.nsh) {
+      const int kind = 2 * ea.l[sa] + eb.l[sb];  // 0 s s, 1 s p, 2 p s, 3 p p
+      const double a = ea.alpha[sa][i], b = eb.alpha[sb][j];
+      const double ip = 1.0 / (a + b);
+      const double s0 = ea.coef[sa][i] * eb.coef[sb][j] * PI * ip * sqrt(PI * ip);
+      const double fa = -b * ip, fb = a * ip;
+      v.x = a * b * ip;
+      v.y = kind == 0 ? s0 : kind == 1 ? fb * s0 : kind == 2 ? fa * s0 : fa * fb * s0;
+      v.z = kind == 3 ? 0.5 * ip * s0 : 0.0;
+    }
+    out[(long long)blockIdx.x * PRIM_PAIRS + e] = v;
+  }
+}
+
+template <int L>
+__device__ void atom_pair_overlap(const DevElem& ea, const DevElem& eb, const double4* prim, int l, double Rx,
+                                  double Ry, double Rz, double out[MAXAO_EL][MAXAO_EL]) {
   double R2 = Rx * Rx + Ry * Ry + Rz * Rz;
   double Rv[3] = {Rx, Ry, Rz};
   for (int i = 0; i < MAXAO_EL; ++i)
@@ -160,27 +188,17 @@ __device__ void atom_pair_overlap(const DevElem& ea, const DevElem& eb, double R
     for (int sb = 0; sb < MAXSH_EL; ++sb) {
       if (sa >= ea.nsh || sb >= eb.nsh) continue;
       const int kind = 2 * ea.l[sa] + eb.l[sb];  // 0 s s, 1 s p, 2 p s, 3 p p
+      const double4* pr = prim + (sa * MAXSH_EL + sb) * NPRIM * NPRIM;
       double t0 = 0.0, t2 = 0.0;
-#pragma unroll 1
-      for (int i = 0; i < NPRIM; ++i) {
-        const double a = ea.alpha[sa][i];
-        for (int j = 0; j < NPRIM; ++j) {
-          const double b = eb.alpha[sb][j];
-          const double ip = 1.0 / (a + b);
-          const double mu = a * b * ip;
-          const double s00 = ea.coef[sa][i] * eb.coef[sb][j] * PI * ip * sqrt(PI * ip) * exp(-mu * R2);
-          if (kind == 0) {
-            t0 += s00;
-          } else if (kind == 2) {
-            t0 += -b * ip * s00;
-          } else if (kind == 1) {
-            t0 += a * ip * s00;
-          } else {
-            t0 += (-b * ip) * (a * ip) * s00;
-            t2 += 0.5 * ip * s00;
-          }
-        }
+#pragma unroll 3
+      for (int p = l; p < NPRIM * NPRIM; p += L) {
+        const double4 q = pr[p];
+        const double e = exp(-q.x * R2);
+        t0 += q.y * e;
+        t2 += q.z * e;
       }
+      t0 = lanes_sum<L>(t0);
+      t2 = lanes_sum<L>(t2);
       const int oa = sa, ob = sb;
       if (kind == 0) {
         out[oa][ob] = t0;
@@ -218,8 +236,9 @@ __device__ inline double h0_prefactor(const DevGlobals& g, const DevElem& ea, in
 
 // S and H0 blocks of the atom pair (a, b), a != b, written in both
 // triangles; returns the pair's repulsion energy
+template <int L>
 __device__ inline double pair_block(const DevSystem& sys, const DevBatch& bt, const SysDesc& d, int n,
-                                    const int* atoms, const int* aao, int a, int b, double* S, double* H) {
+                                    const int* atoms, const int* aao, int a, int b, int l, double* S, double* H) {
   const int A = atoms[a], B = atoms[b];
   const DevElem& ea = sys.elems[sys.elem[A]];
   const DevElem& eb = sys.elems[sys.elem[B]];
@@ -228,7 +247,8 @@ __device__ inline double pair_block(const DevSystem& sys, const DevBatch& bt, co
   const double Rz = sys.xyz[3 * A + 2] - sys.xyz[3 * B + 2];
   const double R = sqrt(Rx * Rx + Ry * Ry + Rz * Rz);
   double blk[MAXAO_EL][MAXAO_EL];
-  atom_pair_overlap(ea, eb, Rx, Ry, Rz, blk);
+  atom_pair_overlap<L>(ea, eb, prim_pairs(sys, sys.elem[A], sys.elem[B]), l, Rx, Ry, Rz, blk);
+  if (l != 0) return 0.0;
   const int oa = aao[a], ob = aao[b];
   double f[MAXSH_EL][MAXSH_EL];
 #pragma unroll
@@ -262,8 +282,10 @@ __device__ inline double pair_block(const DevSystem& sys, const DevBatch& bt, co
 // is copied from the monomer batch, and only the pairs between components
 // are evaluated; the repulsion adds the monomers' own.
 // gridDim.y work-groups share a system (every element has one writer; only
-// the repulsion energy is a sum over them, completed by k_erep_sum): 28
-// pentacene pairs took 307 us on 28 CUs, 84 us on 224.
+// the repulsion energy is a sum over them, completed by k_erep_sum), L lanes
+// an atom pair.  13 pentacene pairs: 307 us on 13 CUs with one lane per pair,
+// 33 us so; 3425 of them 3.3 -> 2.7 ms by the table of primitive pairs.
+template <int L>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono,
                    double* erep_part) {
@@ -346,7 +368,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   // pairs off(a) = a nat - a (a + 1) / 2 .. off(a + 1) - 1; with copied
   // components, the pairs between components only
   const int nat = d.nat, np = copy ? roff[nrect] : nat * (nat - 1) / 2;
-  for (int idx = tid; idx < np; idx += nth) {
+  for (int x = tid; x < np * L; x += nth) {
+    const int idx = x / L;
     int a, b;
     if (copy) {
       int k = 0;
@@ -362,7 +385,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
       while ((a + 1) * nat - (a + 1) * (a + 2) / 2 <= idx) ++a;
       b = idx - (a * nat - a * (a + 1) / 2) + a + 1;
     }
-    erep += pair_block(sys, bt, d, n, atoms, aao, a, b, S, H);
+    erep += pair_block<L>(sys, bt, d, n, atoms, aao, a, b, x % L, S, H);
   }
   // gamma of the system's shells (with copied components: between them)
   double* G = bt.gam + d.gam_off;
@@ -402,6 +425,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
       erep_part[(long long)si * gridDim.y + blockIdx.y] = e;
   }
 }
+
+template __global__ void k_build_system<1>(DevSystem, DevBatch, const int*, DevBatch, int, double*);
+template __global__ void k_build_system<4>(DevSystem, DevBatch, const int*, DevBatch, int, double*);
 
 // repulsion energies of systems that k_build_system built in slices: their
 // parts in slice order

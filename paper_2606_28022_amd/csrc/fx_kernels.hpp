@@ -11,8 +11,10 @@ namespace fx {
 __global__ void k_cn(DevSystem sys, int nchunk, double* part);
 __global__ void k_pair_contacts(DevSystem sys, const int* frag_atoms, const int* frag_off, int lanes, int rule, double cut2,
                                 double lam2, double lam3, int8_t* flag);
+template <int L>
 __global__ void k_build_system(DevSystem sys, DevBatch bt, const int* list, DevBatch mono, int from_mono,
                                double* erep_part);
+__global__ void k_prim_table(const DevElem* elems, const int* present, int rows, double4* out);
 __global__ void k_erep_sum(DevBatch bt, int nsys, int slices, const double* erep_part);
 __global__ void k_field_partial(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_partial_f32(DevSystem sys, const double* q, int nchunk, double* part);
@@ -254,6 +256,7 @@ __global__ void k_sub_healed(DevBatch bt, const double* vgh, double* v);
 __global__ void k_gather_csr(int n, const int* rowptr, const int* ent, const double* src, const double* base,
                              double sign, double* dst);
 __global__ void k_axpy(long long n, const double* x, double a, const double* y, double* out);
+template <int L>
 __global__ void k_grad_pairs(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* DSp,
                              const double* gx, const double* gy, int with_rep, double* scratch);
 __global__ void k_grad_gather(DevSystem sys, DevBatch bt, const int* list, const double* DHp, const double* wsys,

@@ -377,7 +377,9 @@ template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const 
 // within 0.05 Eh of the gap's edges.  Where it no longer keeps the
 // occupations at 0 and 2 to 1e-10, the system leaves the rotation route for
 // good (mode 2) and becomes active again; *reopened counts them.
-__global__ void __launch_bounds__(256) k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened) {
+// Bound by the chain of orbitals, one product with F each: sixteen waves (four
+// took 162 us for 13 pentacene pairs and 1.5 ms for 3425; now 85 us and 1.2 ms).
+__global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened) {
   const int si = list[blockIdx.x];
   if (bt.status[si] != 1 || !(bt.xn[si] >= 0.0)) return;
   const SysDesc d = bt.desc[si];
@@ -386,23 +388,26 @@ __global__ void __launch_bounds__(256) k_ov_gap(DevBatch bt, const int* list, do
   const int* ox = bt.ov_idx + d.ao_off;
   const double* F = bt.F + d.mat_off;
   const double* Ct = bt.Ct + d.mat_off;
-  __shared__ double red[4];
+  __shared__ double red[16];
   __shared__ double crow[MAXN];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  __shared__ double es[MAXN];
+  for (int k = threadIdx.x; k < n; k += blockDim.x) es[k] = eps[ox[k]];
+  __syncthreads();
   double homo = -1e300, lumo = 1e300;
   for (int k = 0; k < n; ++k) {
-    if (k < no) homo = fmax(homo, eps[ox[k]]);
-    else lumo = fmin(lumo, eps[ox[k]]);
+    if (k < no) homo = fmax(homo, es[k]);
+    else lumo = fmin(lumo, es[k]);
   }
   double ho = -1e300, lu = 1e300;
   for (int k = 0; k < n; ++k) {
     const int o = ox[k];
-    const double e = eps[o];
+    const double e = es[k];
     if (k < no ? e < homo - 0.05 : e > lumo + 0.05) continue;
-    for (int j = threadIdx.x; j < n; j += 256) crow[j] = Ct[(long long)o * n + j];
+    for (int j = threadIdx.x; j < n; j += blockDim.x) crow[j] = Ct[(long long)o * n + j];
     __syncthreads();
     double v = 0.0;
-    for (int r = wave; r < n; r += 4) {
+    for (int r = wave; r < n; r += nw) {
       double t = 0.0;
       for (int j = lane; j < n; j += 64) t = fma(F[(long long)r * n + j], crow[j], t);
       v = fma(crow[r], t, v);
@@ -410,7 +415,8 @@ __global__ void __launch_bounds__(256) k_ov_gap(DevBatch bt, const int* list, do
     v = wave_sum_f64(v);
     if (lane == 0) red[wave] = v;
     __syncthreads();
-    v = (red[0] + red[1]) + (red[2] + red[3]);
+    v = 0.0;
+    for (int w = 0; w < nw; ++w) v += red[w];
     __syncthreads();
     if (k < no) ho = fmax(ho, v);
     else lu = fmin(lu, v);
