@@ -534,9 +534,11 @@ __global__ void k_gemm(DevBatch bt, const int* list, int mode, const double* Aba
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 // MODE is a template argument: each product form gets its own kernel with
-// only its own addressing, and every thread keeps 32-bit element offsets that
-// advance by one K slab per step (few registers, so several work-groups share
-// a CU and hide each other's load latency).
+// only its own addressing.  Bound by the matrix cores together with the latency
+// of the slabs: loads, weights and padding blocks under conditions made every
+// slab wait for the next one's loads (mode 2 with populations: 254 us per
+// iteration of 3425 pentacene dimers on average, 11.8 us for 13); with neither
+// branch nor use of a load before its slab is stored, 217 and 9.7 us.
 // WIN = 1 (modes 0 and 1, a two-fragment cluster whose basis rows are its
 // monomers' orbitals, block diagonal, the first fragment's AOs 0 .. n1 - 1):
 // only the output rows >= n1 and columns < n1 are needed (the fragment-pair
@@ -591,24 +593,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   constexpr int KS = 32, LD = 65;
   __shared__ double As[KS][LD];  // [k][i]
   __shared__ double Bs[KS][LD];  // [k][j]
-  __shared__ int kxs[MODE == 2 ? MAXN : 1];  // the listed orbitals, staged once
+  __shared__ int kxs[MODE == 2 ? MAXN : 1];     // the listed orbitals, staged once
+  __shared__ double kws[MODE == 2 ? MAXN : 1];  // and the weights
   const int tid = threadIdx.x;
-  if (use_list) {
+  if (MODE == 2) {
     const int* kg = bt.occ_idx + d.ao_off;
-    for (int k = tid; k < nk; k += 256) kxs[k] = kg[k];
+    for (int k = tid; k < nk; k += 256) {
+      const int g = use_list ? kg[k] : k;
+      kxs[k] = g;
+      if (w) kws[k] = w[g];
+    }
     __syncthreads();
   }
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = wave >> 1, wj = wave & 1;
   const int i0 = ti * 64, j0 = tj * 64;
-  // 16 x 16 output blocks of this wave that hold a real element: the others
-  // lie wholly in the padding and are neither computed nor stored
-  bool blk[2][2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v) blk[u][v] = i0 + wi * 32 + 16 * u < n && j0 + wj * 32 + 16 * v < n;
-  const bool all4 = blk[1][1];
   v4d acc[2][2];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -619,110 +618,61 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   //   "k-major" operand (A in mode 2, B in modes 0/2):   k = tid / 64 + 4 h, r = tid % 64
   const int rr = tid >> 5, rk = tid & 31;  // row-major
   const int kk_ = tid >> 6, kr = tid & 63; // k-major
-  // A: slab element offsets at k0 = 0 and validity of the fixed index
-  int a_off, b_off, a_step, b_step, a_hstep, b_hstep;
-  bool a_fix, b_fix;
-  if (MODE == 2) {
-    a_off = kk_ * n + i0 + kr;
-    a_hstep = 4 * n;
-    a_step = KS * n;
-    a_fix = i0 + kr < n;
-  } else {
-    a_off = (i0 + rr) * n + rk;
-    a_hstep = 8 * n;
-    a_step = KS;
-    a_fix = true;
-  }
-  if (MODE == 1) {
-    b_off = (j0 + rr) * n + rk;
-    b_hstep = 8 * n;
-    b_step = KS;
-    b_fix = true;
-  } else {
-    b_off = kk_ * n + j0 + kr;
-    b_hstep = 4 * n;
-    b_step = KS * n;
-    b_fix = j0 + kr < n;
-  }
-  if (WIN == 1) {  // start at K = kbeg (row-major operands: + kbeg, k-major: + kbeg rows)
-    a_off += MODE == 2 ? kbeg * n : kbeg;
-    b_off += MODE == 1 ? kbeg : kbeg * n;
-  }
+  // No branch around a load or a product: rows and columns past n repeat the
+  // last one (their results are not stored), k indices past nk repeat the last
+  // with a zero on A's side.  A slab is in flight during the products of the
+  // one before, so the weights wait until it is stored (staged once here).
+  const int a_row0 = (i0 + rr) * n, b_row0 = (j0 + rr) * n, row8 = 8 * n, last = (n - 1) * n;
+  const int a_col = min(i0 + kr, n - 1), b_col = min(j0 + kr, n - 1);  // (k-major operands)
   double ra[8], rb[8];
   auto fetch = [&](int k0) {
-    if (MODE == 2 && use_list) {
-      int gk[8];
 #pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        const int pk = k0 + kk_ + 4 * h;
-        gk[h] = pk < nk ? kxs[pk] : -1;
-      }
-#pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        ra[h] = (a_fix && gk[h] >= 0) ? A[gk[h] * n + i0 + kr] * w[gk[h]] : 0.0;
-        rb[h] = (b_fix && gk[h] >= 0) ? B[gk[h] * n + j0 + kr] : 0.0;
-      }
-      return;
+    for (int h = 0; h < 8; ++h) {
+      const int kr_ = min(k0 + rk, nk - 1), pk = min(k0 + kk_ + 4 * h, nk - 1);
+      const int km = (use_list ? kxs[MODE == 2 ? pk : 0] : pk) * n;
+      ra[h] = A[MODE == 2 ? km + a_col : min(a_row0 + h * row8, last) + kr_];
+      rb[h] = B[MODE == 1 ? min(b_row0 + h * row8, last) + kr_ : km + b_col];
     }
+  };
+  auto stage = [&](int k0) {
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
       if (MODE == 2) {
-        const int gk = k0 + kk_ + 4 * h;
-        ra[h] = (a_fix && gk < nk) ? A[a_off + h * a_hstep] * (w ? w[gk] : 1.0) : 0.0;
+        const int pk = k0 + kk_ + 4 * h;
+        As[kk_ + 4 * h][kr] = pk < nk ? (w ? ra[h] * kws[pk] : ra[h]) : 0.0;
       } else {
-        const int gi = i0 + rr + 8 * h, gk = k0 + rk;
-        ra[h] = (gi < n && gk < nk) ? A[a_off + h * a_hstep] : 0.0;
+        As[rk][rr + 8 * h] = k0 + rk < nk ? ra[h] : 0.0;
       }
-      if (MODE == 1) {
-        const int gj = j0 + rr + 8 * h, gk = k0 + rk;
-        rb[h] = (gj < n && gk < nk) ? B[b_off + h * b_hstep] : 0.0;
-      } else {
-        const int gk = k0 + kk_ + 4 * h;
-        rb[h] = (b_fix && gk < nk) ? B[b_off + h * b_hstep] : 0.0;
-      }
-    }
-    a_off += a_step;
-    b_off += b_step;
-  };
-  fetch(kbeg);
-  for (int k0 = kbeg; k0 < nk; k0 += KS) {
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      if (MODE == 2)
-        As[kk_ + 4 * h][kr] = ra[h];
-      else
-        As[rk][rr + 8 * h] = ra[h];
       if (MODE == 1)
         Bs[rk][rr + 8 * h] = rb[h];
       else
         Bs[kk_ + 4 * h][kr] = rb[h];
     }
-    __syncthreads();
-    if (k0 + KS < nk) fetch(k0 + KS);
-    if (all4 && k0 + KS <= nk) {
+  };
+  auto products = [&](int kk) {
+    const int krow = kk + (lane >> 4), c = lane & 15;
+    const double a0 = As[krow][wi * 32 + c], a1 = As[krow][wi * 32 + 16 + c];
+    const double b0 = Bs[krow][wj * 32 + c], b1 = Bs[krow][wj * 32 + 16 + c];
+    acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
+    acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
+    acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+    acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+  };
+  if (nk > kbeg) {
+    fetch(kbeg);
+    int k0 = kbeg;
+    for (; k0 + KS < nk; k0 += KS) {
+      stage(k0);
+      __syncthreads();
+      fetch(k0 + KS);
 #pragma unroll
-      for (int kk = 0; kk < KS; kk += 4) {
-        const int krow = kk + (lane >> 4), c = lane & 15;
-        const double a0 = As[krow][wi * 32 + c], a1 = As[krow][wi * 32 + 16 + c];
-        const double b0 = Bs[krow][wj * 32 + c], b1 = Bs[krow][wj * 32 + 16 + c];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-      }
-    } else {
-      // a wave with padding blocks, or the last slab: the steps past nk
-      // (zero padding) and the padding blocks are left out
-      for (int kk = 0; kk < KS && k0 + kk < nk; kk += 4) {
-        const int krow = kk + (lane >> 4), c = lane & 15;
-        const double a0 = As[krow][wi * 32 + c], a1 = As[krow][wi * 32 + 16 + c];
-        const double b0 = Bs[krow][wj * 32 + c], b1 = Bs[krow][wj * 32 + 16 + c];
-        if (blk[0][0]) acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        if (blk[0][1]) acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        if (blk[1][0]) acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        if (blk[1][1]) acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-      }
+      for (int kk = 0; kk < KS; kk += 4) products(kk);
+      __syncthreads();
     }
+    // the last slab: 1 to KS long, whole steps of four
+    stage(k0);
+    __syncthreads();
+    for (int kk = 0; k0 + kk < nk; kk += 4) products(kk);
     __syncthreads();
   }
   if (WIN == 2) {
