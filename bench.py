@@ -23,12 +23,12 @@ sys.path.insert(0, ROOT)
 
 MI355X_FP64_PEAK_TFLOPS = 78.6
 
-# HBM traffic of the dominant kernel on this workload, from two rocprofv3 PMC
+# HBM traffic of the largest kernels on this workload, from two rocprofv3 PMC
 # passes (FETCH_SIZE scaled by 2 and WRITE_SIZE by 1, the factors a 1 GiB
 # device copy gives), bytes per launch averaged over the launches of the
 # warm-up and the timed step; valid while the kernel and the SCC schedule are
-# unchanged (profiles/k_apply_rot_dual_pentacene_fmo2.md gives the commands)
-PMC_TRAFFIC_BYTES = {"fx::k_apply_rot_dual": 2.14e9 + 0.90e9, "fx::k_apply_rot": 0.14e9 + 0.06e9}
+# unchanged (profiles/pentacene_fmo2.md gives the commands)
+PMC_TRAFFIC_BYTES = {"fx::k_gemm_mfma": 0.36e9 + 0.10e9, "fx::k_ov_apply": 0.61e9 + 0.62e9, "fx::k_ov_grad": 0.79e9 + 0.07e9}
 
 
 def scc_iteration_work(n, n_occ):
@@ -446,7 +446,8 @@ def main():
 
     # roofline of the dominant kernel: the library times its hot kernels with
     # HIP events on the context stream (fx_result.kstat, largest first) and
-    # credits each with algorithmic work: the eigensolver kernels 3.3 n^3 per
+    # credits each with algorithmic work: orbital rotations their products, the
+    # eigensolver kernels 3.3 n^3 per
     # SCC iteration (the split form: 1.3 n^3 to the rotation kernel, 2 n^3,
     # the back-transformation of the eigenvectors, to the apply kernel),
     # products 2 n^3 (symmetric ones by the tiles computed, the density over
@@ -461,7 +462,7 @@ def main():
                            "avg_launch_ms": avg, "launches": k["launches"], "total_ms": k["ms"],
                            "share_of_step": k["ms"] / (1000.0 * sec)}
     dom = r["kernels"][0]["name"]
-    bound = "mfma" if "gemm" in dom else "alu"
+    bound = "mfma" if "gemm" in dom or "k_ov" in dom else "alu"
     # whole step: the SCC iterations at 3.3 n^3 + 5 n^2 n_occ each plus the
     # field passes, over the measured step time
     nm, om = fragment_sizes(s)

@@ -165,10 +165,16 @@ typedef struct fx_counts {
 /* Event-timed statistics of one kernel over a fx_run call: summed device
  * time of its launches (HIP events recorded on the context stream around each
  * launch), launch count and algorithmic work in GFLOP:
- *   fx::k_jacobi_lds<float|double>, fx::k_jacobi   6 n^2 (n - 1) per sweep
+ *   fx::k_jacobi_rot<float|double>, fx::k_apply_rot(_dual)
+ *                            1.3 n^3 and 2 n^3 per SCC iteration
+ *   fx::k_jacobi_lds<float|double>, fx::k_jacobi    3.3 n^3 per SCC iteration
+ *   fx::k_ov_grad            2 (n^2 o + n o v), o occupied and v virtual orbitals
+ *   fx::k_ov_apply           8 n o v per rotation
+ *   fx::k_scc_small          7.3 n^3 + n^2 electrons per SCC iteration
  *   fx::k_gemm_mfma, fx::k_gemm                      2 n^3 per product
- *   fx::k_field_sym,         8 per ordered inter-fragment shell pair (one
- *   fx::k_field_partial      rsqrt, the distance shared by an atom pair's
+ *   fx::k_field_wave, fx::k_field_sym,
+ *   fx::k_field_partial      8 per ordered inter-fragment shell pair (one
+ *                            rsqrt, the distance shared by an atom pair's
  *                            shells); the symmetric form evaluates each
  *                            unordered pair once and uses it both ways */
 #define FX_MAX_KSTAT 8
@@ -377,9 +383,9 @@ int fx_embedding_field(fx_ctx* ctx, const double* dq, double* phi);
 int fx_embedding_field_noalloc(fx_ctx* ctx, const double* d_dq, double* d_phi);
 
 /* Batched symmetric eigensolver used by the SCC, as the SCC runs it: the
- * LDS-resident Jacobi of a cold solve (working matrix in FP64 where it fits
- * in LDS, else FP32 with FP64 angles and eigenvectors), run to convergence,
- * then one warm iteration (A' = V A V^T rebuilt in FP64 on the matrix cores,
+ * passes of a cold solve (Jacobi sweeps on a working matrix in LDS, FP64 where
+ * it fits, else FP32 with FP64 angles and eigenvectors; the matrix rebuilt in
+ * FP64 between them), run to convergence, then one warm iteration (A' = V A V^T rebuilt in FP64 on the matrix cores,
  * the rotation kernel on the LDS working matrix, the apply kernel on V);
  * matrices smaller than 8 (no SCC system is) and sizes without an LDS plan
  * use a global-memory Jacobi.  nmat matrices of

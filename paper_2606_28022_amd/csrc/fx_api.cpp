@@ -1970,11 +1970,11 @@ int Ctx::solve_batch(Batch& b, bool cold, long long* iters_out) {
   return failed;
 }
 
-void Ctx::max_absdiff(const double* a, const double* b, int n, double* out, const double* extra, int nextra) {
+void Ctx::max_absdiff(const double* a, const double* b, int n, double* out) {
   const int np = std::max(1, std::min(64, (n + 2047) / 2048));
   if (red_part.n < 64LL * 36) red_part.alloc(64LL * 36);
   hipLaunchKernelGGL(k_absdiff_part, dim3(np), dim3(256), 0, stream, a, b, n, red_part.p);
-  hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(256), 0, stream, red_part.p, np, extra, nextra, out);
+  hipLaunchKernelGGL(k_max_reduce, dim3(1), dim3(256), 0, stream, red_part.p, np, out);
 }
 
 void Ctx::hist_coef(const double* R, long long n, const Slots& sl, double* coef) {

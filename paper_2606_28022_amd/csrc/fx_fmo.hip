@@ -44,26 +44,17 @@ __global__ void k_absdiff_part(const double* a, const double* b, int n, double* 
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// (with extra also its largest entry, into out[1])
-__global__ void k_max_reduce(const double* part, int np, const double* extra, int nextra, double* out) {
-  __shared__ double red[256], red2[256];
-  double m = 0.0, x = 0.0;
+__global__ void k_max_reduce(const double* part, int np, double* out) {
+  __shared__ double red[256];
+  double m = 0.0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) m = fmax(m, part[i]);
-  for (int i = threadIdx.x; i < nextra; i += blockDim.x) x = fmax(x, extra[i]);
   red[threadIdx.x] = m;
-  red2[threadIdx.x] = x;
   __syncthreads();
   for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-      red2[threadIdx.x] = fmax(red2[threadIdx.x], red2[threadIdx.x + w]);
-    }
+    if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    out[0] = red[0];
-    if (extra) out[1] = red2[0];
-  }
+  if (threadIdx.x == 0) out[0] = red[0];
 }
 
 // per cluster system: ddq (written per local shell), Delta E^V and Delta E_X

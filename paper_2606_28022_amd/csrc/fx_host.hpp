@@ -570,7 +570,7 @@ struct Ctx {
   // entry into out[1], and the Anderson mixing
   // coefficients of the history residuals R (slots sl, n entries each)
   DevBuf<double> red_part;
-  void max_absdiff(const double* a, const double* b, int n, double* out, const double* extra = nullptr, int nextra = 0);
+  void max_absdiff(const double* a, const double* b, int n, double* out);
   void hist_coef(const double* R, long long n, const Slots& sl, double* coef);
   // compensated sum of the arrays into *out (device)
   void sum_arrays(const SumArrays& a, double* out);

@@ -187,7 +187,7 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int e
 __global__ void k_gather_shell(DevBatch bt, const double* src_global, double* dst_local);
 __global__ void k_scatter_shell(DevBatch bt, const double* src_local, double* dst_global);
 __global__ void k_absdiff_part(const double* a, const double* b, int n, double* part);
-__global__ void k_max_reduce(const double* part, int np, const double* extra, int nextra, double* out);
+__global__ void k_max_reduce(const double* part, int np, double* out);
 __global__ void k_cluster_terms(DevBatch bt, const double* qmono, const double* e_mono, double* ddq, double* dEV,
                                 double* dE);
 // the arrays of one compensated sum

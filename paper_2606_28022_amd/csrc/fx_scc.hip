@@ -76,7 +76,7 @@ __device__ inline double block_max_waves(double v, double* red) {
 // (keep_err: the residual of the previous pass stays, so the eigensolver's
 // rotation threshold follows the outer iteration)
 // route: 0 the first iteration is an eigensolver's (a system taken off the
-// rotations stays off them), 1 also for those, 2 as the last solve left it
+// rotations stays off them), 1 also for those
 __global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err, int route) {
   int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nl) return;
@@ -86,8 +86,8 @@ __global__ void k_reset_state(DevBatch bt, const int* list, int nl, int keep_err
   bt.nhist[si] = 0;
   bt.e_prev[si] = 0.0;
   if (!keep_err) bt.err[si] = 1e-2;
-  if (route == 1 || (route == 0 && bt.mode[si] != 2)) bt.mode[si] = 0;
-  if (route != 2) bt.xn[si] = -1.0;
+  if (route == 1 || bt.mode[si] != 2) bt.mode[si] = 0;
+  bt.xn[si] = -1.0;
 }
 
 // clear the Anderson history of the listed systems
