@@ -579,6 +579,10 @@ struct Ctx {
   // (a wave per target atom): a host call on 288 atoms takes 53 us by it and 96
   // by the symmetric form, 3,456 atoms 85 and 101, 4,608 atoms 113 and 132,
   // 5,760 atoms 144 and 136
+  // Fewest atoms of the allocation-free field's pass over super-block pairs
+  // (kg = 2; tiles against k_field_partial: 6,000 atoms 0.157 and 0.107 ms,
+  // 9,000 0.168 and 0.195, 12,000 0.293 and 0.307, 30,000 1.07 and 1.59)
+  int field_tile_min = std::getenv("FX_FIELD_TILE_MIN") ? std::atoi(std::getenv("FX_FIELD_TILE_MIN")) : 9000;
   int field_wave_max = std::getenv("FX_FIELD_WAVE_MAX") ? std::atoi(std::getenv("FX_FIELD_WAVE_MAX")) : 5000;
   void build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters, int nfrag_each);
   void build_matrices(Batch& b, bool from_mono = false);

@@ -16,6 +16,9 @@ __global__ void k_build_system(DevSystem sys, DevBatch bt, const int* list, DevB
                                double* erep_part);
 __global__ void k_prim_table(const DevElem* elems, const int* present, int rows, double4* out);
 __global__ void k_erep_sum(DevBatch bt, int nsys, int slices, const double* erep_part);
+constexpr int FT_BLOCKS = 8;  // 64-atom blocks per super-block of k_field_tile
+__global__ void k_field_tile(DevSystem sys, const double* q, int nsb, int t0, double* part);
+__global__ void k_field_tile_reduce(DevSystem sys, int nsb, int t0, int t1, int first, const double* part, double* phi);
 __global__ void k_field_partial(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_partial_f32(DevSystem sys, const double* q, int nchunk, double* part);
 __global__ void k_field_wave(DevSystem sys, const double* q, double* phi);

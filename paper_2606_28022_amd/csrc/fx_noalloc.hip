@@ -1,7 +1,8 @@
 // Embedding field for callers that cannot allocate device memory.
 //
-// The chunked field pass (k_field_partial, k_field_reduce) needs partial sums
-// of nchunk x n_shells doubles.  Here they live in a file-scope device array
+// The field passes need partial sums (k_field_partial nchunk x n_shells
+// doubles, k_field_tile 2,048 per super-block pair).  Here they live in a
+// file-scope device array
 // of FX_NOALLOC_SCRATCH_DOUBLES doubles, held by every GPU the library runs
 // on until the process ends.  Host code never passes the array's own name to
 // a kernel (on the host it is only a stand-in symbol): init_device looks up
@@ -57,6 +58,22 @@ void Ctx::field_noalloc(const double* d_q, double* d_phi) {
     return;
   }
   double* part = noalloc_scratch(device);
+  const long long nsb = (Ne + 64 * FT_BLOCKS - 1) / (64 * FT_BLOCKS), pairs = nsb * (nsb + 1) / 2;
+  if (P.g.kg == 2.0 && Ne >= field_tile_min && pairs <= 0x3fffffffLL) {
+    // every pair of atoms once, as many super-block pairs per launch as the
+    // scratch holds (512: two per CU; a last launch of one per CU is faster
+    // than the same number in each)
+    const long long per = FX_NOALLOC_SCRATCH_DOUBLES / (4 * 64 * FT_BLOCKS);
+    for (long long t0 = 0; t0 < pairs; t0 += per) {
+      const int t1 = (int)std::min(pairs, t0 + per);
+      hipLaunchKernelGGL(k_field_tile, dim3((unsigned)(t1 - t0)), dim3(64 * FT_BLOCKS), 0, stream, dev_system(), d_q,
+                         (int)nsb, (int)t0, part);
+      hipLaunchKernelGGL(k_field_tile_reduce, dim3((Ne + 255) / 256), dim3(256), 0, stream, dev_system(), (int)nsb,
+                         (int)t0, t1, t0 == 0 ? 1 : 0, (const double*)part, d_phi);
+    }
+    check(hipGetLastError(), "field (no allocation)");
+    return;
+  }
   // as many source chunks as the scratch holds, at most those of the
   // allocating pass
   const int by_grid = std::max(1, std::min(64, (Ne + 255) / 256 > 0 ? 2048 / ((Ne + 255) / 256) : 1));
