@@ -51,7 +51,14 @@ void Ctx::field_noalloc(const double* d_q, double* d_phi) {
   if (Nsh > FX_NOALLOC_SCRATCH_DOUBLES)
     throw FxError(FX_E_INVALID, "system has " + std::to_string(Nsh) + " shells; the allocation-free field pass "
                                 "handles at most " + std::to_string((long long)FX_NOALLOC_SCRATCH_DOUBLES));
-  if (Ne <= field_wave_max && P.g.kg == 2.0) {
+  // Charges and result may be the same buffer or overlap: then only the
+  // chunked pass serves, which has read every charge before it writes a result
+  // (k_field_wave writes while other work-groups still read, k_field_tile's
+  // second launch would read the first one's results).
+  const uintptr_t q0 = reinterpret_cast<uintptr_t>(d_q), phi0 = reinterpret_cast<uintptr_t>(d_phi);
+  const uintptr_t bytes = sizeof(double) * (uintptr_t)Nsh;
+  const bool apart = q0 + bytes <= phi0 || phi0 + bytes <= q0;
+  if (apart && Ne <= field_wave_max && P.g.kg == 2.0) {
     // small systems: the one-launch form, which has no partial sums
     hipLaunchKernelGGL(k_field_wave, dim3((Ne + 3) / 4), dim3(256), 0, stream, dev_system(), d_q, d_phi);
     check(hipGetLastError(), "field (no allocation)");
@@ -59,7 +66,7 @@ void Ctx::field_noalloc(const double* d_q, double* d_phi) {
   }
   double* part = noalloc_scratch(device);
   const long long nsb = (Ne + 64 * FT_BLOCKS - 1) / (64 * FT_BLOCKS), pairs = nsb * (nsb + 1) / 2;
-  if (P.g.kg == 2.0 && Ne >= field_tile_min && pairs <= 0x3fffffffLL) {
+  if (apart && P.g.kg == 2.0 && Ne >= field_tile_min && pairs <= 0x3fffffffLL) {
     // every pair of atoms once, as many super-block pairs per launch as the
     // scratch holds (512: two per CU; a last launch of one per CU is faster
     // than the same number in each)
