@@ -1211,11 +1211,11 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     const double beta = b.has_pre ? precond_beta : mix_beta;
     if (n32 > 0)
       hipLaunchKernelGGL(k_charges_mix, dim3(n32), dim3(256), 0, stream, ds, db, dl, 1, -1.0, -1.0,
-                         single ? 1 : opt.max_iter, beta, (const double*)nullptr, 0);
+                         single ? 1 : opt.max_iter, beta, (const double*)nullptr, 0, ov_lim);
     if (n64 > 0)
       hipLaunchKernelGGL(k_charges_mix, dim3(n64), dim3(256), 0, stream, ds, db, dl64, some_eig ? 1 : 0,
                          scc_tol_cur > 0 ? scc_tol_cur : opt.scc_tol, etol_cur > 0 ? etol_cur : opt.energy_tol,
-                         single ? 1 : opt.max_iter, beta, sums ? (const double*)b.pop_part.p : nullptr, b.pop_stride);
+                         single ? 1 : opt.max_iter, beta, sums ? (const double*)b.pop_part.p : nullptr, b.pop_stride, ov_lim);
     check(hipGetLastError(), "scc iteration");
   };
   // FX_BATCHED_GRAPH: after the first (eager) iteration, the iteration over
@@ -1659,7 +1659,7 @@ void Ctx::launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na) {
   auto* apply = wide ? k_ov_apply<2, 2> : b.max_ovb <= 2 * OV_WAVES ? k_ov_apply<1, 2> : k_ov_apply<1, 3>;
   hipLaunchKernelGGL(apply, dim3((unsigned)xcd_grid(na, ta)), dim3(64 * OV_WAVES),
                      ov_apply_lds_bytes(b.max_nao, wide ? 2 : 1), stream, db, dl, na, ta, (const double*)b.Pm.p,
-                     (const double*)b.xpart.p);
+                     (const double*)b.xpart.p, ov_lim.x);
   if (timed) timers.end(stream, ev, kt("fx::k_ov_apply"), 0.0);
   check(hipGetLastError(), "orbital rotation");
 }
@@ -1829,7 +1829,7 @@ Ctx::RotShape Ctx::rot_shape(Batch& b, const DevBatch& db, const int* dl, int na
 }
 
 double* Ctx::step_target() {
-  if (!step_host) check(hipHostMalloc((void**)&step_host, 2 * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+  if (!step_host) check(hipHostMalloc((void**)&step_host, STEP_MAXIMA * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
   if (!step_ev) check(hipEventCreateWithFlags(&step_ev, hipEventDisableTiming), "hipEventCreate");
   return step_host;
 }
@@ -1838,8 +1838,7 @@ void Ctx::step_mark() { check(hipEventRecord(step_ev, stream), "hipEventRecord")
 
 void Ctx::step_wait(double* maxima) {
   check(hipEventSynchronize(step_ev), "hipEventSynchronize");
-  maxima[0] = step_host[0];
-  maxima[1] = step_host[1];
+  std::copy(step_host, step_host + STEP_MAXIMA, maxima);
 }
 
 // ---------------------------------------------------------------------------
@@ -2430,7 +2429,7 @@ void Ctx::run(fx_result* out) {
   DevBuf<double> hG;  // Gram matrix of the fused steps' residuals, by slot
   hG.alloc(HIST * HIST);
   step_part.alloc((long long)HIST * mb.nsys);
-  step_max.alloc(2);
+  step_max.alloc(STEP_MAXIMA);
   std::vector<int> slots;
   int next_slot = 0;
   const unsigned gN = (unsigned)((Nsh + 255) / 256);
@@ -2495,19 +2494,13 @@ void Ctx::run(fx_result* out) {
       field_queued = !field32 && field_is_wave();
       if (field_queued) field(d_q.p, d_phi.p);
       const bool ov = ov_batch(mb);
-      double mx[2];
+      double mx[STEP_MAXIMA];
       step_wait(mx);
       delta = mx[0];
       if (ov) {
         // a rotation leaves the orbitals up to a fifth of |X| behind
         if (!(0.2 * mx[1] <= delta)) delta = 0.2 * mx[1];
-        if (mono_eig) {
-          std::vector<int> modes;
-          fetch(mb.mode, modes);
-          mono_eig = std::any_of(modes.begin(), modes.end(), [](int m) { return m != 1; });
-        } else {
-          mono_eig = mx[1] > OV_XMAX;
-        }
+        mono_eig = mx[2] != 0.0;  // (the device's own account: it decides who rotates)
       }
       refresh = false;
       if (verbose)

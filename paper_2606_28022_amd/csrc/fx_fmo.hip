@@ -296,7 +296,8 @@ __global__ void __launch_bounds__(64) k_mono_begin(DevBatch bt, const double* q,
       bt.mode[si] = 0;
       bt.xn[si] = -1.0;
     }
-    if (si == 0) maxima[0] = maxima[1] = 0ULL;
+    if (si == 0)
+      for (int k = 0; k < STEP_MAXIMA; ++k) maxima[k] = 0ULL;
   }
 }
 
@@ -330,7 +331,8 @@ __device__ inline void max_into(unsigned long long* m, double v) {
 }
 
 // end of a fused monomer step, per monomer (one wave): its charges into q_new,
-// max |q_out - q_in| and max |X| (DevBatch), and the history row of the
+// max |q_out - q_in|, max |X| (DevBatch) and whether it rotates next, and the
+// history row of the
 // Newton step (1 + M G)^-1 (q_out - q_in) (bt.pre, stored transposed)
 __global__ void __launch_bounds__(64) k_mono_end(DevBatch bt, double* q_new, double* X, double* R, long long n, Slots sl,
                                                  double* part, unsigned long long* maxima) {
@@ -364,6 +366,7 @@ __global__ void __launch_bounds__(64) k_mono_end(DevBatch bt, double* q_new, dou
   if (lane == 0) {
     max_into(maxima, nan ? __longlong_as_double(0x7ff8000000000000LL) : dm);
     max_into(maxima + 1, fmax(bt.xn[si], 0.0));
+    max_into(maxima + 2, bt.mode[si] == 1 ? 0.0 : 1.0);
   }
 }
 
@@ -390,7 +393,7 @@ __global__ void __launch_bounds__(64) k_resp_sweep(DevBatch bt, const double* R,
     for (int t = 0; t < ns; ++t) v += M[d.gam_off + (long long)t * ns + s] * ws[t];  // (M is symmetric)
     u[bt.sys_sh_global[d.sh_off + s]] = -v;
   }
-  if (si == 0 && threadIdx.x == 0) maxima[0] = maxima[1] = 0ULL;
+  if (si == 0 && threadIdx.x < STEP_MAXIMA) maxima[threadIdx.x] = 0ULL;
 }
 
 // its end, per monomer: y_new = v + field of u, max |y_new - y|, history row
@@ -426,7 +429,7 @@ __global__ void __launch_bounds__(256) k_hist_next(const double* X, const double
                                                    const double* part, int nparts, double* gram, double beta,
                                                    double* q, const double* maxima, double* host_maxima) {
   const int m = sl.m, M = m + 1, W = M + 1, t = threadIdx.x;
-  if (blockIdx.x == 0 && t < 2) host_maxima[t] = maxima[t];  // (pinned: the step's residual for the host)
+  if (blockIdx.x == 0 && t < STEP_MAXIMA) host_maxima[t] = maxima[t];  // (pinned: the step's residual for the host)
   __shared__ double sum[32][HIST], row[HIST], B[(HIST + 1) * (HIST + 2)], f[HIST + 1], coef[HIST];
   {
     const int k = t & (HIST - 1);

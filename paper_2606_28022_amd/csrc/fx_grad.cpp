@@ -392,7 +392,7 @@ void Ctx::gradient() {
       check(hipGetLastError(), "response sweep");
       step_mark();
       sweep(yg.p);  // the next one's, while the host wakes
-      double mx[2];
+      double mx[STEP_MAXIMA];
       step_wait(mx);
       delta = mx[0];
       if (verbose) std::fprintf(stderr, "[fx] response sweep %d: max |dy| = %.3e\n", it, delta);

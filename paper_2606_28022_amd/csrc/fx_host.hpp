@@ -633,6 +633,10 @@ struct Ctx {
   // launches; up to 256 AOs by the kernels' LDS and register tiles.
   bool ov_on = !(std::getenv("FX_OV") && std::atoi(std::getenv("FX_OV")) == 0);
   bool ov_batch(const Batch& b) const { return ov_on && !b.has_hop && b.max_nao > 32 && b.max_nao <= OV_MAXN; }
+  // limits of the route (FX_OV_XMAX, FX_OV_ERRMAX: narrower ones make a test's
+  // systems leave it)
+  OvLimits ov_lim{std::getenv("FX_OV_XMAX") ? std::min(OV_XMAX, std::atof(std::getenv("FX_OV_XMAX"))) : OV_XMAX,
+                  std::getenv("FX_OV_ERRMAX") ? std::min(OV_ERRMAX, std::atof(std::getenv("FX_OV_ERRMAX"))) : OV_ERRMAX};
   // monomer loop: whether some monomer's next iteration is an eigensolver's
   bool mono_eig = true;
   void launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na);
@@ -710,7 +714,7 @@ struct Ctx {
   std::vector<hipEvent_t> cnt_ev;
   void count_ring_init();
   // maxima of a step of the iterations over the whole charge vector
-  // (k_mono_end, k_resp_end): device pair, pinned copy (written by
+  // (k_mono_end, k_resp_end): on the device, pinned copy (written by
   // k_hist_next)
   DevBuf<unsigned long long> step_max;
   double* step_host = nullptr;

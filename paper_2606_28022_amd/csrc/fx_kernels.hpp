@@ -87,6 +87,10 @@ __global__ void k_scc_small(DevSystem sys, DevBatch bt, const int* list, SmallSc
 // residuals near 1, did not settle for up to 62 iterations by rotations)
 constexpr int OV_MAXN = 256, OV_ROWS = 32, OV_WAVES = 8;
 constexpr double OV_XMAX = 0.1, OV_ERRMAX = 0.1;
+// (these two as the context holds them: a test can narrow them)
+struct OvLimits {
+  double x, err;
+};
 __host__ __device__ inline unsigned ov_grad_lds_bytes(int n) { return 8u * 2u * 16u * (((unsigned)n + 15u) & ~15u); }
 // (both classes padded to 16: at most 30 rows more than n)
 __host__ __device__ inline unsigned ov_apply_lds_bytes(int n, int cb) {
@@ -95,7 +99,7 @@ __host__ __device__ inline unsigned ov_apply_lds_bytes(int n, int cb) {
 __global__ void k_ov_grad(DevBatch bt, const int* list, int nl, int tiles_per_sys, double* Xpool, double* xpart);
 template <int CB, int BLK>
 __global__ void k_ov_apply(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* Xpool,
-                           const double* xpart);
+                           const double* xpart, double xmax);
 __global__ void k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened);
 __global__ void k_jacobi(DevBatch bt, const int* list, int max_sweeps, double rel_tol, double thr_scale,
                          double cap_err, int* sweeps_out);
@@ -184,7 +188,7 @@ __global__ void k_eigh_batched(const int* nvec, const long long* off, double* Ab
                                const long long* woff, int max_sweeps, double rel_tol);
 __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate);
 __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol, int max_iter,
-                              double beta, const double* parts, int pstride);
+                              double beta, const double* parts, int pstride, OvLimits lim);
 
 // FMO assembly (fx_fmo.hip)
 __global__ void k_gather_shell(DevBatch bt, const double* src_global, double* dst_local);
@@ -205,7 +209,10 @@ __global__ void k_hist_gram_part(const double* R, long long n, Slots sl, double*
 __global__ void k_hist_solve(const double* part, int np, Slots sl, double* coef);
 __global__ void k_hist_mix(const double* X, const double* R, long long n, Slots sl, const double* coef, double beta,
                            double* q);
-// the iterations over the whole charge vector in few launches
+// the iterations over the whole charge vector in few launches; a step's maxima:
+// largest change of a charge, largest |X| (DevBatch), 1 where some system is
+// not in rotation mode
+constexpr int STEP_MAXIMA = 3;
 __global__ void k_mono_begin(DevBatch bt, const double* q, const double* phi, int refresh, unsigned long long* maxima);
 __global__ void k_mono_end(DevBatch bt, double* q_new, double* X, double* R, long long n, Slots sl, double* part,
                            unsigned long long* maxima);

@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(64 * OV_WAVES)
 template <int CB, int BLK>
 __global__ void __launch_bounds__(64 * OV_WAVES) __attribute__((amdgpu_waves_per_eu(4)))
     k_ov_apply(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* __restrict__ Xpool,
-               const double* xpart) {
+               const double* xpart, double xmax) {
   extern __shared__ double ov_lds[];
   int sl, tile;
   xcd_slot_tile(blockIdx.x, tiles_per_sys, sl, tile);
@@ -267,12 +267,12 @@ __global__ void __launch_bounds__(64 * OV_WAVES) __attribute__((amdgpu_waves_per
   const int i = lane & 15, g = lane >> 4;
   const double* X = Xpool + d.mat_off;
   const int nob = nop >> 4;
-  // |X| and, where it exceeds OV_XMAX (the couplings are too large for this
+  // |X| and, where it exceeds xmax (the couplings are too large for this
   // route; the mixer sends the system back to the eigensolver), a shorter step
   double x2 = 0.0;
   for (int t = 0; t * OV_ROWS < no; ++t) x2 += xpart[16 * si + t];
   const double xn = sqrt(x2);
-  const double sc = xn > OV_XMAX ? OV_XMAX / xn : 1.0;
+  const double sc = xn > xmax ? xmax / xn : 1.0;
   const double xk = xn * sc;
   if (tile == 0 && threadIdx.x == 0) bt.xn[si] = xn;
   // products with K: the first term of U^T U left out stays below 1e-15 (7:
@@ -368,9 +368,9 @@ __global__ void __launch_bounds__(64 * OV_WAVES) __attribute__((amdgpu_waves_per
   }
 }
 
-template __global__ void k_ov_apply<1, 2>(DevBatch, const int*, int, int, const double*, const double*);
-template __global__ void k_ov_apply<1, 3>(DevBatch, const int*, int, int, const double*, const double*);
-template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const double*, const double*);
+template __global__ void k_ov_apply<1, 2>(DevBatch, const int*, int, int, const double*, const double*, double);
+template __global__ void k_ov_apply<1, 3>(DevBatch, const int*, int, int, const double*, const double*, double);
+template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const double*, const double*, double);
 
 // After a solve: the gap of the systems that converged in a rotation from the
 // expectation values C_i^T F C_i of the orbitals whose last eigenvalue lies

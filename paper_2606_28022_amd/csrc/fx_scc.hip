@@ -1268,7 +1268,7 @@ __global__ void k_fermi(DevSystem sys, DevBatch bt, const int* list, int rotate)
 // (k_gemm_mfma<2, 2>, pstride doubles per system), or null: from P itself
 // (systems of up to 32 AOs, FP32 iterations).
 __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int eig, double tol, double etol,
-                              int max_iter, double beta, const double* parts, int pstride) {
+                              int max_iter, double beta, const double* parts, int pstride, OvLimits lim) {
   int si = list[blockIdx.x];
   if (bt.status[si] != 0 || (!eig && bt.mode[si] != 1)) return;
   const SysDesc d = bt.desc[si];
@@ -1401,7 +1401,7 @@ __global__ void k_charges_mix(DevSystem sys, DevBatch bt, const int* list, int e
   bool conv = (err < tol) && (de < etol) && (it > 1) && (xn < 5.0 * tol);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (bt.mode[si] == 1 && (xn > OV_XMAX || err > OV_ERRMAX)) bt.mode[si] = 0;
+    if (bt.mode[si] == 1 && (xn > lim.x || err > lim.err)) bt.mode[si] = 0;
     bt.e_int[si] = e;
     bt.e_prev[si] = e;
     bt.err[si] = err;
