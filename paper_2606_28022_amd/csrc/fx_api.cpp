@@ -2499,7 +2499,7 @@ void Ctx::run(fx_result* out) {
       delta = mx[0];
       if (ov) {
         // a rotation leaves the orbitals up to a fifth of |X| behind
-        if (!(0.2 * mx[1] <= delta)) delta = 0.2 * mx[1];
+        if (!(0.2 * mx[1] <= delta) && delta == delta) delta = 0.2 * mx[1];  // (a NaN in either stays)
         mono_eig = mx[2] != 0.0;  // (the device's own account: it decides who rotates)
       }
       refresh = false;

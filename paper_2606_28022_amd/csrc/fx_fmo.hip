@@ -365,7 +365,8 @@ __global__ void __launch_bounds__(64) k_mono_end(DevBatch bt, double* q_new, dou
   hist_row(bt, d, si, X, R, n, sl, qi, v, part);
   if (lane == 0) {
     max_into(maxima, nan ? __longlong_as_double(0x7ff8000000000000LL) : dm);
-    max_into(maxima + 1, fmax(bt.xn[si], 0.0));
+    const double xn = bt.xn[si];
+    max_into(maxima + 1, xn < 0.0 ? 0.0 : xn);  // (a NaN goes on as one)
     max_into(maxima + 2, bt.mode[si] == 1 ? 0.0 : 1.0);
   }
 }
