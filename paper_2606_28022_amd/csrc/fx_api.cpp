@@ -744,7 +744,7 @@ void Ctx::learned_guess() {
   mlp_features(mlp_feat.p);
   mlp_infer(mlp_feat.p, mlp_out.p, N);
   DevBuf<int> fc;
-  fc.upload(frag_charge);
+  put(fc, frag_charge);
   hipLaunchKernelGGL(k_guess_assemble, dim3((Ne + 255) / 256), dim3(256), 0, stream, dev_system(), mlp_out.p, d_q.p);
   hipLaunchKernelGGL(k_guess_project, dim3(F), dim3(256), 0, stream, dev_system(), d_frag_atoms.p, d_frag_off.p,
                      fc.p, d_q.p);
@@ -894,10 +894,10 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
   const JacobiPlan jp = global_kernel ? JacobiPlan{} : jacobi_plan(b.max_nao, false, false);
   if (jp.elt == 0) {
     DevBuf<int> dn;
-    dn.upload(nv);
+    put(dn, nv);
     DevBuf<long long> doff, dwoff;
-    doff.upload(off);
-    dwoff.upload(woff);
+    put(doff, off);
+    put(dwoff, woff);
     hipLaunchKernelGGL(k_eigh_batched, dim3(nmat), dim3(256), 0, stream, dn.p, doff.p, b.Fm.p, b.Ct.p, b.eps.p,
                        dwoff.p, 60, 1e-15);
     check(hipGetLastError(), "k_eigh_batched");
@@ -1361,7 +1361,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     put(d_act, active);
     const int na = (int)active.size();
     if (!switched.empty()) {
-      d_switched.upload(switched);
+      put(d_switched, switched);
       hipLaunchKernelGGL(k_hist_reset, dim3(((int)switched.size() + 255) / 256), dim3(256), 0, stream, db,
                          (const int*)d_switched.p, (int)switched.size());
       switched.clear();
@@ -1725,7 +1725,7 @@ bool Ctx::canonical_basis(Batch& b) {
       mode[s] = 2;
       gapped = false;
     }
-  if (!gapped) b.mode.upload(mode);
+  if (!gapped) put(b.mode, mode);
   return gapped;
 }
 
@@ -2288,6 +2288,7 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
   d_qnew.alloc(Nsh);
   d_phi.alloc(Nsh);
   d_scalar.alloc(8);
+  sync();  // (the tables are in place when the call returns; one wait for all)
   guess.assign(Nsh, 0.0);
   warm_valid = false;
   has_system = true;
@@ -2296,9 +2297,10 @@ void Ctx::set_system(int32_t n_atoms, const int32_t* Z, const double* xyz, int32
   has_grad = false;
 }
 
-// New positions for the current system (same atoms, fragments and bonds):
-// every geometry-derived table is rebuilt as by set_system; the starting
-// charges of FX_GUESS_USER are kept.
+// New positions for the current system (same atoms, fragments and bonds): only
+// the coordinates are replaced, here and, with the lists, matrices and CN that
+// follow from them, in the next run; the starting charges of FX_GUESS_USER are
+// kept.
 void Ctx::set_coordinates(const double* xyz) {
   if (!has_system) throw FxError(FX_E_STATE, "no system set");
   if (!xyz) throw FxError(FX_E_INVALID, "null coordinates");
@@ -2314,6 +2316,7 @@ void Ctx::set_coordinates(const double* xyz) {
   Transfer up(*this, false);
   up.put(d_xyz, xyz_h);
   up.flush();
+  sync();  // (in place when the call returns)
   has_system = true;
   lists_built = false;
   has_result = false;

@@ -347,6 +347,9 @@ struct JacobiPlan {
 
 struct Ctx {
   ~Ctx() {
+    // (queued work, of fx_embedding_field_noalloc or of a call that failed on
+    // the way, still uses the buffers, which may be a caller's workspace)
+    (void)hipStreamSynchronize(stream);
     if (gstream) (void)hipStreamDestroy(gstream);
     for (hipEvent_t e : cnt_ev)
       if (e) (void)hipEventDestroy(e);
