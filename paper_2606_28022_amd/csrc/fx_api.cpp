@@ -1232,6 +1232,10 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   const bool async = opt.schedule == FX_BATCHED && !single && !f32_ok && !verbose && split_ok;
   int ub = nl;
   int neig = 1;  // systems that the eigensolver takes next, by the latest count
+  // launches without the eigensolver: a system taken off the rotations since
+  // that count waits in them, so each may add one to the launches that
+  // max_iter iterations of every system take (the loop ends with the counts)
+  int idle = 0;
   std::deque<int> pending;
   const std::vector<int> no_list;
   if (async) {
@@ -1273,7 +1277,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     if (iters_out) *iters_out += nl;
     return 0;
   }
-  for (int it = 0; it < max_it && !active.empty(); ++it) {
+  for (int it = 0; it < max_it + idle && !active.empty(); ++it) {
     const double cap = (cold && it == 0 && !b.init_from_mono) ? 1e300 : jacobi_cap_err;
     if (graph_mode && it >= 1) {
       if (!gexec) {
@@ -1304,7 +1308,9 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     }
     if (async) {
       if (want_tune(it)) tune_fused(d_act.p, ub, cap);
-      launch_iteration(no_list, d_act.p, ub, 0, cap, true, it == 0, it == 0 || neig != 0);
+      const bool some_eig = it == 0 || neig != 0;
+      launch_iteration(no_list, d_act.p, ub, 0, cap, true, it == 0, some_eig);
+      idle += some_eig ? 0 : 1;
       if (first_solve && it == 0) {
         // median first-iteration residual over the batch (all listed systems
         // took part in iteration 0)
@@ -1316,9 +1322,10 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         res.first_residual_median = v[v.size() / 2];
       }
       if (first_solve && opt.guess == FX_GUESS_LEARNED &&
-          ((it == 0 && opt.guess_tau > 0) || (opt.guess_max_iter > 0 && it + 1 == opt.guess_max_iter))) {
+          ((it == 0 && opt.guess_tau > 0) ||
+           (opt.guess_max_iter > 1 && it + 1 >= opt.guess_max_iter && it + 1 <= opt.guess_max_iter + idle))) {
         hipLaunchKernelGGL(k_guess_fallback, dim3(ub), dim3(64), 0, stream, db, d_act.p, ub, it == 0 ? 0 : 1,
-                           opt.guess_tau, fallback_flag.p);
+                           opt.guess_tau, opt.guess_max_iter, fallback_flag.p);
         check(hipGetLastError(), "k_guess_fallback");
       }
       const int slot = it % CNT_RING;
@@ -1384,7 +1391,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     if (first_solve && opt.guess == FX_GUESS_LEARNED &&
         ((it == 0 && opt.guess_tau > 0) || (opt.guess_max_iter > 0 && it + 1 == opt.guess_max_iter))) {
       hipLaunchKernelGGL(k_guess_fallback, dim3(na), dim3(64), 0, stream, db, d_act.p, na, it == 0 ? 0 : 1,
-                         opt.guess_tau, fallback_flag.p);
+                         opt.guess_tau, opt.guess_max_iter, fallback_flag.p);
       check(hipGetLastError(), "k_guess_fallback");
     }
     std::vector<double> errs;
@@ -1557,7 +1564,7 @@ int Ctx::run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::
     res.first_residual_median = v[v.size() / 2];
     auto fallback = [&](int phase) {
       hipLaunchKernelGGL(k_guess_fallback, dim3(nl), dim3(64), 0, stream, db, lst, nl, phase, opt.guess_tau,
-                         fallback_flag.p);
+                         opt.guess_max_iter, fallback_flag.p);
       check(hipGetLastError(), "k_guess_fallback");
     };
     if (opt.guess == FX_GUESS_LEARNED) {

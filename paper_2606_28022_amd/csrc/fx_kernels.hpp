@@ -299,5 +299,5 @@ __global__ void k_mlp_round(const float* master, float* wr);
 __global__ void k_guess_assemble(DevSystem sys, const float* Y, double* q);
 __global__ void k_guess_project(DevSystem sys, const int* frag_atoms, const int* frag_off, const int* frag_charge,
                                 double* q);
-__global__ void k_guess_fallback(DevBatch bt, const int* list, int nl, int phase, double tau, int* flag);
+__global__ void k_guess_fallback(DevBatch bt, const int* list, int nl, int phase, double tau, int after, int* flag);
 }  // namespace fx

@@ -316,12 +316,14 @@ __global__ void k_guess_project(DevSystem sys, const int* frag_atoms, const int*
 
 // restart from superposition charges: phase 0 after the first iteration for
 // systems whose residual exceeds tau, phase 1 for systems still unconverged
-__global__ void k_guess_fallback(DevBatch bt, const int* list, int nl, int phase, double tau, int* flag) {
+// after `after` iterations of their own (a launch may leave a system waiting
+// for the eigensolver; a second reset of one that waits changes nothing)
+__global__ void k_guess_fallback(DevBatch bt, const int* list, int nl, int phase, double tau, int after, int* flag) {
   const int k = blockIdx.x;
   if (k >= nl) return;
   const int si = list[k];
   const SysDesc d = bt.desc[si];
-  const bool reset = phase == 0 ? (tau > 0.0 && bt.err[si] > tau) : (bt.status[si] == 0);
+  const bool reset = phase == 0 ? (tau > 0.0 && bt.err[si] > tau) : (bt.status[si] == 0 && bt.niter[si] == after);
   if (!reset) return;
   for (int s = threadIdx.x; s < d.nsh; s += blockDim.x) bt.q_in[d.sh_off + s] = 0.0;
   if (threadIdx.x == 0) {
