@@ -110,7 +110,7 @@ typedef struct fx_options {
                              superposition charges (<= 0: never) */
   int32_t guess_max_iter; /* learned guess: a monomer not converged after this
                              many iterations of its first solve restarts from
-                             superposition charges (<= 0: never) */
+                             superposition charges (<= 1: never) */
   double scc_tol;         /* SCC convergence: max |dq_out - dq_in| */
   double energy_tol;      /* SCC convergence: |E_k - E_(k-1)| */
   double macro_tol;       /* monomer loop: max change of any monomer charge */

@@ -1569,7 +1569,6 @@ int Ctx::run_scc_small(Batch& b, const DevBatch& db, const int* lst, const std::
     };
     if (opt.guess == FX_GUESS_LEARNED) {
       if (opt.guess_tau > 0) fallback(0);
-      if (opt.guess_max_iter == 1) fallback(1);
       if (opt.guess_max_iter > 1 && opt.guess_max_iter - 1 < left) {
         launch(opt.guess_max_iter - 1);
         left -= opt.guess_max_iter - 1;
