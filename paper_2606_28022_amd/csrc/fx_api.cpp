@@ -1032,6 +1032,19 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       hipLaunchKernelGGL(k_ns_poly, dim3(8, nl), dim3(256), 0, stream, db, lst, b.Fm.p, b.Pm.p);
       gemm_batch(b, db, nl, lst, 0, b.Fm.p, b.Tm.p, b.Ct.p, (const double*)nullptr, gf);
     };
+    // the listed systems' C^T from a scratch pool (the others keep theirs: one
+    // system at a time, they are the solved ones)
+    auto basis_from = [&](const double* pool) {
+      if (nl == b.nsys) {
+        check(hipMemcpyAsync(b.Ct.p, pool, sizeof(double) * b.tot_mat, hipMemcpyDeviceToDevice, stream), "copy");
+        return;
+      }
+      for (int s : list) {
+        const SysDesc& sd = b.h_desc[s];
+        check(hipMemcpyAsync(b.Ct.p + sd.mat_off, pool + sd.mat_off, sizeof(double) * sd.nao * sd.nao,
+                             hipMemcpyDeviceToDevice, stream), "copy");
+      }
+    };
     if (b.init_from_mono && mb.nsys > 0) {
       // C0 = blockdiag(monomer C); G = C0^T S C0 = L L^T; C = C0 L^-T
       hipLaunchKernelGGL(k_cluster_init_ct, dim3(nl), dim3(256), 0, stream, db, lst, mb.dev(),
@@ -1059,7 +1072,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
       if (chol_elt == 0) {
         cholinv(b.Fm.p, b.Tm.p);  // (k_cholinv uses Pm as its workspace)
         gemm_batch(b, db, nl, lst, 0, b.Tm.p, b.Ct.p, b.Fm.p, (const double*)nullptr, gf);
-        check(hipMemcpyAsync(b.Ct.p, b.Fm.p, sizeof(double) * b.tot_mat, hipMemcpyDeviceToDevice, stream), "copy");
+        basis_from(b.Fm.p);
       } else {
         if (block2) {
           const int ev = capturing ? -1 : timers.begin(stream);
@@ -1078,8 +1091,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
         if (chol_elt == 4)
           refine_rows();
         else
-          check(hipMemcpyAsync(b.Ct.p, b.Tm.p, sizeof(double) * b.tot_mat, hipMemcpyDeviceToDevice, stream),
-                "copy");
+          basis_from(b.Tm.p);
       }
     } else if (chol_elt == 4) {
       cholinv(b.S.p, b.Tm.p);
