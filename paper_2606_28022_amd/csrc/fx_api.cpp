@@ -1462,7 +1462,8 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   std::vector<int> open(1, 0), modes;
   if (ov && !single) {
     put(d_open, open);
-    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(1024), 0, stream, db, (const int*)lst, P.g.kT, d_open.p);
+    hipLaunchKernelGGL(k_ov_gap, dim3(nl), dim3(1024), 0, stream, db, (const int*)lst, P.g.kT, ov_occ,
+                       d_open.p);
     check(hipGetLastError(), "k_ov_gap");
   }
   {
@@ -1525,7 +1526,13 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   }
   if (iters_out) *iters_out += iters;
   // (systems whose gap closed on the way: the eigensolver from here on)
-  if (!again.empty()) failed += run_scc(b, again, false, iters_out);
+  if (!again.empty()) {
+    if (verbose) std::fprintf(stderr, "[fx] %d of %d systems reopened: gap closed\n", (int)again.size(), nl);
+    const bool first = first_solve;
+    first_solve = false;  // (its residuals and its fallback are behind)
+    failed += run_scc(b, again, false, iters_out);
+    first_solve = first;
+  }
   return single ? 0 : failed;
 }
 
@@ -1744,6 +1751,7 @@ bool Ctx::canonical_basis(Batch& b) {
       gapped = false;
     }
   if (!gapped) put(b.mode, mode);
+  if (!gapped && verbose) std::fprintf(stderr, "[fx] monomers reopened: gap closed\n");
   return gapped;
 }
 

@@ -640,6 +640,9 @@ struct Ctx {
   // systems leave it)
   OvLimits ov_lim{std::getenv("FX_OV_XMAX") ? std::min(OV_XMAX, std::atof(std::getenv("FX_OV_XMAX"))) : OV_XMAX,
                   std::getenv("FX_OV_ERRMAX") ? std::min(OV_ERRMAX, std::atof(std::getenv("FX_OV_ERRMAX"))) : OV_ERRMAX};
+  // largest occupation above and hole below the gap, over 2, at the end of a
+  // rotated solve (FX_OV_OCC: a smaller one reopens systems for a test)
+  double ov_occ = std::getenv("FX_OV_OCC") ? std::min(1e-10, std::atof(std::getenv("FX_OV_OCC"))) : 1e-10;
   // monomer loop: whether some monomer's next iteration is an eigensolver's
   bool mono_eig = true;
   void launch_ov(const Batch& b, const DevBatch& db, const int* dl, int na);

@@ -100,7 +100,7 @@ __global__ void k_ov_grad(DevBatch bt, const int* list, int nl, int tiles_per_sy
 template <int CB, int BLK>
 __global__ void k_ov_apply(DevBatch bt, const int* list, int nl, int tiles_per_sys, const double* Xpool,
                            const double* xpart, double xmax);
-__global__ void k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened);
+__global__ void k_ov_gap(DevBatch bt, const int* list, double kT, double occ, int* reopened);
 __global__ void k_jacobi(DevBatch bt, const int* list, int max_sweeps, double rel_tol, double thr_scale,
                          double cap_err, int* sweeps_out);
 // LDS layout of k_jacobi_lds for an n x n system: packed strict upper

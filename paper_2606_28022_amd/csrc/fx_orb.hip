@@ -375,11 +375,11 @@ template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const 
 // After a solve: the gap of the systems that converged in a rotation from the
 // expectation values C_i^T F C_i of the orbitals whose last eigenvalue lies
 // within 0.05 Eh of the gap's edges.  Where it no longer keeps the
-// occupations at 0 and 2 to 1e-10, the system leaves the rotation route for
+// occupations at 0 and 2 to 2 occ, the system leaves the rotation route for
 // good (mode 2) and becomes active again; *reopened counts them.
 // Bound by the chain of orbitals, one product with F each: sixteen waves (four
 // took 162 us for 13 pentacene pairs and 1.5 ms for 3425; now 85 us and 1.2 ms).
-__global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, double kT, int* reopened) {
+__global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, double kT, double occ, int* reopened) {
   const int si = list[blockIdx.x];
   if (bt.status[si] != 1 || !(bt.xn[si] >= 0.0)) return;
   const SysDesc d = bt.desc[si];
@@ -421,7 +421,7 @@ __global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, d
     if (k < no) ho = fmax(ho, v);
     else lu = fmin(lu, v);
   }
-  if (threadIdx.x == 0 && !(exp(-0.5 * (lu - ho) / kT) <= 1e-10)) {
+  if (threadIdx.x == 0 && !(exp(-0.5 * (lu - ho) / kT) <= occ)) {
     bt.mode[si] = 2;
     bt.status[si] = 0;
     atomicAdd(reopened, 1);

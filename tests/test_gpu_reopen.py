@@ -1,0 +1,88 @@
+"""Rotated solves whose gap closes on the way (reopened by the eigensolver), and a monomer loop whose converged step has no gap any
+more; against the eigensolver throughout (FX_OV=0).  Both sides converge the
+charges to 1e-10; the energies are stationary in them, the gradient is first
+order in the density."""
+
+import json
+import os
+
+import numpy as np
+import pytest
+
+import workloads as w
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(kind):
+    if kind == "waters":  # monomers of 36 AOs, pairs of 72
+        return w.water_droplet(n=24, radius=5.55, seed=3).grouped(6)
+    if kind == "anthracene":
+        return w.anthracene_crystal(reps=(1, 1, 2), sigma=0.05, seed=1)
+    return w.pentacene_crystal(reps=(1, 1, 2), sigma=0.05, seed=1)
+
+
+def _run(s, options=None, params_path=None, **env):
+    from paper_2606_28022_amd import FmoXtb
+    old = {k: os.environ.get(k) for k in env}
+    os.environ.update(env)
+    try:
+        c = FmoXtb(params_path=params_path)
+    finally:
+        for k, v in old.items():
+            os.environ.pop(k) if v is None else os.environ.__setitem__(k, v)
+    c.set_system(s.Z, s.xyz, s.frag, s.frag_charge)
+    c.set_options(**(options or {}))
+    r = c.run()
+    out = r, c.energies(), c.charges(), c.gradient()
+    c.close()
+    return out
+
+
+def _at_temperature(tmp_path, kelvin):
+    from paper_2606_28022_amd.binding import default_params_path
+    p = json.load(open(default_params_path()))
+    p["globals"]["Tel_K"] = kelvin
+    f = tmp_path / "params.json"
+    f.write_text(json.dumps(p))
+    return str(f)
+
+
+def _close(a, b):
+    assert abs(a[0]["e_total"] - b[0]["e_total"]) < 1e-9
+    for x, y in zip(a[1], b[1]):
+        assert x.size == 0 or np.abs(x - y).max() < 1e-9
+    assert np.abs(a[2] - b[2]).max() < 1e-9
+    assert np.abs(a[3] - b[3]).max() < 5e-9
+
+
+# FX_OV_OCC=0: no gap is wide enough at the end, every rotated solve reopens
+@pytest.mark.parametrize("kind,order", [("waters", 2), ("anthracene", 2), ("anthracene", 3), ("pentacene", 2)])
+def test_reopened_solves(kind, order, capfd):
+    s = _system(kind)
+    a = _run(s, dict(order=order), FX_OV_OCC="0")
+    b = _run(s, dict(order=order), FX_OV="0")
+    _close(a, b)
+    # the first residuals are the first solve's, not the reopened one's
+    assert a[0]["first_residual_median"] == _run(s, dict(order=order))[0]["first_residual_median"]
+    capfd.readouterr()
+    _run(s, dict(order=order), FX_OV_OCC="0", FX_VERBOSE="1")
+    assert "systems reopened" in capfd.readouterr().err
+
+
+def test_reopened_solves_by_every_schedule():
+    from paper_2606_28022_amd.binding import FX_BATCHED, FX_BATCHED_GRAPH, FX_BATCHED_HOST_SYNC, FX_PLAIN_LOOP
+    s = _system("waters")
+    ref = _run(s, dict(schedule=FX_BATCHED), FX_OV_OCC="0")
+    for k in (FX_PLAIN_LOOP, FX_BATCHED_GRAPH, FX_BATCHED_HOST_SYNC):
+        x = _run(s, dict(schedule=k), FX_OV_OCC="0")
+        assert x[0]["e_total"] == ref[0]["e_total"]
+        assert np.array_equal(x[2], ref[2]) and np.array_equal(x[3], ref[3])
+
+
+@pytest.mark.parametrize("kelvin", [798.5, 799.8, 799.9, 800.0, 801.0])
+def test_converged_monomer_without_a_gap(kelvin, tmp_path):
+    """About 799.9 K one anthracene's gap is just wide enough for rotations when
+    the monomer loop starts and no longer when its step has converged."""
+    s, p = _system("anthracene"), _at_temperature(tmp_path, kelvin)
+    _close(_run(s, None, p), _run(s, None, p, FX_OV="0"))
