@@ -1525,9 +1525,13 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
     iters += niter[s];
   }
   if (iters_out) *iters_out += iters;
-  // (systems whose gap closed on the way: the eigensolver from here on)
+  // (systems whose gap closed on the way: the eigensolver from here on, in the
+  // eigenvectors of the last Fock matrix; the rotations left couplings inside
+  // the classes that the one or two sweeps of an iteration this close to the
+  // solution would not all remove, and W = C n eps C^T sees them to first order)
   if (!again.empty()) {
     if (verbose) std::fprintf(stderr, "[fx] %d of %d systems reopened: gap closed\n", (int)again.size(), nl);
+    diagonalise_last(b, again);
     const bool first = first_solve;
     first_solve = false;  // (its residuals and its fallback are behind)
     failed += run_scc(b, again, false, iters_out);
@@ -1715,18 +1719,12 @@ void Ctx::ensure_density(Batch& b) {
   b.p_valid = true;
 }
 
-bool Ctx::canonical_basis(Batch& b) {
-  if (!ov_batch(b) || b.nsys == 0) return true;
-  std::vector<double> xn;
-  fetch(b.xn, xn);
-  std::vector<int> l;
-  for (int s = 0; s < b.nsys; ++s)
-    if (xn[s] >= 0.0) l.push_back(s);
-  if (l.empty()) return true;
+// Eigenvectors and eigenvalues of the last iteration's Fock matrix (in F) for
+// the listed systems, and the occupations that follow
+void Ctx::diagonalise_last(Batch& b, const std::vector<int>& l) {
   const int nl = (int)l.size();
   DevBatch db = b.dev();
   DevSystem ds = dev_system();
-  ensure_density(b);  // (of the orbitals that gave the charges)
   put(b.d_list, l);
   hipLaunchKernelGGL(k_reset_state, dim3((nl + 255) / 256), dim3(256), 0, stream, db, b.d_list.p, nl, 1, 0);
   JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);
@@ -1736,12 +1734,23 @@ bool Ctx::canonical_basis(Batch& b) {
       (long long)std::max(jacobi_max_log, cold_log()) * jacobi_rot_log_entries(b.max_nao);
   b.rotlog.alloc((long long)b.nsys * stride);
   b.nlog.alloc(b.nsys);
-  // (F holds the last iteration's Fock matrix)
   gemm_batch(b, db, nl, b.d_list.p, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(l), 1);
   gemm_batch(b, db, nl, b.d_list.p, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(l), 1, jp.elt != 0 ? 2 : 1);
   rot_passes(b, db, b.d_list.p, nl, jp, 1e300, rot_shape(b, db, b.d_list.p, nl, jp, 1e300, stride, false), stride, true);
   hipLaunchKernelGGL(k_fermi, dim3(nl), dim3(256), 0, stream, ds, db, b.d_list.p, 1);
   check(hipGetLastError(), "canonical basis");
+}
+
+bool Ctx::canonical_basis(Batch& b) {
+  if (!ov_batch(b) || b.nsys == 0) return true;
+  std::vector<double> xn;
+  fetch(b.xn, xn);
+  std::vector<int> l;
+  for (int s = 0; s < b.nsys; ++s)
+    if (xn[s] >= 0.0) l.push_back(s);
+  if (l.empty()) return true;
+  ensure_density(b);  // (of the orbitals that gave the charges)
+  diagonalise_last(b, l);
   std::vector<int> mode;
   fetch(b.mode, mode);
   bool gapped = true;
