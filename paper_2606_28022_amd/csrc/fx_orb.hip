@@ -372,27 +372,36 @@ template __global__ void k_ov_apply<1, 2>(DevBatch, const int*, int, int, const 
 template __global__ void k_ov_apply<1, 3>(DevBatch, const int*, int, int, const double*, const double*, double);
 template __global__ void k_ov_apply<2, 2>(DevBatch, const int*, int, int, const double*, const double*, double);
 
-// After a solve: the gap of the systems that converged in a rotation from the
-// expectation values C_i^T F C_i of the orbitals whose last eigenvalue lies
-// within 0.05 Eh of the gap's edges.  Where it no longer keeps the
-// occupations at 0 and 2 to 2 occ, the system leaves the rotation route for
-// good (mode 2) and becomes active again; *reopened counts them.
-// Bound by the chain of orbitals, one product with F each: sixteen waves (four
-// took 162 us for 13 pentacene pairs and 1.5 ms for 3425; now 85 us and 1.2 ms).
+// After a solve: the gap of the systems that converged in a rotation.  The
+// couplings A_kj inside the classes, which the rotations leave, move the levels
+// to second order, about as much as the expectation values A_kk have moved (1e-3
+// Eh in pentacene pairs), so a level is taken as A_kk and, towards the gap, the
+// sum of min(|A_kj|, A_kj^2 / |eps_k - eps_j|) over its class, for the orbitals
+// whose last eigenvalue eps lies within 0.05 Eh of the gap's edges.  Where the
+// gap no longer keeps the occupations at 0 and 2 to 2 occ, the system leaves the
+// rotation route for good (mode 2) and becomes active again; *reopened counts
+// them.
+// (The true gap is met to 2e-4 Eh in pentacene pairs and to 1e-3 in pairs of six
+// waters; the expectation values alone missed it by 1e-3 and 4e-3.)
+// Bound by the chain of orbitals, a product with F and one with the class
+// each: sixteen waves, 0.12 ms for 13 pentacene pairs and 2.05 ms for 3425 (without
+// the couplings 0.085 and 1.2; four waves without them 0.16 and 1.5).
 __global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, double kT, double occ, int* reopened) {
   const int si = list[blockIdx.x];
   if (bt.status[si] != 1 || !(bt.xn[si] >= 0.0)) return;
   const SysDesc d = bt.desc[si];
   const int n = d.nao, no = bt.ov_no[si];
   const double* eps = bt.eps + d.ao_off;
-  const int* ox = bt.ov_idx + d.ao_off;
+  const int* ov = bt.ov_idx + d.ao_off;
   const double* F = bt.F + d.mat_off;
   const double* Ct = bt.Ct + d.mat_off;
-  __shared__ double red[16];
-  __shared__ double crow[MAXN];
+  __shared__ double diag, shift[16], crow[OV_MAXN], u[OV_MAXN], es[OV_MAXN];
+  __shared__ int ox[OV_MAXN];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __shared__ double es[MAXN];
-  for (int k = threadIdx.x; k < n; k += blockDim.x) es[k] = eps[ox[k]];
+  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    ox[k] = ov[k];
+    es[k] = eps[ox[k]];
+  }
   __syncthreads();
   double homo = -1e300, lumo = 1e300;
   for (int k = 0; k < n; ++k) {
@@ -401,25 +410,37 @@ __global__ void __launch_bounds__(1024) k_ov_gap(DevBatch bt, const int* list, d
   }
   double ho = -1e300, lu = 1e300;
   for (int k = 0; k < n; ++k) {
-    const int o = ox[k];
     const double e = es[k];
     if (k < no ? e < homo - 0.05 : e > lumo + 0.05) continue;
-    for (int j = threadIdx.x; j < n; j += blockDim.x) crow[j] = Ct[(long long)o * n + j];
+    for (int j = threadIdx.x; j < n; j += blockDim.x) crow[j] = Ct[ox[k] * n + j];
     __syncthreads();
-    double v = 0.0;
     for (int r = wave; r < n; r += nw) {
       double t = 0.0;
-      for (int j = lane; j < n; j += 64) t = fma(F[(long long)r * n + j], crow[j], t);
-      v = fma(crow[r], t, v);
+      for (int j = lane; j < n; j += 64) t = fma(F[r * n + j], crow[j], t);
+      t = wave_sum_f64(t);
+      if (lane == 0) u[r] = t;
     }
-    v = wave_sum_f64(v);
-    if (lane == 0) red[wave] = v;
     __syncthreads();
-    v = 0.0;
-    for (int w = 0; w < nw; ++w) v += red[w];
+    double sh = 0.0;
+    for (int c = (k < no ? 0 : no) + wave; c < (k < no ? no : n); c += nw) {
+      double t = 0.0;
+      for (int j = lane; j < n; j += 64) t = fma(Ct[ox[c] * n + j], u[j], t);
+      t = fabs(wave_sum_f64(t));
+      if (c != k) sh += fmin(t, t * t / fabs(e - es[c]));
+    }
+    if (lane == 0) shift[wave] = sh;
+    if (wave == 0) {
+      double t = 0.0;
+      for (int j = lane; j < n; j += 64) t = fma(crow[j], u[j], t);
+      t = wave_sum_f64(t);
+      if (lane == 0) diag = t;
+    }
     __syncthreads();
-    if (k < no) ho = fmax(ho, v);
-    else lu = fmin(lu, v);
+    sh = 0.0;
+    for (int w = 0; w < nw; ++w) sh += shift[w];
+    if (k < no) ho = fmax(ho, diag + sh);
+    else lu = fmin(lu, diag - sh);
+    __syncthreads();  // (diag, shift, crow and u have been read)
   }
   if (threadIdx.x == 0 && !(exp(-0.5 * (lu - ho) / kT) <= occ)) {
     bt.mode[si] = 2;

@@ -1,9 +1,11 @@
-"""Rotated solves whose gap closes on the way (reopened by the eigensolver), and a monomer loop whose converged step has no gap any
+"""Rotated solves whose gap closes on the way (reopened by the eigensolver), the
+test of the gap itself, and a monomer loop whose converged step has no gap any
 more; against the eigensolver throughout (FX_OV=0).  Both sides converge the
 charges to 1e-10; the energies are stationary in them, the gradient is first
 order in the density."""
 
 import json
+import math
 import os
 
 import numpy as np
@@ -12,6 +14,7 @@ import pytest
 import workloads as w
 
 pytestmark = pytest.mark.gpu
+KB = 3.166811563e-6  # Eh per K
 
 
 def _system(kind):
@@ -82,6 +85,17 @@ def test_reopened_solves_by_every_schedule():
         x = _run(s, dict(schedule=k), FX_OV_OCC="0")
         assert x[0]["e_total"] == ref[0]["e_total"]
         assert np.array_equal(x[2], ref[2]) and np.array_equal(x[3], ref[3])
+
+
+def test_gap_sees_couplings_inside_a_class(tmp_path, capfd):
+    """The six pairs' gaps: 0.31328, 0.29690, 0.30678, 0.30660, 0.31090, 0.30762
+    Eh; the fourth's expectation values alone give 0.31033.  A limit of 0.3090
+    (as an occupation at 1500 K) reopens four of them."""
+    s = _system("waters")
+    p = _at_temperature(tmp_path, 1500.0)
+    a = _run(s, None, p, FX_OV_OCC=repr(math.exp(-0.5 * 0.3090 / (KB * 1500.0))), FX_VERBOSE="1")
+    assert "4 of 6 systems reopened" in capfd.readouterr().err
+    _close(a, _run(s, None, p, FX_OV="0"))
 
 
 @pytest.mark.parametrize("kelvin", [798.5, 799.8, 799.9, 800.0, 801.0])
