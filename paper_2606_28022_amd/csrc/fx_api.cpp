@@ -843,7 +843,8 @@ JacobiPlan Ctx::jacobi_plan(int n, bool fp64_only, bool prefer_fp32) const {
 // Eigenpairs of symmetric matrices with the eigensolver of the SCC: a cold
 // solve to convergence, then one iteration of the form every later SCC
 // iteration runs (A' = V A V^T rebuilt in FP64 on the matrix cores, the
-// rotation kernel on the LDS working matrix, the apply kernel on V).  The cold
+// rotation kernel on the LDS working matrix, the apply kernel on V), with V
+// made orthonormal to rounding between them.  The cold
 // solve takes passes of that same split form, a few sweeps each, until a pass
 // ends on a sweep without rotations; where the split form has no plan, the
 // LDS-resident kernel, which keeps V in global memory and reads and writes it
@@ -892,6 +893,17 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
   DevBatch db = b.dev();
   hipLaunchKernelGGL(k_identity, dim3(nmat, 8), dim3(256), 0, stream, db, b.Ct.p);
   const JacobiPlan jp = global_kernel ? JacobiPlan{} : jacobi_plan(b.max_nao, false, false);
+  // the thousands of rotations of a row leave V V^T off unity by 1e-13, and the
+  // eigenvalues with it: V <- V + (1 - V V^T) V / 2
+  auto orthonormal = [&]() {
+    const unsigned g = (unsigned)((mat + 255) / 256);
+    gemm_batch(b, db, nmat, b.d_list.p, 1, b.Ct.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(all), 0, 1);
+    gemm_batch(b, db, nmat, b.d_list.p, 0, b.Fm.p, b.Ct.p, b.Tm.p, nullptr, b.gemm_gflop(all), 0);
+    hipLaunchKernelGGL(k_axpy, dim3(g), dim3(256), 0, stream, mat, (const double*)b.Ct.p, -1.0,
+                       (const double*)b.Tm.p, b.Fm.p);
+    hipLaunchKernelGGL(k_axpy, dim3(g), dim3(256), 0, stream, mat, (const double*)b.Ct.p, 0.5,
+                       (const double*)b.Fm.p, b.Ct.p);
+  };
   if (jp.elt == 0) {
     DevBuf<int> dn;
     put(dn, nv);
@@ -901,6 +913,7 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
     hipLaunchKernelGGL(k_eigh_batched, dim3(nmat), dim3(256), 0, stream, dn.p, doff.p, b.Fm.p, b.Ct.p, b.eps.p,
                        dwoff.p, 60, 1e-15);
     check(hipGetLastError(), "k_eigh_batched");
+    orthonormal();
   } else {
     const int m4 = (b.max_nao + 3) & ~3;
     const bool split_ok = (long long)apply_rot_lds_bytes(b.max_nao) <= lds_max &&
@@ -921,6 +934,7 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
     else
       hipLaunchKernelGGL(k_jacobi_lds<float>, dim3(nmat), dim3(jp.threads), jp.lds, stream, db, b.d_list.p,
                          jacobi_max_sweeps, jacobi_tol, jacobi_thr_scale, 1e300, b.sweeps.p, jp.chunk);
+    orthonormal();
     check(hipGetLastError(), "cold eigensolver");
     // the warm iteration: A' = V A V^T (FP64), then rotations and their
     // application to V
