@@ -955,6 +955,7 @@ void Ctx::eigh_hot(const std::vector<int>& nv, const double* A, double* w, doubl
   b.eps.download_raw(w, ao, stream);
   b.Ct.download_raw(V, mat, stream);
   sync();
+  timers.drop();
 }
 
 void Ctx::build_matrices(Batch& b, bool from_mono) {
@@ -2449,6 +2450,7 @@ void Ctx::run(fx_result* out) {
   if (NB > 0 && opt.want_gradient && opt.order >= 3)
     throw FxError(FX_E_UNSUPPORTED, "the FMO3 gradient with cut covalent bonds is not available");
   std::memset(&res, 0, sizeof(res));
+  timers.drop();  // (of component calls, or of a run that failed on the way)
   ktimers.clear();
   resp_ok = false;
   bool all_conv = true;
@@ -3177,6 +3179,7 @@ int fx_embedding_field(fx_ctx* ctx, const double* dq, double* phi) {
     c.field(q.p, p.p, c.opt.precision == FX_MIXED);
     p.download_raw(phi, c.Nsh, c.stream);
     c.sync();
+    c.timers.drop();
   });
 }
 

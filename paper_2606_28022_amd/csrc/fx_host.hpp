@@ -558,6 +558,8 @@ struct Ctx {
       }
       used = 0;
     }
+    // launches outside a run belong to no fx_result
+    void drop() { used = 0; }
   } timers;
 
 
