@@ -600,7 +600,7 @@ void Ctx::launch_resp_M(const Batch& b, const DevBatch& db, const int* order, co
                         const double* Q, double* M) {
   int nsh = 0;
   for (const auto& d : b.h_desc) nsh = std::max(nsh, d.nsh);
-  if (!launch_resp_M_mfma(b.nsys, n_cu, lds_max, stream, db, nsh, order, nocc, qoff, Q, M))
+  if (!launch_resp_M_mfma(b.nsys, n_cu, lds_max, resp_M_form, stream, db, nsh, order, nocc, qoff, Q, M))
     hipLaunchKernelGGL(k_resp_M, dim3(b.nsys), dim3(256), resp_M_lds(b), stream, db, order, nocc, qoff, Q, M);
 }
 

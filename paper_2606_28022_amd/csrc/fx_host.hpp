@@ -499,6 +499,9 @@ struct Ctx {
   bool monomer_response_setup();
   // dynamic LDS of k_resp_M for a batch (throws when a system is too large)
   unsigned resp_M_lds(const Batch& b) const;
+  // FX_RESP_M forces the form of the susceptibility launch (0, 1 or 2:
+  // launch_resp_M_mfma) for a test
+  int resp_M_form = std::getenv("FX_RESP_M") ? std::atoi(std::getenv("FX_RESP_M")) : -1;
   void launch_resp_M(const Batch& b, const DevBatch& db, const int* order, const int* nocc, const long long* qoff,
                      const double* Q, double* M);
   void build_precond(Batch& b);
@@ -655,12 +658,13 @@ struct Ctx {
   // Work-groups per system for kernels whose loops over a system's elements
   // or atom pairs can be cut anywhere: one where the batch alone covers the
   // chip (the loop's setup is then paid once), up to eight where it does not,
-  // as long as every slice keeps 32 rows (FX_SLICES: at most that many).
+  // as long as every slice keeps 32 rows (a power of two; FX_SLICES: at most
+  // that many, 1 also one for the pair kernels).
   // 8 pentacenes, one or four: transition charges 270 -> 105 us.
   int max_slices = std::getenv("FX_SLICES") ? std::atoi(std::getenv("FX_SLICES")) : 8;
   int slices(const Batch& b, int nsys) const {
     int s = 1;
-    while (s < max_slices && 2LL * s * nsys <= 2LL * n_cu && b.max_nao > 32 * s) s *= 2;
+    while (2 * s <= max_slices && 2LL * s * nsys <= 2LL * n_cu && b.max_nao > 32 * s) s *= 2;
     return s;
   }
   DevBuf<double> erep_part;

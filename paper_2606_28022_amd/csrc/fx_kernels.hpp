@@ -243,7 +243,7 @@ __global__ void k_resp_M(DevBatch bt, const int* order, const int* nocc, const l
 size_t resp_M_lds_bytes(int nsh);
 // k_resp_M_mfma: systems of at most 16 RMM_MAXB shells
 constexpr int RMM_MAXB = 8;
-bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, hipStream_t stream, const DevBatch& bt, int nsh,
+bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, int form, hipStream_t stream, const DevBatch& bt, int nsh,
                         const int* order, const int* nocc, const long long* qoff, const double* Q, double* M);
 constexpr int RQ_CH = 16;        // AOs per staged run of k_resp_Q
 size_t resp_Q_lds_bytes(int n);  // dynamic LDS of k_resp_Q for systems of up to n AOs

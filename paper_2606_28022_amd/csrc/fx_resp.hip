@@ -293,11 +293,13 @@ __global__ void __launch_bounds__(256, 2) k_resp_M_mfma(DevBatch bt, const int* 
 
 // A block per wave where that fits the idle CUs (two work-groups each), else
 // a quarter of the blocks per wave.
-bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, hipStream_t stream, const DevBatch& bt, int nsh,
+// (form: 0 not at all, 1 one work-group per system, 2 a block per wave, else
+// by this rule)
+bool launch_resp_M_mfma(int nsys, int n_cu, int lds_max, int form, hipStream_t stream, const DevBatch& bt, int nsh,
                         const int* order, const int* nocc, const long long* qoff, const double* Q, double* M) {
   const int nb = (nsh + 15) / 16, wg = (nb * (nb + 1) / 2 + 3) / 4;
-  if (nb > RMM_MAXB || (16 * nb * RMM_LD + RM_KC + MAXN) * (int)sizeof(double) > lds_max) return false;
-  const bool split = (long long)wg * nsys <= 2LL * n_cu;
+  if (form == 0 || nb > RMM_MAXB || (16 * nb * RMM_LD + RM_KC + MAXN) * (int)sizeof(double) > lds_max) return false;
+  const bool split = form == 1 || form == 2 ? form == 2 : (long long)wg * nsys <= 2LL * n_cu;
   auto go = [&](auto* whole, auto* one) {
     hipLaunchKernelGGL(split ? one : whole, dim3(nsys, split ? wg : 1), dim3(256), 0, stream, bt, order, nocc, qoff, Q,
                        M);
