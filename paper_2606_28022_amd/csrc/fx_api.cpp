@@ -1546,7 +1546,7 @@ int Ctx::run_scc(Batch& b, const std::vector<int>& list, bool cold, long long* i
   // solution would not all remove, and W = C n eps C^T sees them to first order)
   if (!again.empty()) {
     if (verbose) std::fprintf(stderr, "[fx] %d of %d systems reopened: gap closed\n", (int)again.size(), nl);
-    diagonalise_last(b, again);
+    diagonalise_last(b, again, jacobi_max_log);  // (in the log the iterations had)
     const bool first = first_solve;
     first_solve = false;  // (its residuals and its fallback are behind)
     failed += run_scc(b, again, false, iters_out);
@@ -1642,14 +1642,15 @@ double Ctx::small_gflop(const Batch& b, const std::vector<int>& list, const std:
   return g;
 }
 
-// Passes of up to jacobi_cold_log logged sweeps over the na systems listed in
+// Passes of up to `log` logged sweeps (0: cold_log()) over the na systems listed in
 // dl, whose A = C^T F C is in F; a system whose pass ended on a sweep without
 // rotations (fewer logged sweeps than the pass allows) is done, the others
 // start the next pass from C^T F C in the basis this pass left (the Fock
 // matrix is rebuilt: the products overwrite it; or taken from F where the
 // caller has it).
 void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
-                     const RotShape& rs, long long stride, bool timed, const double* F) {
+                     const RotShape& rs, long long stride, bool timed, const double* F, int log) {
+  if (log <= 0) log = cold_log();
   const DevSystem ds = dev_system();
   KernelTimer* kt_rot = kt(jp.elt == 8 ? "fx::k_jacobi_rot<double>" : "fx::k_jacobi_rot<float>");
   KernelTimer* kt_app = kt(apply_dual(b.max_nao) ? "fx::k_apply_rot_dual" : "fx::k_apply_rot");
@@ -1658,7 +1659,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
   check(hipMemcpyAsync(todo.data(), dl, sizeof(int) * na, hipMemcpyDeviceToHost, stream), "list copy");
   const int* dt = dl;
   DevBuf<int> pass_list;
-  const int max_pass = (jacobi_max_sweeps + cold_log() - 1) / cold_log();
+  const int max_pass = (jacobi_max_sweeps + log - 1) / log;
   for (int pass = 0; pass < max_pass && !todo.empty(); ++pass) {
     const int nt = (int)todo.size();
     if (pass > 0) {
@@ -1669,7 +1670,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
       gemm_batch(b, db, nt, dt, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, 0.0, 1, sym_A);
     }
     int ev = timed ? timers.begin(stream) : -1;
-    launch_rot(b, db, dt, nt, jp.elt, cap, rs, stride, cold_log());
+    launch_rot(b, db, dt, nt, jp.elt, cap, rs, stride, log);
     if (timed) timers.end(stream, ev, kt_rot, 0.0);
     ev = timed ? timers.begin(stream) : -1;
     launch_apply(b, db, dt, nt, stride);
@@ -1677,7 +1678,7 @@ void Ctx::rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const 
     fetch(b.nlog, nlog);
     std::vector<int> next;
     for (int s : todo)
-      if (nlog[s] >= cold_log()) next.push_back(s);
+      if (nlog[s] >= log) next.push_back(s);
     // (given matrices: all of them while one is left, which costs no time: an
     // FP32 working matrix sees levels 1e-9 apart only through the rebuilds)
     if (!F || next.empty()) todo.swap(next);
@@ -1735,8 +1736,8 @@ void Ctx::ensure_density(Batch& b) {
 }
 
 // Eigenvectors and eigenvalues of the last iteration's Fock matrix (in F) for
-// the listed systems, and the occupations that follow
-void Ctx::diagonalise_last(Batch& b, const std::vector<int>& l) {
+// the listed systems, and the occupations that follow, by passes of `log` sweeps
+void Ctx::diagonalise_last(Batch& b, const std::vector<int>& l, int log) {
   const int nl = (int)l.size();
   DevBatch db = b.dev();
   DevSystem ds = dev_system();
@@ -1745,13 +1746,13 @@ void Ctx::diagonalise_last(Batch& b, const std::vector<int>& l) {
   JacobiPlan jp = jacobi_plan(b.max_nao, b.has_hop, false);
   auto itp = tuned.find(jp_key(b.max_nao, jp.elt));
   if (itp != tuned.end()) jp = itp->second;
-  const long long stride =
-      (long long)std::max(jacobi_max_log, cold_log()) * jacobi_rot_log_entries(b.max_nao);
+  const long long stride = (long long)log * jacobi_rot_log_entries(b.max_nao);
   b.rotlog.alloc((long long)b.nsys * stride);
   b.nlog.alloc(b.nsys);
   gemm_batch(b, db, nl, b.d_list.p, 0, b.Ct.p, b.Fm.p, b.Tm.p, nullptr, b.gemm_gflop(l), 1);
   gemm_batch(b, db, nl, b.d_list.p, 1, b.Tm.p, b.Ct.p, b.Fm.p, nullptr, b.gemm_gflop_sym(l), 1, jp.elt != 0 ? 2 : 1);
-  rot_passes(b, db, b.d_list.p, nl, jp, 1e300, rot_shape(b, db, b.d_list.p, nl, jp, 1e300, stride, false), stride, true);
+  rot_passes(b, db, b.d_list.p, nl, jp, 1e300, rot_shape(b, db, b.d_list.p, nl, jp, 1e300, stride, false), stride, true,
+             nullptr, log);
   hipLaunchKernelGGL(k_fermi, dim3(nl), dim3(256), 0, stream, ds, db, b.d_list.p, 1);
   check(hipGetLastError(), "canonical basis");
 }
@@ -1765,7 +1766,7 @@ bool Ctx::canonical_basis(Batch& b) {
     if (xn[s] >= 0.0) l.push_back(s);
   if (l.empty()) return true;
   ensure_density(b);  // (of the orbitals that gave the charges)
-  diagonalise_last(b, l);
+  diagonalise_last(b, l, std::max(jacobi_max_log, cold_log()));
   std::vector<int> mode;
   fetch(b.mode, mode);
   bool gapped = true;

@@ -699,10 +699,10 @@ struct Ctx {
   // a rotation; false when one of them has no gap any more (it is then left to
   // the eigensolver, mode 2)
   bool canonical_basis(Batch& b);
-  void diagonalise_last(Batch& b, const std::vector<int>& l);
+  void diagonalise_last(Batch& b, const std::vector<int>& l, int log);
   // passes of logged sweeps to convergence (cold solves by the split form)
   void rot_passes(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
-                  const RotShape& rs, long long stride, bool timed, const double* F = nullptr);
+                  const RotShape& rs, long long stride, bool timed, const double* F = nullptr, int log = 0);
   void launch_apply(const Batch& b, const DevBatch& db, const int* dl, int na, long long log_stride);
   RotShape rot_shape(Batch& b, const DevBatch& db, const int* dl, int na, const JacobiPlan& jp, double cap,
                      long long log_stride, bool may_tune);

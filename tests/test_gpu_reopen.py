@@ -87,6 +87,28 @@ def test_reopened_solves_by_every_schedule():
         assert np.array_equal(x[2], ref[2]) and np.array_equal(x[3], ref[3])
 
 
+@pytest.mark.parametrize("kind", ["waters", "pentacene"])
+def test_reopening_needs_no_more_memory(kind):
+    """A workspace sized by a run in which nothing reopened serves one in which
+    something does (4 MiB and 1/32 are the margin of fx_workspace_size)."""
+    from paper_2606_28022_amd import FmoXtb
+    s = _system(kind)
+    need = []
+    for env in ({}, {"FX_OV_OCC": "0"}):
+        os.environ.update(env)
+        try:
+            c = FmoXtb()
+        finally:
+            for k in env:
+                os.environ.pop(k)
+        c.set_system(s.Z, s.xyz, s.frag, s.frag_charge)
+        c.run()
+        need.append(c.workspace_size())
+        c.close()
+    margin = (4 << 20) + need[0] / 32
+    assert need[1] - need[0] < margin
+
+
 def test_gap_sees_couplings_inside_a_class(tmp_path, capfd):
     """The six pairs' gaps: 0.31328, 0.29690, 0.30678, 0.30660, 0.31090, 0.30762
     Eh; the fourth's expectation values alone give 0.31033.  A limit of 0.3090
