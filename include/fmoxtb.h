@@ -98,7 +98,9 @@ typedef struct fx_options {
                              tolerances.  In both forms the Jacobi working
                              matrix of systems too large for an FP64 copy in
                              LDS (more than about 180 AOs) is stored in FP32
-                             between FP64 rebuilds of C^T F C. */
+                             between FP64 rebuilds of C^T F C.  FX_MIXED is the
+                             slower form on the crystals measured (660
+                             pentacenes: 0.278 s a step against 0.221). */
   int32_t schedule;       /* FX_BATCHED (device-compacted active lists),
                              FX_BATCHED_HOST_SYNC, FX_BATCHED_GRAPH or
                              FX_PLAIN_LOOP (one fragment at a time) */
@@ -111,7 +113,13 @@ typedef struct fx_options {
   int32_t guess_max_iter; /* learned guess: a monomer not converged after this
                              many iterations of its first solve restarts from
                              superposition charges (<= 1: never) */
-  double scc_tol;         /* SCC convergence: max |dq_out - dq_in| */
+  double scc_tol;         /* SCC convergence: max |dq_out - dq_in|.  A system of
+                             33 to 256 AOs without cut bonds whose Fermi
+                             occupations are within 2e-11 of 0 and 2 keeps
+                             these occupations (and their entropy term) from
+                             its last diagonalisation while its orbitals are
+                             rotated; at the solve's end its gap holds them to
+                             2e-10, or it goes on by diagonalisation */
   double energy_tol;      /* SCC convergence: |E_k - E_(k-1)| */
   double macro_tol;       /* monomer loop: max change of any monomer charge */
   int32_t max_iter;       /* SCC iterations per fragment solve */
@@ -218,7 +226,9 @@ typedef struct fx_result {
  * 4 MiB (launch shapes chosen by timing can change a few buffer sizes between
  * otherwise identical calls).  Typical use: fx_set_system and fx_run once
  * without a workspace, query the size, allocate it, call fx_set_workspace,
- * then fx_set_system again and run; repeating the same calls fits.
+ * then fx_set_system again and run; repeating the same calls fits.  A size
+ * holds for the library that reported it: ask again after an update (buffers
+ * change with the kernels).
  *
  * fx_set_workspace: dev_ptr is DEVICE memory on the context's device, at
  * least 256-byte aligned, `bytes` long; the caller keeps ownership and must

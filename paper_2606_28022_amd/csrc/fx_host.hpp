@@ -574,8 +574,7 @@ struct Ctx {
                   const int32_t* fchg, int32_t n_bonds, const int32_t* bonds);
   void build_lists_impl();
   void compute_cn();
-  // max |a - b| over n entries into out[0] (device), with extra its largest
-  // entry into out[1], and the Anderson mixing
+  // max |a - b| over n entries into *out (device), and the Anderson mixing
   // coefficients of the history residuals R (slots sl, n entries each)
   DevBuf<double> red_part;
   void max_absdiff(const double* a, const double* b, int n, double* out);
@@ -586,12 +585,14 @@ struct Ctx {
   // FP64 field passes (kg = 2) of up to this many atoms by the one-launch form
   // (a wave per target atom): a host call on 288 atoms takes 53 us by it and 96
   // by the symmetric form, 3,456 atoms 85 and 101, 4,608 atoms 113 and 132,
-  // 5,760 atoms 144 and 136
+  // 5,760 atoms 144 and 136; the allocation-free call 4.8 us by it and 29 by
+  // k_field_partial on 300 atoms, 17 and 42 on 2,001, 47 and 63 on 3,999, 67 and
+  // 77 on 4,899
+  int field_wave_max = std::getenv("FX_FIELD_WAVE_MAX") ? std::atoi(std::getenv("FX_FIELD_WAVE_MAX")) : 5000;
   // Fewest atoms of the allocation-free field's pass over super-block pairs
   // (kg = 2; tiles against k_field_partial: 6,000 atoms 0.157 and 0.107 ms,
   // 9,000 0.168 and 0.195, 12,000 0.293 and 0.307, 30,000 1.07 and 1.59)
   int field_tile_min = std::getenv("FX_FIELD_TILE_MIN") ? std::atoi(std::getenv("FX_FIELD_TILE_MIN")) : 9000;
-  int field_wave_max = std::getenv("FX_FIELD_WAVE_MAX") ? std::atoi(std::getenv("FX_FIELD_WAVE_MAX")) : 5000;
   void build_batch(Batch& b, const std::vector<std::array<int, 3>>& clusters, int nfrag_each);
   void build_matrices(Batch& b, bool from_mono = false);
   void eigh_hot(const std::vector<int>& nv, const double* A, double* w, double* V, bool global_kernel = false);

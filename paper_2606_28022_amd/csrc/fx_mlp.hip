@@ -32,7 +32,7 @@ __device__ inline float bf16r(float x) {
 // packed, and at the end, each lane evaluates one radial function (lane % 16)
 // for every fourth of them, so that the exponentials, which bound the kernel,
 // run with full waves.  (One thread per atom: 12 work-groups for 1,024 waters,
-// whose lanes diverge at every neighbour, 3.76 ms; this form 0.05 ms.)
+// whose lanes diverge at every neighbour, 3.76 ms; this form 0.022 ms.)
 __global__ void __launch_bounds__(256) k_mlp_features(DevSystem sys, float* out) {
   using namespace mlp;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

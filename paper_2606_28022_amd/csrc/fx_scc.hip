@@ -538,7 +538,11 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // of the slabs: loads, weights and padding blocks under conditions made every
 // slab wait for the next one's loads (mode 2 with populations: 254 us per
 // iteration of 3425 pentacene dimers on average, 11.8 us for 13); with neither
-// branch nor use of a load before its slab is stored, 217 and 9.7 us.
+// branch nor use of a load before its slab is stored, 217 and 9.7 us.  Mode 0
+// 12.9 -> 12.0 ms per step of these dimers, mode 1 9.1 -> 9.4, the one form that
+// lost.  Sizes just above a multiple of 64 gained too, though the padding blocks
+// are multiplied now (all products of waters by 6, 8 and 11, pairs of 72, 96 and
+// 132 AOs: 0.99 -> 0.92, 1.07 -> 0.96, 1.36 -> 1.24 ms).
 // WIN = 1 (modes 0 and 1, a two-fragment cluster whose basis rows are its
 // monomers' orbitals, block diagonal, the first fragment's AOs 0 .. n1 - 1):
 // only the output rows >= n1 and columns < n1 are needed (the fragment-pair
